@@ -4,7 +4,7 @@
 //
 //   * rows_of_edges: the destination row of every forward CSR position (the
 //     keys the transposed CSR is sorted by carry it as payload), one
-//     wavefront per 64 rows.
+//     wavefront per 1024 positions.
 //   * scale_inv_deg: grad_out / in-degree per destination row, the input of
 //     the gradient of mean.
 //   * spmm_grad_w: the gradient with respect to the edge weights, one dot
@@ -40,42 +40,89 @@ __device__ inline int64_t rp_at(const void* rp, int rp64, int64_t i) {
     return rp64 ? static_cast<const int64_t*>(rp)[i] : (int64_t) static_cast<const int32_t*>(rp)[i];
 }
 
-// row[p] = the v with rowptr[v] <= p < rowptr[v+1].  Each wavefront takes 64
-// consecutive rows: it stages their 65 bounds in LDS, then writes the
-// positions from its first row's start to its last row's end 64 at a time
-// (one store instruction each, however long or short the rows), each lane
-// finding the row of its position by a binary search over the staged
-// bounds.  Bounds are read as 0 for row 0 and E for row N and clamped to
-// [0, E], so every position is written, with a row id below N, whatever the
+// row[p] = the v with rowptr[v] <= p < rowptr[v+1].  Bound by the 4-byte
+// stores (and, where rows are few next to positions, nothing else is read
+// more than once).  Each wavefront takes kRowsSpan consecutive POSITIONS
+// rather than consecutive rows, so a hub row is shared by many wavefronts: 64
+// rows per wavefront took 240 us on a power-law graph of 1.2M edges whose
+// largest row has 36k, all of it one wavefront's serial stores (now 12 us;
+// 124M edges of even rows 227 -> 180 us).  A wavefront finds the row of its first position by a
+// 64-way search (64 bounds per round trip, 4 rounds for 2.4M rows), then
+// stages the next kRowsBatch bounds in LDS, relative to its span, and each
+// lane searches them once per four consecutive positions, which it stores
+// together.  A batch without a single position of the span (empty rows) is
+// followed by another search instead of the next batch, so runs of empty rows
+// cost nothing.
+//
+// Bounds are read as 0 for row 0 and E for row N and clamped to [0, E], and
+// every position of the span is written, with a row id below N, whatever the
 // input (an inconsistent rowptr only makes ids wrong).
-template <typename IT>
+constexpr int kRowsSpan = 1024;   // positions per wavefront
+constexpr int kRowsBatch = 256;   // row bounds staged at a time
+
+template <typename IT, bool VEC>
 __global__ __launch_bounds__(kBlock) void rows_of_edges(const IT* __restrict__ rowptr, int64_t N,
                                                         int64_t E, int32_t* __restrict__ row) {
-    __shared__ int64_t s_b[kWavesPerBlock][kWave + 1];
+    __shared__ int32_t s_b[kWavesPerBlock][kRowsBatch];
     const int lane = threadIdx.x & (kWave - 1);
-    const int wl = threadIdx.x / kWave;
-    const int64_t v0 = ((int64_t)blockIdx.x * kWavesPerBlock + wl) * kWave;
-    if (v0 >= N) return;  // uniform per wavefront
-    auto bound = [&](int64_t v) -> int64_t {
-        if (v <= 0) return 0;
-        if (v >= N) return E;
-        const int64_t b = (int64_t)rowptr[v];
-        return b < 0 ? 0 : (b > E ? E : b);
-    };
-    s_b[wl][lane] = bound(v0 + lane);
-    if (lane == 0) s_b[wl][kWave] = bound(v0 + kWave);
-    // the wavefront reads what its own lanes wrote: LDS operations of one
-    // wavefront complete in order
-    __builtin_amdgcn_wave_barrier();
-    const int nr = (int)(N - v0 < kWave ? N - v0 : kWave);  // rows of this wavefront
-    const int64_t p1 = s_b[wl][nr];
-    for (int64_t p = s_b[wl][0] + lane; p < p1; p += kWave) {
-        int lo = 0, hi = nr - 1;  // the last row whose start is <= p
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_b[wl][mid] <= p) lo = mid; else hi = mid - 1;
+    const int wl = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int64_t p0 = ((int64_t)blockIdx.x * kWavesPerBlock + wl) * kRowsSpan;
+    if (p0 >= E) return;  // uniform per wavefront
+    const int span = (int)(E - p0 < kRowsSpan ? E - p0 : kRowsSpan);
+    int32_t* const bnd = s_b[wl];
+    int at = 0;  // positions p0 .. p0 + at - 1 are written
+    int64_t r = row_of_position(rowptr, N, E, p0, lane);
+    while (at < span) {
+        // bnd[i] = where row r + i + 1 starts, relative to p0 and cut to the span
+#pragma unroll
+        for (int k = 0; k < kRowsBatch / kWave; ++k) {
+            const int64_t b = row_bound(rowptr, N, E, r + 1 + k * kWave + lane) - p0;
+            bnd[k * kWave + lane] = (int32_t)(b < 0 ? 0 : (b > span ? span : b));
         }
-        row[p] = (int32_t)(v0 + lo);
+        // the wavefront reads what its own lanes wrote: LDS operations of one
+        // wavefront complete in order
+        __builtin_amdgcn_wave_barrier();
+        const int end = __builtin_amdgcn_readfirstlane(bnd[kRowsBatch - 1]);
+        const int nr = (int)(N - r < kRowsBatch ? N - r : kRowsBatch);  // rows of this batch
+        constexpr int V = VEC ? 4 : 1;
+        for (int q = (at & ~3) + lane * V; q < end; q += kWave * V) {
+            int lo = 0, hi = nr - 1;  // the first row whose end lies after q
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (bnd[mid] > q) hi = mid; else lo = mid + 1;
+            }
+            if constexpr (VEC) {
+                int4 v;
+                int32_t* const e = &v.x;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    while (lo < nr - 1 && bnd[lo] <= q + i) ++lo;
+                    e[i] = (int32_t)(r + lo);
+                }
+                if (q >= at && q + 4 <= end) {
+                    *reinterpret_cast<int4*>(row + p0 + q) = v;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (q + i >= at && q + i < end) row[p0 + q + i] = e[i];
+                }
+            } else if (q >= at) {
+                row[p0 + q] = (int32_t)(r + lo);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (end > at) {
+            at = end;
+            r = r + kRowsBatch < N ? r + kRowsBatch : N - 1;
+        } else {
+            // a batch of rows that end before position at: look it up
+            r = row_of_position(rowptr, N, E, p0 + at, lane);
+            if (row_bound(rowptr, N, E, r + 1) <= p0 + at) {
+                // only an inconsistent rowptr: finish the span with this id
+                for (int q = at + lane; q < span; q += kWave) row[p0 + q] = (int32_t)r;
+                at = span;
+            }
+        }
     }
 }
 
@@ -421,13 +468,15 @@ hipError_t launch_gw_epl(const GradWParams& p, int epl, unsigned grid, hipStream
 hipError_t launch_rows_of_edges(const void* rowptr, int rp64, int64_t N, int64_t E, int32_t* row,
                                 hipStream_t s) {
     if (E <= 0 || N <= 0) return hipSuccess;
-    const unsigned grid = (unsigned)ceil_div(ceil_div(N, kWave), kWavesPerBlock);
-    if (rp64)
-        hipLaunchKernelGGL(rows_of_edges<int64_t>, dim3(grid), dim3(kBlock), 0, s,
-                           static_cast<const int64_t*>(rowptr), N, E, row);
-    else
-        hipLaunchKernelGGL(rows_of_edges<int32_t>, dim3(grid), dim3(kBlock), 0, s,
-                           static_cast<const int32_t*>(rowptr), N, E, row);
+    const unsigned grid = (unsigned)ceil_div(ceil_div(E, kRowsSpan), kWavesPerBlock);
+    const bool vec = (uintptr_t)row % 16 == 0;  // four ids per store
+    const int64_t* r8 = static_cast<const int64_t*>(rowptr);
+    const int32_t* r4 = static_cast<const int32_t*>(rowptr);
+    const dim3 g(grid), b(kBlock);
+    if (rp64 && vec) hipLaunchKernelGGL((rows_of_edges<int64_t, true>), g, b, 0, s, r8, N, E, row);
+    else if (rp64) hipLaunchKernelGGL((rows_of_edges<int64_t, false>), g, b, 0, s, r8, N, E, row);
+    else if (vec) hipLaunchKernelGGL((rows_of_edges<int32_t, true>), g, b, 0, s, r4, N, E, row);
+    else hipLaunchKernelGGL((rows_of_edges<int32_t, false>), g, b, 0, s, r4, N, E, row);
     return hipGetLastError();
 }
 

@@ -216,6 +216,38 @@ struct SpmmParams {
     int32_t* part_amin;
 };
 
+// ---- rows of CSR positions ---------------------------------------------------
+// Start of row v (0 for row 0, E for row N and beyond), clamped to [0, E].
+template <typename IT>
+__device__ inline int64_t row_bound(const IT* __restrict__ rowptr, int64_t N, int64_t E, int64_t v) {
+    if (v <= 0) return 0;
+    if (v >= N) return E;
+    const int64_t b = (int64_t)rowptr[v];
+    return b < 0 ? 0 : (b > E ? E : b);
+}
+
+// The last row v in [0, N) that starts at or before position p (the row of p
+// when 0 <= p < E), found by the whole wavefront: every round splits the
+// candidates into 64 parts by one load per lane, so 2.4M rows take four
+// round trips.  p is the same in all lanes; all of them must be active.  The
+// number of rounds depends on N alone, so it ends whatever rowptr holds.
+template <typename IT>
+__device__ inline int64_t row_of_position(const IT* __restrict__ rowptr, int64_t N, int64_t E,
+                                          int64_t p, int lane) {
+    int64_t lo = 0, n = N;  // the row is one of lo .. lo + n - 1
+    while (n > 1) {
+        const int64_t step = (n + kWave - 1) / kWave;
+        // candidate starts lo + (lane + 1) * step, while they lie in the range
+        const int64_t c = (int64_t)(lane + 1) * step;
+        const bool le = c < n && row_bound(rowptr, N, E, lo + c) <= p;
+        const int k = __popcll(__ballot(le));
+        lo += (int64_t)k * step;
+        const int64_t left = n - (int64_t)k * step;
+        n = left < step ? left : step;
+    }
+    return lo;
+}
+
 // ---- backward (backward.hip) -----------------------------------------------
 struct GradWParams {
     const void* rowptr;

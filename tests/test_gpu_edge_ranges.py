@@ -1,0 +1,92 @@
+"""Kernels that cut the edge list into ranges of positions, at the sizes where
+a range's ends fall inside hub rows, on row ends and among empty rows: the row
+of every position (1024 positions per wavefront, 256 row bounds at a time) and
+the gradient of materialized messages (a row's first 256 or 1024 edges, then
+parts of that many).  Integers and copies are exact; the mean's quotient is
+correctly rounded."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_16991_amd as mp
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+@pytest.fixture(autouse=True)
+def _announce(request):
+    sys.stderr.write(f"\n[gpu-case] {request.node.nodeid}\n")
+    sys.stderr.flush()
+    yield
+    torch.cuda.synchronize()
+
+
+def degrees(name):
+    rng = np.random.default_rng(3)
+    if name == "one row":
+        return np.array([5000])
+    if name == "one edge":
+        return np.array([0, 0, 1, 0])
+    if name == "range ends":  # rows that end on and next to multiples of 1024 and 256
+        return np.array([1024, 1023, 1, 1025, 255, 256, 257, 0, 511, 1, 2048, 3])
+    if name == "hub among empty rows":
+        d = np.zeros(200_000, dtype=np.int64)
+        d[[7, 100_000, 100_001, 199_999]] = [3, 40_000, 1, 5]
+        return d
+    if name == "trailing empty rows":
+        return np.concatenate([np.full(300, 4), np.zeros(70_000, dtype=np.int64)])
+    if name == "degree one":
+        return np.ones(3000, dtype=np.int64)
+    return np.minimum(rng.zipf(1.3, 20_000), 30_000)  # power law
+
+
+NAMES = ["one row", "one edge", "range ends", "hub among empty rows", "trailing empty rows",
+         "degree one", "power law"]
+
+
+def rowptr_of(deg, dtype):
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    return rp, torch.from_numpy(rp).to(DEV, dtype)
+
+
+@pytest.mark.parametrize("name", NAMES)
+@pytest.mark.parametrize("itype", [torch.int32, torch.int64])
+@pytest.mark.parametrize("shift", [0, 1])  # ids stored four at a time, or one
+def test_row_of_every_position(name, itype, shift):
+    deg = degrees(name)
+    rp, rp_d = rowptr_of(deg, itype)
+    E, N = int(rp[-1]), len(deg)
+    buf = torch.full((E + shift + 8,), -7, dtype=torch.int32, device=DEV)
+    mp.mp_csr_rows(rp_d, mp.MP_I32 if itype == torch.int32 else mp.MP_I64, N, E,
+                   buf[shift:shift + E])
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[shift:shift + E], np.repeat(np.arange(N), deg))
+    assert (got[:shift] == -7).all() and (got[shift + E:] == -7).all()
+
+
+@pytest.mark.parametrize("name", NAMES)
+@pytest.mark.parametrize("reduce", ["sum", "mean", "max"])
+@pytest.mark.parametrize("F", [8, 7])
+def test_message_gradient(name, reduce, F):
+    deg = degrees(name)
+    rp, rp_d = rowptr_of(deg, torch.int64 if F == 7 else torch.int32)
+    E, N = int(rp[-1]), len(deg)
+    rng = np.random.default_rng(5)
+    g = rng.standard_normal((N, F)).astype(np.float32)
+    row = np.repeat(np.arange(N), deg)
+    arg = None
+    want = g[row]
+    if reduce == "mean":
+        want = (want.astype(np.float64) / deg[row][:, None]).astype(np.float32)
+    if reduce == "max":
+        arg = np.where(deg[:, None] > 0,
+                       rp[:-1, None] + rng.integers(0, 1 << 30, (N, F)) % np.maximum(deg, 1)[:, None],
+                       -1).astype(np.int32)
+        want = np.where(arg[row] == np.arange(E)[:, None], want, np.float32(0))
+    got = mp.message_backward(rp_d, torch.from_numpy(g).to(DEV),
+                              {"sum": mp.MP_SUM, "mean": mp.MP_MEAN, "max": mp.MP_MAX}[reduce], E=E,
+                              argout=None if arg is None else torch.from_numpy(arg).to(DEV))
+    assert np.array_equal(got.cpu().numpy(), want)
