@@ -240,35 +240,51 @@ __global__ __launch_bounds__(kBlock) void message_scale(const float* __restrict_
     }
 }
 
-__device__ inline int64_t rp_load(const void* rp, int rp64, int64_t i) {
-    return rp64 ? static_cast<const int64_t*>(rp)[i] : (int64_t) static_cast<const int32_t*>(rp)[i];
-}
-
 // dmsg[p, :] for the CSR edges p of destination row v, from g = dL/dout
 // [N, F]: sum g[v, :]; mean g[v, :] / deg(v) (correctly rounded; in fp64 for
 // degrees beyond 2^24, which fp32 cannot hold); max g[v, f] where
-// argout[v, f] == p.  One wavefront per row: its lanes load the row's
-// gradient chunks once (and, for max, its argmax chunks), then stream them
-// to the message rows of all of v's edges, which are consecutive: slot s of
-// the S slots of L lanes writes edges s, s + S, ..., so one store
+// argout[v, f] == p.  Bound by the stores of the table.  A wavefront's lanes
+// load a row's gradient chunks once (and, for max, its argmax chunks), then
+// stream them to the message rows of the row's edges, which are consecutive:
+// slot s of the S slots of L lanes writes edges s, s + S, ..., so one store
 // instruction covers S whole consecutive rows.  Rows wider than 64
 // lane-chunks take one more pass per 64 chunks.  No loads in the store loop.
-template <typename TG, int EPL, int MODE>
-__global__ __launch_bounds__(kBlock) void message_backward(const void* __restrict__ rowptr,
-                                                           int rp64,
+// One wavefront per row writes the row's first `part` edges; the edges beyond
+// them go to further wavefronts, one per `part` positions of the edge list,
+// which look up the row of their first position and write what it has there
+// beyond its first `part` edges (a row that starts inside a wavefront's
+// positions reaches its part-th edge in a later wavefront's).  Without them a
+// hub row's stores are one wavefront's work: 550 us for a power-law graph of
+// 1.2M edges, F = 128, whose largest row has 36k edges; with them 107 us
+// (0.6 GB stored at 5.6 TB/s).
+template <typename TG, typename IT, int EPL, int MODE>
+__global__ __launch_bounds__(kBlock) void message_backward(const IT* __restrict__ rowptr,
                                                            const int32_t* __restrict__ argout,
                                                            const TG* __restrict__ g, int64_t N,
-                                                           int64_t F, int64_t cpr, int L, int S,
+                                                           int64_t E, int64_t F, int64_t cpr,
+                                                           int L, int S, int part,
                                                            float* __restrict__ dmsg) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t v = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)) +
-                      (int64_t)blockIdx.x * (kBlock / kWave);
-    if (v >= N) return;
-    const int64_t beg = rp_load(rowptr, rp64, v);
-    const int64_t deg = rp_load(rowptr, rp64, v + 1) - beg;
+    const int64_t wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)) +
+                       (int64_t)blockIdx.x * (kBlock / kWave);
+    int64_t v = wv, e0 = 0;  // the row, and its first edge of this wavefront
+    int64_t beg, deg, e1;
+    if (wv < N) {
+        beg = (int64_t)rowptr[v];
+        deg = (int64_t)rowptr[v + 1] - beg;
+        e1 = deg < part ? deg : part;
+    } else {
+        const int64_t p0 = (wv - N + 1) * part;  // a row's first edges are not in its way
+        if (p0 >= E) return;
+        v = row_of_position(rowptr, N, E, p0, lane);
+        beg = (int64_t)rowptr[v];
+        deg = (int64_t)rowptr[v + 1] - beg;
+        e0 = p0 - beg > part ? p0 - beg : part;
+        e1 = p0 + part - beg < deg ? p0 + part - beg : deg;
+    }
     const int slot = lane / L;
     const int j = lane - slot * L;
-    if (deg <= 0 || slot >= S) return;
+    if (e1 <= e0 || slot >= S) return;
     for (int64_t k = j; k < cpr; k += L) {
         const int64_t o = v * F + k * EPL;
         float gv[EPL];
@@ -281,9 +297,9 @@ __global__ __launch_bounds__(kBlock) void message_backward(const void* __restric
                 gv[e] = deg <= (int64_t(1) << 24) ? gv[e] / (float)deg
                                                  : (float)((double)gv[e] / (double)deg);
         }
-        float* out = dmsg + (beg + slot) * F + k * EPL;
+        float* out = dmsg + (beg + e0 + slot) * F + k * EPL;
         const int64_t step = (int64_t)S * F;
-        for (int64_t e = slot; e < deg; e += S, out += step) {
+        for (int64_t e = e0 + slot; e < e1; e += S, out += step) {
             float d[EPL];
 #pragma unroll
             for (int x = 0; x < EPL; ++x) {
@@ -303,6 +319,13 @@ __global__ __launch_bounds__(kBlock) void message_backward(const void* __restric
         }
     }
 }
+
+// Edges of a row that its own wavefront writes.  Short parts balance better
+// and cost a row lookup per part of the edge list (4 round trips, hidden by
+// the other wavefronts' stores where there are many): 256 while the parts
+// fit the card's wavefronts about 8 times over, 1024 beyond.
+constexpr int64_t kPartEdges = int64_t(1) << 24;
+inline int backward_part(int64_t E) { return E <= kPartEdges ? 256 : 1024; }
 
 // Launch at most this many blocks; larger tables are walked by the grid stride.
 constexpr int64_t kMaxGrid = int64_t(1) << 20;
@@ -349,31 +372,34 @@ hipError_t gather_epl(const MessageGather& a, hipStream_t s) {
     }
 }
 
-template <typename TG, int EPL>
+template <typename TG, typename IT, int EPL>
 hipError_t backward_mode(const MessageBackward& a, hipStream_t s) {
     const int64_t cpr = a.F / EPL;
     const int L = cpr < kWave ? (int)cpr : kWave;
     const int S = kWave / L;
     const TG* g = static_cast<const TG*>(a.g);
-    const dim3 grid((unsigned)ceil_div(a.N, kBlock / kWave)), block(kBlock);
+    const IT* rp = static_cast<const IT*>(a.rowptr);
+    const int part = backward_part(a.E);
+    const int64_t waves = a.N + ceil_div(a.E, part) - 1;  // every row, every part but the first
+    const dim3 grid((unsigned)ceil_div(waves, kBlock / kWave)), block(kBlock);
     if (a.reduce == kMax)
-        hipLaunchKernelGGL((message_backward<TG, EPL, kMax>), grid, block, 0, s, a.rowptr, a.rp64,
-                           a.argout, g, a.N, a.F, cpr, L, S, a.dmsg);
+        hipLaunchKernelGGL((message_backward<TG, IT, EPL, kMax>), grid, block, 0, s, rp, a.argout,
+                           g, a.N, a.E, a.F, cpr, L, S, part, a.dmsg);
     else if (a.reduce == kMean)
-        hipLaunchKernelGGL((message_backward<TG, EPL, kMean>), grid, block, 0, s, a.rowptr, a.rp64,
-                           a.argout, g, a.N, a.F, cpr, L, S, a.dmsg);
+        hipLaunchKernelGGL((message_backward<TG, IT, EPL, kMean>), grid, block, 0, s, rp, a.argout,
+                           g, a.N, a.E, a.F, cpr, L, S, part, a.dmsg);
     else
-        hipLaunchKernelGGL((message_backward<TG, EPL, kSum>), grid, block, 0, s, a.rowptr, a.rp64,
-                           a.argout, g, a.N, a.F, cpr, L, S, a.dmsg);
+        hipLaunchKernelGGL((message_backward<TG, IT, EPL, kSum>), grid, block, 0, s, rp, a.argout,
+                           g, a.N, a.E, a.F, cpr, L, S, part, a.dmsg);
     return hipGetLastError();
 }
 
-template <typename TG>
+template <typename TG, typename IT>
 hipError_t backward_epl(const MessageBackward& a, hipStream_t s) {
     switch (a.epl) {
-        case 4: return backward_mode<TG, 4>(a, s);
-        case 2: return backward_mode<TG, 2>(a, s);
-        default: return backward_mode<TG, 1>(a, s);
+        case 4: return backward_mode<TG, IT, 4>(a, s);
+        case 2: return backward_mode<TG, IT, 2>(a, s);
+        default: return backward_mode<TG, IT, 1>(a, s);
     }
 }
 
@@ -413,7 +439,9 @@ hipError_t launch_message_scale(const float* in, float* out, const float* mask,
 
 hipError_t launch_message_backward(const MessageBackward& a, hipStream_t s) {
     if (a.E <= 0 || a.N <= 0) return hipSuccess;
-    return a.g_bf16 ? backward_epl<uint16_t>(a, s) : backward_epl<float>(a, s);
+    if (a.rp64)
+        return a.g_bf16 ? backward_epl<uint16_t, int64_t>(a, s) : backward_epl<float, int64_t>(a, s);
+    return a.g_bf16 ? backward_epl<uint16_t, int32_t>(a, s) : backward_epl<float, int32_t>(a, s);
 }
 
 }  // namespace mp
