@@ -265,57 +265,59 @@ __global__ __launch_bounds__(kBlock) void message_backward(const IT* __restrict_
                                                            int L, int S, int part,
                                                            float* __restrict__ dmsg) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)) +
-                       (int64_t)blockIdx.x * (kBlock / kWave);
-    int64_t v = wv, e0 = 0;  // the row, and its first edge of this wavefront
-    int64_t beg, deg, e1;
-    if (wv < N) {
-        beg = (int64_t)rowptr[v];
-        deg = (int64_t)rowptr[v + 1] - beg;
-        e1 = deg < part ? deg : part;
-    } else {
-        const int64_t p0 = (wv - N + 1) * part;  // a row's first edges are not in its way
-        if (p0 >= E) return;
-        v = row_of_position(rowptr, N, E, p0, lane);
-        beg = (int64_t)rowptr[v];
-        deg = (int64_t)rowptr[v + 1] - beg;
-        e0 = p0 - beg > part ? p0 - beg : part;
-        e1 = p0 + part - beg < deg ? p0 + part - beg : deg;
-    }
     const int slot = lane / L;
     const int j = lane - slot * L;
-    if (e1 <= e0 || slot >= S) return;
-    for (int64_t k = j; k < cpr; k += L) {
-        const int64_t o = v * F + k * EPL;
-        float gv[EPL];
-        load_chunk<TG, EPL>(g + o, gv);
-        int32_t am[MODE == kMax ? EPL : 1];
-        if constexpr (MODE == kMax) load_ints<EPL>(argout + o, am);
-        if constexpr (MODE == kMean) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e)
-                gv[e] = deg <= (int64_t(1) << 24) ? gv[e] / (float)deg
-                                                 : (float)((double)gv[e] / (double)deg);
+    const int64_t waves = N + (E + part - 1) / part - 1;  // every row, every part but the first
+    for (int64_t wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)) +
+                      (int64_t)blockIdx.x * (kBlock / kWave);
+         wv < waves; wv += (int64_t)gridDim.x * (kBlock / kWave)) {
+        int64_t v = wv, e0 = 0;  // the row, and its first edge of this wavefront
+        int64_t beg, deg, e1;
+        if (wv < N) {
+            beg = (int64_t)rowptr[v];
+            deg = (int64_t)rowptr[v + 1] - beg;
+            e1 = deg < part ? deg : part;
+        } else {
+            const int64_t p0 = (wv - N + 1) * part;  // a row's first edges are not in its way
+            v = row_of_position(rowptr, N, E, p0, lane);
+            beg = (int64_t)rowptr[v];
+            deg = (int64_t)rowptr[v + 1] - beg;
+            e0 = p0 - beg > part ? p0 - beg : part;
+            e1 = p0 + part - beg < deg ? p0 + part - beg : deg;
         }
-        float* out = dmsg + (beg + e0 + slot) * F + k * EPL;
-        const int64_t step = (int64_t)S * F;
-        for (int64_t e = e0 + slot; e < e1; e += S, out += step) {
-            float d[EPL];
+        // lanes without work rejoin the others here: the lookup above takes all
+        for (int64_t k = e1 > e0 && slot < S ? j : cpr; k < cpr; k += L) {
+            const int64_t o = v * F + k * EPL;
+            float gv[EPL];
+            load_chunk<TG, EPL>(g + o, gv);
+            int32_t am[MODE == kMax ? EPL : 1];
+            if constexpr (MODE == kMax) load_ints<EPL>(argout + o, am);
+            if constexpr (MODE == kMean) {
 #pragma unroll
-            for (int x = 0; x < EPL; ++x) {
-                if constexpr (MODE == kMax)
-                    d[x] = am[x] == (int32_t)(beg + e) ? gv[x] : 0.f;
-                else
-                    d[x] = gv[x];
+                for (int e = 0; e < EPL; ++e)
+                    gv[e] = deg <= (int64_t(1) << 24) ? gv[e] / (float)deg
+                                                     : (float)((double)gv[e] / (double)deg);
             }
-            // plain stores: measured faster here than non-temporal ones
-            // (which the read-and-write kernels above prefer)
-            if constexpr (EPL == 4)
-                *reinterpret_cast<float4*>(out) = make_float4(d[0], d[1], d[2], d[3]);
-            else if constexpr (EPL == 2)
-                *reinterpret_cast<float2*>(out) = make_float2(d[0], d[1]);
-            else
-                *out = d[0];
+            float* out = dmsg + (beg + e0 + slot) * F + k * EPL;
+            const int64_t step = (int64_t)S * F;
+            for (int64_t e = e0 + slot; e < e1; e += S, out += step) {
+                float d[EPL];
+#pragma unroll
+                for (int x = 0; x < EPL; ++x) {
+                    if constexpr (MODE == kMax)
+                        d[x] = am[x] == (int32_t)(beg + e) ? gv[x] : 0.f;
+                    else
+                        d[x] = gv[x];
+                }
+                // plain stores: measured faster here than non-temporal ones
+                // (which the read-and-write kernels above prefer)
+                if constexpr (EPL == 4)
+                    *reinterpret_cast<float4*>(out) = make_float4(d[0], d[1], d[2], d[3]);
+                else if constexpr (EPL == 2)
+                    *reinterpret_cast<float2*>(out) = make_float2(d[0], d[1]);
+                else
+                    *out = d[0];
+            }
         }
     }
 }
@@ -380,8 +382,8 @@ hipError_t backward_mode(const MessageBackward& a, hipStream_t s) {
     const TG* g = static_cast<const TG*>(a.g);
     const IT* rp = static_cast<const IT*>(a.rowptr);
     const int part = backward_part(a.E);
-    const int64_t waves = a.N + ceil_div(a.E, part) - 1;  // every row, every part but the first
-    const dim3 grid((unsigned)ceil_div(waves, kBlock / kWave)), block(kBlock);
+    const int64_t blocks = ceil_div(a.N + ceil_div(a.E, part) - 1, kBlock / kWave);
+    const dim3 grid((unsigned)(blocks < kMaxGrid ? blocks : kMaxGrid)), block(kBlock);
     if (a.reduce == kMax)
         hipLaunchKernelGGL((message_backward<TG, IT, EPL, kMax>), grid, block, 0, s, rp, a.argout,
                            g, a.N, a.E, a.F, cpr, L, S, part, a.dmsg);

@@ -1418,77 +1418,156 @@ __global__ __launch_bounds__(kBlock) void spmm_tiny(SpmmParams P) {
     }
 }
 
-// Combine the chunk partials of every hub row, in chunk order, and write the
-// row.  One wavefront per (hub row, 64-feature tile); lane = one feature.
+// Combine the chunk partials of every hub row, in a fixed order, and write
+// the row.  Lane = one feature of a (hub row, 64-feature tile) item.  Bound by
+// the latency of its loads.  A wavefront combines an item of up to kFixSplit
+// chunks by itself; longer ones are combined by the whole workgroup, wavefront
+// w taking the w-th of kFixWaves equal ranges of the chunks, and the ranges'
+// results added through LDS in range order.  (One wavefront per item took
+// 503 us for a hub of 7M edges in its 2048 chunks, a tenth of that graph's
+// fused sum + max, F = 64; now 67 us.  A workgroup for every item was
+// slower where hubs are many and short: 13 -> 62 us for 6,000 items of the
+// stacked statistics.)
 // HX: the stats partials too (the shifted sums and sums of squares, all
 // chunks of a row using the same shift, and min with its position).
+constexpr int kFixWaves = 8;
+constexpr int kFixSplit = 64;
+constexpr int64_t kFixMaxGrid = 1 << 20;
+
 template <bool HS, bool HM, bool HX>
-__global__ __launch_bounds__(kBlock) void spmm_fixup(SpmmParams P) {
+struct FixAcc {
+    float sum, dsum, sq, m, mn;
+    int32_t mi, ni;
+
+    __device__ inline void init() {
+        sum = dsum = sq = m = mn = 0.f;
+        mi = ni = -1;
+    }
+    // the partials of chunks [c0, c1) of feature f
+    __device__ inline void add_chunks(const SpmmParams& P, int64_t c0, int64_t c1, int64_t f) {
+        constexpr int A = HX ? 4 : 8;  // chunks in flight
+        constexpr int AS = 4;          // running sums
+        float s[AS] = {0.f, 0.f, 0.f, 0.f};
+        float ds[AS] = {0.f, 0.f, 0.f, 0.f};
+        float qs[AS] = {0.f, 0.f, 0.f, 0.f};
+        for (int64_t c = c0; c < c1; c += A) {
+            float ps[A], pm[A], pd[A], pq[A], pn[A];
+            int32_t pi[A], pj[A];
+#pragma unroll
+            for (int a = 0; a < A; ++a) {
+                const bool ok = c + a < c1;
+                const int64_t o = (c + a) * P.F + f;
+                if constexpr (HS) ps[a] = ok ? P.part_sum[o] : 0.f;
+                if constexpr (HM) { pm[a] = ok ? P.part_max[o] : 0.f; pi[a] = ok ? P.part_arg[o] : -1; }
+                if constexpr (HX) {
+                    pd[a] = ok ? P.part_dsum[o] : 0.f;
+                    pq[a] = ok ? P.part_sq[o] : 0.f;
+                    pn[a] = ok ? P.part_min[o] : 0.f;
+                    pj[a] = ok ? P.part_amin[o] : -1;
+                }
+            }
+#pragma unroll
+            for (int a = 0; a < A; ++a) {
+                if constexpr (HS) s[a % AS] += ps[a];
+                if constexpr (HM) max_merge(m, mi, pm[a], pi[a]);
+                if constexpr (HX) {
+                    ds[a % AS] += pd[a];
+                    qs[a % AS] += pq[a];
+                    min_merge(mn, ni, pn[a], pj[a]);
+                }
+            }
+        }
+        sum = (s[0] + s[1]) + (s[2] + s[3]);
+        dsum = (ds[0] + ds[1]) + (ds[2] + ds[3]);
+        sq = (qs[0] + qs[1]) + (qs[2] + qs[3]);
+    }
+
+    __device__ inline void store(const SpmmParams& P, int64_t h, int64_t f) const {
+        const int64_t row = P.rowlist[P.hub_base + h];
+        const int64_t deg = load_rp(P.rowptr, P.rp64, row + 1) - load_rp(P.rowptr, P.rp64, row);
+        const int64_t o = row * P.F + f;
+        if constexpr (HX) {
+            const float sum1[1] = {sum}, dsum1[1] = {dsum}, sq1[1] = {sq};
+            const float mx[1] = {m}, nn[1] = {mn};
+            const int32_t im[1] = {mi}, in[1] = {ni};
+            store_stats<1>(P, row, f, deg, sum1, dsum1, sq1, mx, im, nn, in, false);
+            return;
+        }
+        if constexpr (HS) {
+            float v = sum;
+            if (P.reduce & kMean) v = deg > 0 ? v / (float)deg : 0.f;
+            if (P.out_bf16) static_cast<uint16_t*>(P.out)[o] = to_bf16(v);
+            else static_cast<float*>(P.out)[o] = v;
+        }
+        if constexpr (HM) {
+            const float mv = mi < 0 ? 0.f : m;
+            if (P.max_bf16) static_cast<uint16_t*>(P.out_max)[o] = (uint16_t)(__float_as_uint(mv) >> 16);
+            else static_cast<float*>(P.out_max)[o] = mv;
+            P.argout[o] = mi;
+        }
+    }
+};
+
+template <bool HS, bool HM, bool HX>
+__global__ __launch_bounds__(kFixWaves * kWave) void spmm_fixup(SpmmParams P) {
+    using Part = FixAcc<HS, HM, HX>;
+    __shared__ Part s_part[kFixWaves][kWave];
+    __shared__ int s_split[kFixWaves];
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)) +
-                       (int64_t)blockIdx.x * kWavesPerBlock;
+    const int wl = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int64_t ftiles = (P.F + kWave - 1) / kWave;
-    const int64_t h = wv / ftiles;
-    if (h >= P.n_hub) return;
-    const int64_t f = (wv - h * ftiles) * kWave + lane;
-    if (f >= P.F) return;
-    const int64_t row = P.rowlist[P.hub_base + h];
-    const int64_t c0 = P.chunk_off[P.hub_base + h], c1 = P.chunk_off[P.hub_base + h + 1];
-    constexpr int A = 4;
-    float s[A] = {0.f, 0.f, 0.f, 0.f};
-    float ds[A] = {0.f, 0.f, 0.f, 0.f};
-    float qs[A] = {0.f, 0.f, 0.f, 0.f};
-    float m = 0.f, mn = 0.f;
-    int32_t mi = -1, ni = -1;
-    for (int64_t c = c0; c < c1; c += A) {
-        float ps[A], pm[A], pd[A], pq[A], pn[A];
-        int32_t pi[A], pj[A];
-#pragma unroll
-        for (int a = 0; a < A; ++a) {
-            const bool ok = c + a < c1;
-            const int64_t o = (c + a) * P.F + f;
-            if constexpr (HS) ps[a] = ok ? P.part_sum[o] : 0.f;
-            if constexpr (HM) { pm[a] = ok ? P.part_max[o] : 0.f; pi[a] = ok ? P.part_arg[o] : -1; }
-            if constexpr (HX) {
-                pd[a] = ok ? P.part_dsum[o] : 0.f;
-                pq[a] = ok ? P.part_sq[o] : 0.f;
-                pn[a] = ok ? P.part_min[o] : 0.f;
-                pj[a] = ok ? P.part_amin[o] : -1;
+    const int64_t items = P.n_hub * ftiles;
+    const int64_t groups = (items + kFixWaves - 1) / kFixWaves;
+    // group g's items lie `groups` apart, so that the tiles of one long hub
+    // are in different workgroups
+    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
+        const int64_t mine = g + wl * groups;
+        bool split = false;
+        if (mine < items) {
+            const int64_t h = mine / ftiles;
+            const int64_t f = (mine - h * ftiles) * kWave + lane;
+            const int64_t c0 = P.chunk_off[P.hub_base + h], c1 = P.chunk_off[P.hub_base + h + 1];
+            split = c1 - c0 > kFixSplit;
+            if (!split && f < P.F) {
+                Part a;
+                a.init();
+                a.add_chunks(P, c0, c1, f);
+                a.store(P, h, f);
             }
         }
+        if (lane == 0) s_split[wl] = split;
+        __syncthreads();
+        for (int w = 0; w < kFixWaves; ++w) {
+            if (!s_split[w]) continue;  // the same for all threads
+            const int64_t it = g + w * groups;
+            const int64_t h = it / ftiles;
+            const int64_t f = (it - h * ftiles) * kWave + lane;
+            const int64_t c0 = P.chunk_off[P.hub_base + h], c1 = P.chunk_off[P.hub_base + h + 1];
+            const int64_t per = (c1 - c0 + kFixWaves - 1) / kFixWaves;
+            const int64_t b = c0 + wl * per < c1 ? c0 + wl * per : c1;
+            const int64_t e = b + per < c1 ? b + per : c1;
+            Part a;
+            a.init();
+            if (f < P.F) a.add_chunks(P, b, e, f);
+            s_part[wl][lane] = a;
+            __syncthreads();
+            if (wl == 0 && f < P.F) {
 #pragma unroll
-        for (int a = 0; a < A; ++a) {
-            if constexpr (HS) s[a] += ps[a];
-            if constexpr (HM) max_merge(m, mi, pm[a], pi[a]);
-            if constexpr (HX) {
-                ds[a] += pd[a];
-                qs[a] += pq[a];
-                min_merge(mn, ni, pn[a], pj[a]);
+                for (int k = 1; k < kFixWaves; ++k) {
+                    const Part o = s_part[k][lane];
+                    if constexpr (HS) a.sum += o.sum;
+                    if constexpr (HM) max_merge(a.m, a.mi, o.m, o.mi);
+                    if constexpr (HX) {
+                        a.dsum += o.dsum;
+                        a.sq += o.sq;
+                        min_merge(a.mn, a.ni, o.mn, o.ni);
+                    }
+                }
+                a.store(P, h, f);
             }
+            __syncthreads();  // s_part is rewritten for the next item
         }
-    }
-    const int64_t deg = load_rp(P.rowptr, P.rp64, row + 1) - load_rp(P.rowptr, P.rp64, row);
-    const int64_t o = row * P.F + f;
-    if constexpr (HX) {
-        const float sum[1] = {(s[0] + s[1]) + (s[2] + s[3])};
-        const float dsum[1] = {(ds[0] + ds[1]) + (ds[2] + ds[3])};
-        const float sq[1] = {(qs[0] + qs[1]) + (qs[2] + qs[3])};
-        const float mx[1] = {m}, nn[1] = {mn};
-        const int32_t im[1] = {mi}, in[1] = {ni};
-        store_stats<1>(P, row, f, deg, sum, dsum, sq, mx, im, nn, in, false);
-        return;
-    }
-    if constexpr (HS) {
-        float v = (s[0] + s[1]) + (s[2] + s[3]);
-        if (P.reduce & kMean) v = deg > 0 ? v / (float)deg : 0.f;
-        if (P.out_bf16) static_cast<uint16_t*>(P.out)[o] = to_bf16(v);
-        else static_cast<float*>(P.out)[o] = v;
-    }
-    if constexpr (HM) {
-        const float mv = mi < 0 ? 0.f : m;
-        if (P.max_bf16) static_cast<uint16_t*>(P.out_max)[o] = (uint16_t)(__float_as_uint(mv) >> 16);
-        else static_cast<float*>(P.out_max)[o] = mv;
-        P.argout[o] = mi;
+        __syncthreads();  // s_split is rewritten for the next group
     }
 }
 
@@ -1701,14 +1780,14 @@ hipError_t launch_spmm_tiny(const SpmmParams& p, int x_dtype, int epl, hipStream
 
 hipError_t launch_spmm_fixup(const SpmmParams& p, hipStream_t s) {
     if (p.n_hub <= 0) return hipSuccess;
-    const int64_t waves = p.n_hub * ceil_div(p.F, kWave);
-    const unsigned grid = (unsigned)ceil_div(waves, kWavesPerBlock);
+    const int64_t groups = ceil_div(p.n_hub * ceil_div(p.F, kWave), kFixWaves);
+    const dim3 g((unsigned)(groups < kFixMaxGrid ? groups : kFixMaxGrid)), b(kFixWaves * kWave);
     const bool hs = (p.reduce & (kSum | kMean)) != 0;
     const bool hm = (p.reduce & kMax) != 0;
-    if (p.stats) hipLaunchKernelGGL((spmm_fixup<true, true, true>), dim3(grid), dim3(kBlock), 0, s, p);
-    else if (hs && hm) hipLaunchKernelGGL((spmm_fixup<true, true, false>), dim3(grid), dim3(kBlock), 0, s, p);
-    else if (hm) hipLaunchKernelGGL((spmm_fixup<false, true, false>), dim3(grid), dim3(kBlock), 0, s, p);
-    else hipLaunchKernelGGL((spmm_fixup<true, false, false>), dim3(grid), dim3(kBlock), 0, s, p);
+    if (p.stats) hipLaunchKernelGGL((spmm_fixup<true, true, true>), g, b, 0, s, p);
+    else if (hs && hm) hipLaunchKernelGGL((spmm_fixup<true, true, false>), g, b, 0, s, p);
+    else if (hm) hipLaunchKernelGGL((spmm_fixup<false, true, false>), g, b, 0, s, p);
+    else hipLaunchKernelGGL((spmm_fixup<true, false, false>), g, b, 0, s, p);
     return hipGetLastError();
 }
 

@@ -90,3 +90,35 @@ def test_message_gradient(name, reduce, F):
                               {"sum": mp.MP_SUM, "mean": mp.MP_MEAN, "max": mp.MP_MAX}[reduce], E=E,
                               argout=None if arg is None else torch.from_numpy(arg).to(DEV))
     assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("F", [64, 70])  # one and two 64-feature tiles
+def test_hub_rows_of_few_and_many_chunks(F):
+    """Hub rows of one edge per chunk, their chunk counts on both sides of the
+    64 that one wavefront combines and at the 2048 of the longest rows.
+    Integer features: sums are exact in any order."""
+    deg = np.array([2, 63, 64, 65, 0, 66, 512, 2047, 2048, 5000, 1, 130])
+    rp, rp_d = rowptr_of(deg, torch.int32)
+    E, N = int(rp[-1]), len(deg)
+    rng = np.random.default_rng(9)
+    x = rng.integers(-8, 9, (40, F)).astype(np.float32)
+    col = rng.integers(0, 40, E).astype(np.int32)
+    plan = mp.Plan(rp_d, E, F, torch.float32, opts=(1, 1, 1))
+    out, mx, arg = mp.spmm(rp_d, torch.from_numpy(col).to(DEV), torch.from_numpy(x).to(DEV),
+                           mp.MP_SUM | mp.MP_MAX, plan=plan)
+    multi = mp.spmm_multi(rp_d, torch.from_numpy(col).to(DEV), torch.from_numpy(x).to(DEV),
+                          ["sum", "min", "max", "var"], plan=plan)
+    m = x[col]
+    for v in range(N):
+        rows = m[rp[v]:rp[v + 1]]
+        if not len(rows):
+            assert (out[v] == 0).all() and (arg[v] == -1).all() and (multi["argmin"][v] == -1).all()
+            continue
+        assert np.array_equal(out[v].cpu().numpy(), rows.sum(0))
+        assert np.array_equal(multi["sum"][v].cpu().numpy(), rows.sum(0))
+        for got, at, first in ((mx, arg, rows.argmax(0)), (multi["max"], multi["argmax"], rows.argmax(0)),
+                               (multi["min"], multi["argmin"], rows.argmin(0))):
+            assert np.array_equal(at[v].cpu().numpy(), rp[v] + first)
+            assert np.array_equal(got[v].cpu().numpy(), rows[first, np.arange(F)])
+        var = rows.astype(np.float64).var(0)
+        assert np.allclose(multi["var"][v].cpu().numpy(), var, rtol=1e-5, atol=0)
