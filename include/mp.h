@@ -361,8 +361,10 @@ int mp_csr_transpose(const void* rowptr, int rowptr_itype, const int32_t* col, i
 
 /* Workspace bytes for mp_spmm_backward_x: hub partials of planT; for MP_MEAN
  * also an fp32 copy of G divided by the in-degrees (N_dst * F * 4 bytes); for
- * MP_MAX also the win masks, ceil(F / 32) 32-bit words per edge (bit f of the
- * words of forward position p: argout[row(p), f] == p). */
+ * MP_MAX also the wins of every edge: the win masks, ceil(F / 32) 32-bit words
+ * per edge (bit f of the words of forward position p: argout[row(p), f] == p),
+ * or, on larger graphs whose edges win few features, records of 32 bytes per
+ * edge (at most 8 GiB). */
 int mp_spmm_backward_x_workspace(const mp_plan* planT, int64_t N_dst, int64_t E, int64_t F,
                                  int reduce, size_t* bytes);
 
@@ -378,8 +380,8 @@ int mp_spmm_backward_x_workspace(const mp_plan* planT, int64_t N_dst, int64_t E,
  *   E           number of edges (rowptr[N_dst]); must equal planT's.
  *   grad_x      [N_src, F] of out_dtype, written in full (fp32 accumulation;
  *               a bf16 output is rounded to nearest even once).
- * MP_MAX first writes the win masks into the workspace (one pass over argout),
- * then gathers, per edge, only the feature chunks the edge wins.
+ * MP_MAX first writes the wins into the workspace (one pass over argout), then
+ * gathers, per edge, only what the edge wins.
  * Deterministic: one gather-reduce per source row, no atomics.  Asynchronous
  * on `stream`. */
 int mp_spmm_backward_x(const mp_plan* planT, const void* rowptrT, int rowptrT_itype,

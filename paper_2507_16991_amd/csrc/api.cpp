@@ -236,7 +236,9 @@ int run_spmm(const mp_plan* plan, SpmmParams& P, const Geometry& g, int x_dtype,
     const bool hx = P.stats != 0;
     const bool hs = hx || (P.reduce & (MP_SUM | MP_MEAN)) != 0;
     const bool hm = hx || (P.reduce & MP_MAX) != 0;
-    const bool tiny = plan && plan->n_tiny > 0 && g.L > kTinyDeg;
+    const bool tiny = plan && plan->n_tiny > 0 && g.L > kTinyDeg && !P.recs;
+    // wavefronts per row or chunk, and rows per wavefront of small ones
+    const int64_t ft = P.recs ? 1 : g.FT, slots = P.recs ? 8 : g.S;
     if (plan) {
         P.rowlist = plan->rowlist;
         P.rowbeg = plan->rowbeg;
@@ -250,9 +252,9 @@ int run_spmm(const mp_plan* plan, SpmmParams& P, const Geometry& g, int x_dtype,
         P.n_hub = plan->n_hub;
         P.mid_base = plan->mid_base;
         P.hub_base = plan->hub_base;
-        P.n_hub_waves = plan->n_chunks * g.FT;
-        P.n_mid_waves = plan->n_mid * g.FT;
-        P.n_small_waves = ceil_div(P.n_small, g.S) * g.FT;
+        P.n_hub_waves = plan->n_chunks * ft;
+        P.n_mid_waves = plan->n_mid * ft;
+        P.n_small_waves = ceil_div(P.n_small, slots) * ft;
         if (plan->n_chunks > 0) {
             Carver c(ws);
             const size_t cells = (size_t)plan->n_chunks * (size_t)P.F;
@@ -267,13 +269,13 @@ int run_spmm(const mp_plan* plan, SpmmParams& P, const Geometry& g, int x_dtype,
         }
     } else {
         P.rowlist = nullptr;
-        P.n_mid_waves = N_dst * g.FT;
+        P.n_mid_waves = N_dst * ft;
     }
     const int64_t waves = P.n_hub_waves + P.n_mid_waves + P.n_small_waves;
     if (ceil_div(waves, 4) > (int64_t)UINT32_MAX) return MP_ERR_SIZE;
-    hipError_t e = launch_spmm_tiny(P, x_dtype, g.epl, s);
+    hipError_t e = P.recs ? launch_win_gather(P, s) : launch_spmm_tiny(P, x_dtype, g.epl, s);
     if (e != hipSuccess) return MP_ERR_HIP;
-    e = launch_spmm(P, x_dtype, g.epl, s);
+    if (!P.recs) e = launch_spmm(P, x_dtype, g.epl, s);
     if (e != hipSuccess) return MP_ERR_HIP;
     if (plan && plan->n_hub > 0) {
         e = launch_spmm_fixup(P, s);
@@ -842,9 +844,11 @@ int mp_csr_transpose(const void* rowptr, int rowptr_itype, const int32_t* col, i
 }
 
 // Extra workspace of mp_spmm_backward_x beyond the aggregation's own: the
-// fp32 grad_out / in-degree table (mean) or the win masks (max).
+// fp32 grad_out / in-degree table (mean) or the win masks or records (max).
 size_t backward_x_extra(int64_t N_dst, int64_t E, int64_t F, int reduce) {
     if (reduce == MP_MEAN) return align_up((size_t)N_dst * (size_t)F * 4, 256);
+    if (reduce == MP_MAX && use_win_records(N_dst, E, F))
+        return align_up((size_t)E * kWinWords * 4, 256);
     // (at least one position's words: the gather may load word 0 unread)
     if (reduce == MP_MAX)
         return align_up((size_t)(E > 0 ? E : 1) * (size_t)win_mask_words(F) * 4, 256);
@@ -920,13 +924,21 @@ int mp_spmm_backward_x(const mp_plan* planT, const void* rowptrT, int rowptrT_it
         t_dtype = MP_F32;
     }
     uint32_t* mbits = nullptr;
+    // (records are written in 16-byte stores; the masks never need more room)
+    const bool records = reduce == MP_MAX && use_win_records(N_dst, E, F) &&
+                         (uintptr_t)extra_buf % 16 == 0;
     if (reduce == MP_MAX) {
-        // max: the win masks of every forward position, then a sum over the
-        // transposed CSR that keeps the features each edge wins
+        // max: the wins of every forward position, then a sum over the
+        // transposed CSR of the features each edge wins
         mbits = reinterpret_cast<uint32_t*>(extra_buf);
-        if (E > 0 && launch_win_masks(rowptr, rowptr_itype == MP_I64, argout, N_dst, F, mbits,
-                                      s) != hipSuccess)
+        if (records) {
+            if (launch_win_records(rowptr, rowptr_itype == MP_I64, argout, grad_out,
+                                   g_dtype == MP_BF16, N_dst, E, F, mbits, s) != hipSuccess)
+                return MP_ERR_HIP;
+        } else if (E > 0 && launch_win_masks(rowptr, rowptr_itype == MP_I64, argout, N_dst, F, mbits,
+                                             s) != hipSuccess) {
             return MP_ERR_HIP;
+        }
     }
     Geometry g = make_geometry(F, t_dtype, (uintptr_t)table);
     SpmmParams P{};
@@ -942,7 +954,13 @@ int mp_spmm_backward_x(const mp_plan* planT, const void* rowptrT, int rowptrT_it
     P.out = grad_x;
     P.out_bf16 = out_dtype == MP_BF16;
     P.vec_store = ((uintptr_t)grad_x % 16) == 0;
-    if (reduce == MP_MAX) {
+    if (records) {
+        P.ekey = posT;
+        P.recs = mbits;
+        P.win_arg = argout;
+        P.win_g = grad_out;
+        P.win_g_bf16 = g_dtype == MP_BF16;
+    } else if (reduce == MP_MAX) {
         P.ekey = posT;
         P.mbits = mbits;
         P.mw = win_mask_words(F);

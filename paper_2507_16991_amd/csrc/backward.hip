@@ -19,6 +19,9 @@
 //     wins (one bit per feature), so that the masked sum over the transposed
 //     CSR reads one mask word per edge and lane instead of the argmax chunk
 //     of the edge's destination row.
+//   * win_records + win_gather: the same where edges win few features: the
+//     routed gradient values travel with the edge, so that the sum over the
+//     transposed CSR makes one scattered read per edge.
 //
 // The gradient with respect to x reuses the aggregation kernels of spmm.hip
 // over the transposed CSR (sum, mean after scale_inv_deg, and a masked sum
@@ -127,6 +130,13 @@ __global__ __launch_bounds__(kBlock) void rows_of_edges(const IT* __restrict__ r
 }
 
 __device__ inline float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
+
+// fp32 -> bf16 bits, round to nearest even (finite values).
+__device__ inline uint16_t f32_to_bf16_bits(float f) {
+    uint32_t u = __float_as_uint(f);
+    u += 0x7FFFu + ((u >> 16) & 1u);
+    return (uint16_t)(u >> 16);
+}
 
 // out[v, f] = g[v, f] / deg(v) in fp32 (0 for an empty row).  Each thread
 // takes V consecutive elements of one row (V divides F); the row index uses
@@ -250,6 +260,384 @@ __global__ __launch_bounds__(kBlock) void win_masks(const IT* __restrict__ rowpt
                 }
                 __builtin_amdgcn_wave_barrier();
             }
+        }
+    }
+}
+
+// ---- gradient of max by win records ------------------------------------------
+//
+// A record of 32 bytes per forward CSR position: words 0..5 the routed values
+// G[v, f] (fp32) of the first six features f that the position's edge wins, in
+// feature order; bytes 24..29 their feature ids; byte 30 zero; byte 31 the
+// number of wins (at most 255).
+
+constexpr int kRecRows = 4;        // consecutive rows of a wavefront
+constexpr int kRecPart = 1024;     // positions of a row that its own wavefront writes
+
+__device__ inline float grad_at(const void* g, int g_bf16, int64_t i) {
+    return g_bf16 ? bf16_bits_to_f32(static_cast<const uint16_t*>(g)[i])
+                  : static_cast<const float*>(g)[i];
+}
+
+// Bound by its traffic (argout and g read once, 32 bytes written per edge).
+// As in win_masks, a wavefront takes kRecRows consecutive rows with their
+// first loads in flight together and walks a row's positions in chunks of 64:
+// every feature ORs its bit into its winner's mask (LDS, order-free), and then
+// its rank among the winner's features, the bits below its own, is its value's
+// place in the record.  The chunk's 64 records leave LDS in 16-byte stores.
+// A row's positions beyond the first kRecPart go to further wavefronts, as in
+// message_backward.  124M edges, F = 100: 1160 us (masks alone: 740 us).
+template <typename IT>
+__global__ __launch_bounds__(kBlock) void win_records(const IT* __restrict__ rowptr,
+                                                      const int32_t* __restrict__ argout,
+                                                      const void* __restrict__ g, int g_bf16,
+                                                      int64_t N, int64_t E, int64_t F,
+                                                      uint32_t* __restrict__ recs) {
+    __shared__ __align__(16) uint32_t s_mask[kWavesPerBlock][kWave * 4];
+    __shared__ __align__(16) uint32_t s_rec[kWavesPerBlock][kWave * kWinWords];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int64_t wv = wid + (int64_t)blockIdx.x * kWavesPerBlock;
+    const int64_t row_waves = (N + kRecRows - 1) / kRecRows;
+    uint32_t* const mask = s_mask[wid];
+    uint32_t* const rec = s_rec[wid];
+    uint8_t* const rec8 = reinterpret_cast<uint8_t*>(rec);
+    const uint32_t bit = 1u << (lane & 31);
+    const int half = lane >> 5;
+
+    // positions [c0, c1) of row v, relative to its start beg; a0, b0, ga0,
+    // gb0: argout and g of the features lane and 64 + lane
+    auto span = [&](int64_t v, int64_t beg, int64_t c0, int64_t c1, int32_t a0, int32_t b0,
+                    float ga0, float gb0) {
+        for (; c0 < c1; c0 += kWave) {
+            const int n = (int)(c1 - c0 < kWave ? c1 - c0 : kWave);
+            *reinterpret_cast<uint4*>(rec + 8 * lane) = make_uint4(0u, 0u, 0u, 0u);
+            *reinterpret_cast<uint4*>(rec + 8 * lane + 4) = make_uint4(0u, 0u, 0u, 0u);
+            for (int64_t f0 = 0; f0 < F; f0 += 2 * kWave) {
+                const int64_t fa = f0 + lane, fb = f0 + kWave + lane;
+                int32_t aa = a0, ab = b0;
+                float ga = ga0, gb = gb0;
+                if (f0 > 0) {
+                    const int64_t ia = v * F + (fa < F ? fa : F - 1);
+                    const int64_t ib = v * F + (fb < F ? fb : F - 1);
+                    aa = argout[ia];
+                    ab = argout[ib];
+                    ga = grad_at(g, g_bf16, ia);
+                    gb = grad_at(g, g_bf16, ib);
+                }
+                // winners relative to the chunk (outside 0..n-1: not here)
+                const int64_t qa = fa < F ? (int64_t)aa - beg - c0 : -1;
+                const int64_t qb = fb < F ? (int64_t)ab - beg - c0 : -1;
+                const bool ina = qa >= 0 && qa < n, inb = qb >= 0 && qb < n;
+                *reinterpret_cast<uint4*>(mask + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
+                __builtin_amdgcn_wave_barrier();
+                if (ina) atomicOr(mask + 4 * qa + half, bit);
+                if (inb) atomicOr(mask + 4 * qb + 2 + half, bit);
+                __builtin_amdgcn_wave_barrier();
+                // a feature's place: the wins of earlier tiles (byte 31), then
+                // the bits below its own
+                if (ina) {
+                    const uint4 m = *reinterpret_cast<const uint4*>(mask + 4 * qa);
+                    const int r = rec8[32 * qa + 31] + (half ? __popc(m.x) : 0) +
+                                  __popc((half ? m.y : m.x) & (bit - 1u));
+                    if (r < kWinValues) {
+                        rec[8 * qa + r] = __float_as_uint(ga);
+                        rec8[32 * qa + 24 + r] = (uint8_t)fa;
+                    }
+                }
+                if (inb) {
+                    const uint4 m = *reinterpret_cast<const uint4*>(mask + 4 * qb);
+                    const int r = rec8[32 * qb + 31] + __popc(m.x) + __popc(m.y) +
+                                  (half ? __popc(m.z) : 0) +
+                                  __popc((half ? m.w : m.z) & (bit - 1u));
+                    if (r < kWinValues) {
+                        rec[8 * qb + r] = __float_as_uint(gb);
+                        rec8[32 * qb + 24 + r] = (uint8_t)fb;
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+                {
+                    const uint4 m = *reinterpret_cast<const uint4*>(mask + 4 * lane);
+                    const int t = rec8[32 * lane + 31] + __popc(m.x) + __popc(m.y) + __popc(m.z) +
+                                  __popc(m.w);
+                    rec8[32 * lane + 31] = (uint8_t)(t < 255 ? t : 255);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            uint4* const out = reinterpret_cast<uint4*>(recs + (beg + c0) * kWinWords);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int i = k * kWave + lane;  // 16-byte half i of the chunk's records
+                if (i < 2 * n) out[i] = *reinterpret_cast<const uint4*>(rec + 4 * i);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
+
+    const int64_t la = lane < F ? lane : F - 1;
+    const int64_t lb = kWave + lane < F ? kWave + lane : F - 1;
+    if (wv < row_waves) {
+        const int64_t v0 = wv * kRecRows;
+        int64_t rb[kRecRows + 1];
+#pragma unroll
+        for (int i = 0; i <= kRecRows; ++i) rb[i] = (int64_t)rowptr[v0 + i < N ? v0 + i : N];
+        int32_t a0[kRecRows], b0[kRecRows];
+        float ga[kRecRows], gb[kRecRows];
+#pragma unroll
+        for (int i = 0; i < kRecRows; ++i) {
+            const int64_t v = v0 + i < N ? v0 + i : N - 1;
+            a0[i] = argout[v * F + la];
+            b0[i] = argout[v * F + lb];
+            ga[i] = grad_at(g, g_bf16, v * F + la);
+            gb[i] = grad_at(g, g_bf16, v * F + lb);
+        }
+#pragma unroll
+        for (int i = 0; i < kRecRows; ++i) {
+            const int64_t deg = rb[i + 1] - rb[i];
+            if (v0 + i < N)
+                span(v0 + i, rb[i], 0, deg < kRecPart ? deg : kRecPart, a0[i], b0[i], ga[i], gb[i]);
+        }
+    } else {
+        const int64_t p0 = (wv - row_waves + 1) * kRecPart;
+        if (p0 >= E) return;
+        const int64_t v = row_of_position(rowptr, N, E, p0, lane);
+        const int64_t beg = (int64_t)rowptr[v];
+        const int64_t deg = (int64_t)rowptr[v + 1] - beg;
+        const int64_t c0 = p0 - beg > kRecPart ? p0 - beg : kRecPart;
+        const int64_t c1 = p0 + kRecPart - beg < deg ? p0 + kRecPart - beg : deg;
+        if (c0 < c1)
+            span(v, beg, c0, c1, argout[v * F + la], argout[v * F + lb],
+                 grad_at(g, g_bf16, v * F + la), grad_at(g, g_bf16, v * F + lb));
+    }
+}
+
+// Sum of the wins of every row of the transposed CSR.  Bound by its scattered
+// reads: one 128-byte line per edge holds its record (124M edges, F = 100:
+// 3855 us at 5.1 TB/s of lines; masks and chunks of G, about three lines per
+// edge: 7715 us).  A wavefront is 8 slots of 8 lanes; a slot reads one record per load (lane i
+// word i), 8 loads in flight, and adds the record's values into its own F
+// sums in LDS: lane i adds value i.  The features of one record differ and
+// every slot has sums of its own, so no two lanes ever add to one place, and
+// each place's order of additions is fixed.  As in spmm_main, a mid row or hub
+// chunk takes a wavefront, its edges dealt to the slots (whose sums are added
+// in a fixed tree at the end), and small rows take a slot each.
+// NF: 64-feature tiles of a row.
+constexpr int kWinSlots = 8;
+
+template <bool W, int NF>
+__global__ __launch_bounds__(kBlock) void win_gather(SpmmParams P, int fp) {
+    extern __shared__ float s_sum[];  // [kWavesPerBlock][kWinSlots][fp]
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int64_t wv = wid + (int64_t)blockIdx.x * kWavesPerBlock;
+    if (wv >= P.n_hub_waves + P.n_mid_waves + P.n_small_waves) return;
+    const int slot = lane >> 3, i = lane & 7;
+    const int F = (int)P.F;
+    float* const wave_sum = s_sum + wid * kWinSlots * fp;
+    float* const sum = wave_sum + slot * fp;
+    for (int k = 4 * lane; k < kWinSlots * fp; k += 4 * kWave)
+        *reinterpret_cast<float4*>(wave_sum + k) = make_float4(0.f, 0.f, 0.f, 0.f);
+    __builtin_amdgcn_wave_barrier();
+
+    // this lane's word of the record of forward position key (0 without an edge)
+    auto word = [&](int32_t key, bool ok) -> uint32_t {
+        return ok ? P.recs[(int64_t)key * kWinWords + i] : 0u;
+    };
+    // add the record whose word i lane i of the slot holds, weight wt
+    auto add = [&](uint32_t w, float wt) {
+        // words 6 and 7 of the slot's record
+        const uint32_t lo = __builtin_amdgcn_ds_swizzle((int)w, (6 << 5) | 0x18);
+        const uint32_t hi = __builtin_amdgcn_ds_swizzle((int)w, (7 << 5) | 0x18);
+        if (i < kWinValues && i < (int)(hi >> 24)) {
+            const uint32_t id = ((i < 4 ? lo : hi) >> (8 * (i & 3))) & 255u;
+            float v = __uint_as_float(w);
+            if constexpr (W) v = __fmul_rn(wt, v);
+            sum[id] += v;
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    // Edges of more wins than a record holds: the rest from the destination's
+    // argmax and gradient rows, by the whole wavefront, each edge's rows
+    // loading while the previous edge's are added.
+    int32_t pa[NF];
+    float pg[NF];
+    int pslot = -1;  // the slot whose edge's rows are loading (-1: none)
+    int32_t ppos = 0;
+    float pwt = 1.f;
+    auto flush = [&]() {
+        if (pslot < 0) return;
+        float* const to = wave_sum + pslot * fp;
+#pragma unroll
+        for (int q = 0; q < NF; ++q) {
+            const int f = q * kWave + lane;
+            if (pa[q] == ppos) {  // -1: not read (ppos is a position)
+                float x = pg[q];
+                if constexpr (W) x = __fmul_rn(pwt, x);
+                to[f] += x;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        pslot = -1;
+    };
+    // w: this lane's word of the slot's record; key, col, wt: of the edge,
+    // held by lane src(slot)
+    auto rest = [&](uint32_t w, int32_t key, int32_t col, float wt, auto src) {
+        uint64_t more = __ballot(i == 7 && (int)(w >> 24) > kWinValues);
+        while (more) {
+            const int l = __ffsll((unsigned long long)more) - 1;  // lane 7 of a slot
+            more &= more - 1;
+            const int sl = l >> 3;
+            const int64_t v = __builtin_amdgcn_readlane(col, src(sl));
+            // the record's features ascend: only those past its last are read
+            const int last = (int)((uint32_t)__builtin_amdgcn_readlane((int)w, l) >> 8) & 255;
+            int32_t na[NF];
+            float ng[NF];
+#pragma unroll
+            for (int q = 0; q < NF; ++q) {
+                const int f = q * kWave + lane;
+                na[q] = -1;
+                ng[q] = 0.f;
+                if (f < F && f > last) {
+                    na[q] = P.win_arg[v * F + f];
+                    ng[q] = grad_at(P.win_g, P.win_g_bf16, v * F + f);
+                }
+            }
+            flush();
+#pragma unroll
+            for (int q = 0; q < NF; ++q) {
+                pa[q] = na[q];
+                pg[q] = ng[q];
+            }
+            pslot = sl;
+            ppos = __builtin_amdgcn_readlane(key, src(sl));
+            if constexpr (W)
+                pwt = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(wt), src(sl)));
+        }
+    };
+    constexpr int U = 8;
+
+    if (wv < P.n_hub_waves + P.n_mid_waves) {
+        const bool hub = wv < P.n_hub_waves;
+        int64_t row, e0, e1;
+        if (hub) {
+            // the chunk's row, by binary search over the hub rows' chunk offsets
+            int64_t lo = 0, hi = P.n_hub - 1;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi + 1) >> 1;
+                if ((int64_t)P.chunk_off[P.hub_base + mid] <= wv) lo = mid; else hi = mid - 1;
+            }
+            row = P.rowlist[P.hub_base + lo];
+            const int64_t r0 = rp_at(P.rowptr, P.rp64, row), r1 = rp_at(P.rowptr, P.rp64, row + 1);
+            int64_t csz = (r1 - r0 + kMaxChunksPerHub - 1) / kMaxChunksPerHub;
+            if (csz < P.chunk_min) csz = P.chunk_min;
+            e0 = r0 + (wv - (int64_t)P.chunk_off[P.hub_base + lo]) * csz;
+            e1 = e0 + csz < r1 ? e0 + csz : r1;
+        } else {
+            const int64_t k = P.mid_base + wv - P.n_hub_waves;
+            row = P.rowlist ? (int64_t)P.rowlist[k] : k;
+            e0 = P.rowbeg ? (int64_t)P.rowbeg[k] : rp_at(P.rowptr, P.rp64, row);
+            e1 = P.rowend ? (int64_t)P.rowend[k] : rp_at(P.rowptr, P.rp64, row + 1);
+        }
+        // 64 edges at a time: edge u * 8 + slot is the slot's u-th; the next
+        // 64 edges' indices load while these are gathered
+        auto index = [&](int64_t q, int32_t& key, int32_t& col, float& wt) {
+            const bool ok = q + lane < e1;
+            key = ok ? __builtin_nontemporal_load(P.ekey + q + lane) : 0;
+            col = ok ? __builtin_nontemporal_load(P.col + q + lane) : 0;
+            wt = 1.f;
+            if constexpr (W) wt = ok ? __builtin_nontemporal_load(P.w + q + lane) : 1.f;
+        };
+        int32_t key, col;
+        float wt;
+        index(e0, key, col, wt);
+        for (int64_t q = e0; q < e1; q += kWave) {
+            uint32_t w[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                w[u] = word(__shfl(key, u * kWinSlots + slot), q + u * kWinSlots + slot < e1);
+            int32_t nkey, ncol;
+            float nwt;
+            index(q + kWave, nkey, ncol, nwt);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float x = 1.f;
+                if constexpr (W) x = __shfl(wt, u * kWinSlots + slot);
+                add(w[u], x);
+                rest(w[u], key, col, wt, [&](int sl) { return u * kWinSlots + sl; });
+            }
+            key = nkey;
+            col = ncol;
+            wt = nwt;
+        }
+        flush();
+        for (int f = lane; f < F; f += kWave) {
+            float s[kWinSlots];
+#pragma unroll
+            for (int k = 0; k < kWinSlots; ++k) s[k] = wave_sum[k * fp + f];
+            const float r = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+            if (hub) P.part_sum[wv * F + f] = r;
+            else if (P.out_bf16) static_cast<uint16_t*>(P.out)[row * F + f] = f32_to_bf16_bits(r);
+            else static_cast<float*>(P.out)[row * F + f] = r;
+        }
+        return;
+    }
+
+    // small rows: a slot each
+    const int64_t k = (wv - P.n_hub_waves - P.n_mid_waves) * kWinSlots + slot;
+    const bool row_ok = k < P.n_small;
+    int64_t row = 0, e0 = 0;
+    int32_t n = 0;
+    if (row_ok) {
+        row = P.rowlist[P.small_base + k];
+        e0 = P.rowbeg[P.small_base + k];
+        n = P.rowend[P.small_base + k] - (int32_t)e0;
+    }
+    int32_t max_n = n;
+#pragma unroll
+    for (int off = kWinSlots; off < kWave; off <<= 1) {
+        const int32_t o = __shfl_xor(max_n, off);
+        max_n = o > max_n ? o : max_n;
+    }
+    max_n = __builtin_amdgcn_readfirstlane(max_n);
+    // lane i of a slot loads the indices of the row's next i-th edge
+    auto index = [&](int32_t it, int32_t& key, int32_t& col, float& wt) {
+        const bool ok = it + i < n;
+        key = ok ? __builtin_nontemporal_load(P.ekey + e0 + it + i) : 0;
+        col = ok ? __builtin_nontemporal_load(P.col + e0 + it + i) : 0;
+        wt = 1.f;
+        if constexpr (W) wt = ok ? __builtin_nontemporal_load(P.w + e0 + it + i) : 1.f;
+    };
+    int32_t key, col;
+    float wt;
+    index(0, key, col, wt);
+    for (int32_t it = 0; it < max_n; it += U) {
+        uint32_t w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = word(__shfl(key, (lane & ~7) + u), it + u < n);
+        int32_t nkey, ncol;
+        float nwt;
+        index(it + U, nkey, ncol, nwt);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float x = 1.f;
+            if constexpr (W) x = __shfl(wt, (lane & ~7) + u);
+            add(w[u], x);
+            rest(w[u], key, col, wt, [&](int sl) { return sl * 8 + u; });
+        }
+        key = nkey;
+        col = ncol;
+        wt = nwt;
+    }
+    flush();
+    const int64_t left = P.n_small - (k - slot);
+    const int rows = left < kWinSlots ? (int)left : kWinSlots;
+    for (int s = 0; s < rows; ++s) {
+        const int64_t r = ((int64_t)__shfl((int)(row >> 32), s * 8) << 32) |
+                          (uint32_t)__shfl((int)(uint32_t)row, s * 8);
+        for (int f = lane; f < F; f += kWave) {
+            const float x = wave_sum[s * fp + f];
+            if (P.out_bf16) static_cast<uint16_t*>(P.out)[r * F + f] = f32_to_bf16_bits(x);
+            else static_cast<float*>(P.out)[r * F + f] = x;
         }
     }
 }
@@ -492,6 +880,58 @@ hipError_t launch_win_masks(const void* rowptr, int rp64, const int32_t* argout,
         hipLaunchKernelGGL(win_masks<int32_t>, dim3(grid), dim3(kBlock), 0, s,
                            static_cast<const int32_t*>(rowptr), argout, N, F, win_mask_words(F),
                            bits);
+    return hipGetLastError();
+}
+
+// Records or masks, by the number of wins of an average edge, N_dst * F / E
+// (us of the whole gradient by masks -> by records, uniform graphs of 60M
+// edges unless said):
+//   * over kWinMeanMax: records overflow, which costs two row reads per edge
+//     (F = 64: 4 wins 2144 -> 1766, 8 wins 1302 -> 1837; F = 16: 4 wins 661 ->
+//     722; F = 128: 2 wins 2037 -> 1309, 16 wins 2280 -> 3456);
+//   * under 0.6: most edges win nothing, and their masks are shorter than
+//     their records (F = 32: 1 win 2489 -> 2235, 0.25 wins 1730 -> 1890;
+//     F = 64: 0.5 wins 1810 -> 1862; F = 100: 0.78 wins 2002 -> 1544);
+//   * under kWinMinEdges the longer chain of a record's building shows
+//     (F = 64, 2 wins: 0.5M edges 28 -> 40, 1M 54 -> 54, 2M 107 -> 84).
+// The table of records, up to eight times the masks', stays within
+// kWinMaxBytes.
+bool use_win_records(int64_t N_dst, int64_t E, int64_t F) {
+    constexpr int64_t kWinMinEdges = 3 << 19;
+    constexpr int64_t kWinMaxBytes = int64_t(1) << 33;
+    constexpr int64_t kWinMeanMax = 3;
+    const int64_t wins = N_dst * F;
+    return F <= kWinMaxF && E >= kWinMinEdges && E * kWinWords * 4 <= kWinMaxBytes &&
+           wins <= kWinMeanMax * E && 5 * wins >= 3 * E;
+}
+
+hipError_t launch_win_records(const void* rowptr, int rp64, const int32_t* argout, const void* g,
+                              int g_bf16, int64_t N, int64_t E, int64_t F, uint32_t* recs,
+                              hipStream_t s) {
+    if (N <= 0 || E <= 0) return hipSuccess;
+    const int64_t waves = ceil_div(N, kRecRows) + ceil_div(E, kRecPart) - 1;
+    const unsigned grid = (unsigned)ceil_div(waves, kWavesPerBlock);
+    if (rp64)
+        hipLaunchKernelGGL(win_records<int64_t>, dim3(grid), dim3(kBlock), 0, s,
+                           static_cast<const int64_t*>(rowptr), argout, g, g_bf16, N, E, F, recs);
+    else
+        hipLaunchKernelGGL(win_records<int32_t>, dim3(grid), dim3(kBlock), 0, s,
+                           static_cast<const int32_t*>(rowptr), argout, g, g_bf16, N, E, F, recs);
+    return hipGetLastError();
+}
+
+hipError_t launch_win_gather(const SpmmParams& p, hipStream_t s) {
+    const int64_t waves = p.n_hub_waves + p.n_mid_waves + p.n_small_waves;
+    if (waves <= 0) return hipSuccess;
+    const int fp = (int)((p.F + 3) / 4 * 4);  // whole 16-byte groups per slot
+    const size_t lds = sizeof(float) * kWavesPerBlock * kWinSlots * fp;
+    const dim3 g((unsigned)ceil_div(waves, kWavesPerBlock)), b(kBlock);
+    static_assert(kWinMaxF <= 4 * kWave, "at most four feature tiles");
+    const int nf = (int)ceil_div(p.F, kWave);
+    if (p.w && nf <= 2) hipLaunchKernelGGL((win_gather<true, 2>), g, b, lds, s, p, fp);
+    else if (p.w) hipLaunchKernelGGL((win_gather<true, 4>), g, b, lds, s, p, fp);
+    else if (nf <= 2) hipLaunchKernelGGL((win_gather<false, 2>), g, b, lds, s, p, fp);
+    else hipLaunchKernelGGL((win_gather<false, 4>), g, b, lds, s, p, fp);
     return hipGetLastError();
 }
 

@@ -196,6 +196,13 @@ struct SpmmParams {
     const int32_t* ekey;
     const uint32_t* mbits;
     int64_t mw;
+    // the same by win records (backward.hip) in place of the masks: nullptr,
+    // or kWinWords words per forward position; an edge of more wins than a
+    // record holds reads its destination's argmax and gradient rows (g)
+    const uint32_t* recs;
+    const int32_t* win_arg;
+    const void* win_g;
+    int win_g_bf16;
     // stats mode (stacked statistics from one gather): each non-null output
     // [N_dst, F] fp32 (arguments int32) is written
     int stats;
@@ -275,6 +282,18 @@ hipError_t launch_spmm_grad_w(const GradWParams& p, int x_dtype, int g_dtype, in
 inline int64_t win_mask_words(int64_t F) { return (F + 31) / 32; }
 hipError_t launch_win_masks(const void* rowptr, int rp64, const int32_t* argout, int64_t N,
                             int64_t F, uint32_t* bits, hipStream_t s);
+// Win records of the max aggregation: per forward CSR position, the values and
+// feature ids of its first kWinValues wins and the number of its wins.
+constexpr int kWinWords = 8;
+constexpr int kWinValues = 6;
+constexpr int64_t kWinMaxF = 256;  // feature ids are bytes
+// Whether the gradient of max goes by win records rather than masks.
+bool use_win_records(int64_t N_dst, int64_t E, int64_t F);
+hipError_t launch_win_records(const void* rowptr, int rp64, const int32_t* argout, const void* g,
+                              int g_bf16, int64_t N, int64_t E, int64_t F, uint32_t* recs,
+                              hipStream_t s);
+// Sum over the rows of P (a transposed CSR) of the wins in P.recs.
+hipError_t launch_win_gather(const SpmmParams& p, hipStream_t s);
 
 // ---- segment matmul (gmm.hip) --------------------------------------------------
 struct GmmParams {

@@ -1,0 +1,88 @@
+"""Gradient of max by win records (graphs of at least 1.5M edges whose edges
+win 0.6 to 3 features on average): records that hold no win, up to six, and
+more (degree-one rows, whose edge wins every feature), hub rows on both sides,
+empty rows, feature counts on both sides of a 64- and a 128-feature tile.  G
+and the weights are small integers, so that every sum is exact in any order
+and the gradient is compared bit for bit."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_16991_amd as mp
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+E_MIN = 3 << 19
+
+
+@pytest.fixture(autouse=True)
+def _announce(request):
+    sys.stderr.write(f"\n[gpu-case] {request.node.nodeid}\n")
+    sys.stderr.flush()
+    yield
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("F,gdtype,weighted,plan,itype", [
+    (7, torch.float32, False, "default", torch.int32),
+    (64, torch.bfloat16, True, None, torch.int64),
+    (100, torch.float32, True, "default", torch.int32),
+    (128, torch.bfloat16, False, "hubs", torch.int32),
+    (130, torch.float32, False, "default", torch.int64),
+    (256, torch.float32, True, "hubs", torch.int32),
+])
+@pytest.mark.parametrize("shift", [0, 4])  # bytes the workspace is off its alignment
+def test_max_gradient_by_records(F, gdtype, weighted, plan, itype, shift):
+    rng = np.random.default_rng(F)
+    n_dst = 2 * E_MIN // F  # two wins an edge
+    deg = np.minimum(rng.zipf(2.2, n_dst) - 1, 5_000)  # empty rows, degree one, hubs
+    deg[:50] = 1
+    deg[5] = 100_003
+    missing = E_MIN + 77 - int(deg.sum())
+    if missing > 0:
+        deg += rng.multinomial(missing, np.full(n_dst, 1.0 / n_dst))
+    E = int(deg.sum())
+    assert E_MIN <= E and 0.6 * E <= n_dst * F <= 3 * E
+    n_src = max(200, n_dst // 2)
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    col = (n_src * rng.random(E) ** 3).astype(np.int32)  # some sources of many edges
+    arg = np.where(deg[:, None] > 0, rp[:-1, None] + rng.integers(0, 1 << 40, (n_dst, F)) %
+                   np.maximum(deg, 1)[:, None], -1).astype(np.int32)
+    g = rng.integers(-8, 9, (n_dst, F)).astype(np.float32)
+    w = rng.integers(-3, 4, E).astype(np.float32) if weighted else None
+    want = np.zeros((n_src, F), dtype=np.float64)
+    v, f = np.nonzero(arg >= 0)
+    p = arg[v, f]
+    np.add.at(want, (col[p], f), g[v, f] * (w[p] if weighted else 1.0))
+
+    rp_d = torch.from_numpy(rp).to(DEV, itype)
+    col_d = torch.from_numpy(col).to(DEV)
+    rpT, colT, posT, wT = mp.csr_transpose(
+        rp_d, col_d, n_src, val=None if w is None else torch.from_numpy(w).to(DEV))
+    planT = None
+    if plan:
+        planT = mp.Plan(rpT, E, F, opts=(40, 200, 64) if plan == "hubs" else None)
+    h = planT.handle if planT else None
+    nb = mp.mp_spmm_backward_x_workspace(h, n_dst, E, F, mp.MP_MAX)
+    part = mp.mp_spmm_backward_x_workspace(h, n_dst, E, F, mp.MP_SUM)
+    assert nb == (part + 255) // 256 * 256 + (32 * E + 255) // 256 * 256  # records
+    ws = torch.empty(nb + shift, dtype=torch.uint8, device=DEV)[shift:]
+    g_d = torch.from_numpy(g).to(DEV, gdtype)
+    out = torch.full((n_src, F), float("nan"), dtype=torch.float32, device=DEV)
+    it = mp.MP_I32 if itype == torch.int32 else mp.MP_I64
+    mp.mp_spmm_backward_x(h, rpT, mp.MP_I32, colT, posT, wT, rp_d, it, torch.from_numpy(arg).to(DEV),
+                          g_d, mp.MP_F32 if gdtype == torch.float32 else mp.MP_BF16, n_dst, n_src,
+                          E, F, mp.MP_MAX, out, mp.MP_F32, ws, nb)
+    assert np.array_equal(out.cpu().numpy(), want.astype(np.float32))
+
+
+def test_records_are_for_large_graphs_of_few_wins():
+    size = lambda n, E, F: mp.mp_spmm_backward_x_workspace(None, n, E, F, mp.MP_MAX) // E
+    E = E_MIN
+    assert size(3 * E // 64, E, 64) == 32 and size(3 * E // 5 // 64 + 1, E, 64) == 32
+    assert size(3 * E // 64 + 64, E, 64) == 8  # masks: two words per edge
+    assert size(E // 2 // 64, E, 64) == 8 and size(3 * (E - 64) // 64, E - 64, 64) == 8
+    assert size(E // 257, E, 257) == 36
+    assert size(1 << 23, 1 << 28, 64) == 32 and size(1 << 23, (1 << 28) + 64, 64) == 8
