@@ -33,8 +33,7 @@
  *    every output untouched.  MP_ERR_HIP reports a failed launch or copy.
  *    Calls that sort on the device (mp_coo_to_csr, mp_csr_transpose,
  *    mp_hetero_build) report device-side failure asynchronously through an
- *    optional device status word (see mp_coo_to_csr); mp_spmm_plan_build,
- *    which synchronizes anyway, returns it.
+ *    optional device status word (see mp_coo_to_csr).
  *  - Index validity.  Edge indices must satisfy 0 <= src < N_src and
  *    0 <= dst < N_dst, and a rowptr must be non-decreasing with rowptr[0] = 0
  *    and rowptr[N_dst] = E.  Violations are not detected by the compute calls
@@ -165,9 +164,8 @@ int mp_spmm_plan_size(int64_t N_dst, int64_t E, size_t* bytes);
  *   *out        (host) receives a host-side handle; free with
  *               mp_spmm_plan_free.
  * This call SYNCHRONIZES `stream` once: it copies the per-bin row counts to
- * the host to size later launches (and returns MP_ERR_SORT, with *out
- * untouched, if the device sort of the rows by class gave up its bounded
- * wait).  The plan stays valid while rowptr and plan_buf are unchanged. */
+ * the host to size later launches.  The plan stays valid while rowptr and
+ * plan_buf are unchanged. */
 int mp_spmm_plan_build(const void* rowptr, int rowptr_itype, int64_t N_dst, int64_t E,
                        int64_t F, int x_dtype, void* plan_buf, size_t plan_bytes,
                        void* stream, mp_plan** out);

@@ -1,6 +1,6 @@
 // C ABI of libmp (declared in include/mp.h): argument validation, workspace
 // layout and launch sequencing.  Every compute step runs in the HIP kernels
-// of sort.hip, scan.hip and spmm.hip; this file only checks arguments, carves
+// of the .hip sources; this file only checks arguments, carves
 // caller-provided buffers and enqueues launches.
 #include <hip/hip_runtime.h>
 
@@ -166,13 +166,11 @@ int coo_to_csr_impl(const int32_t* src, const int32_t* dst, int64_t E, int64_t N
 // ---- plan --------------------------------------------------------------------
 
 struct PlanLayout {
-    uint32_t* keys;
+    uint32_t* tile_cnt;
     int32_t* rowlist;
     int32_t* rowbeg;
     int32_t* rowend;
     uint32_t* chunk_off;
-    RadixScratch sc;
-    void* scan_ws;
     uint32_t* header;
     size_t bytes;
 };
@@ -181,14 +179,11 @@ PlanLayout plan_layout(void* buf, int64_t N) {
     PlanLayout L{};
     Carver c(buf);
     const size_t n = (size_t)(N > 0 ? N : 1);
-    L.keys = c.take<uint32_t>(n);
     L.rowlist = c.take<int32_t>(n);
     L.rowbeg = c.take<int32_t>(n);
     L.rowend = c.take<int32_t>(n);
     L.chunk_off = c.take<uint32_t>(n + 1);
-    char* scratch = c.take<char>(radix_scratch_bytes(N));
-    if (buf) L.sc = radix_scratch(scratch, N);
-    L.scan_ws = c.take<char>(scan_workspace_bytes(N + 1));
+    L.tile_cnt = c.take<uint32_t>((size_t)plan_tile_counts(N));
     L.header = c.take<uint32_t>(64);
     L.bytes = c.off;
     return L;
@@ -625,41 +620,16 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
         *out = p;
         return MP_OK;
     }
-    hipError_t e = launch_plan_classes(rowptr, rp64, N_dst, p->small_max, p->hub_min, L.keys, s);
-    if (e == hipSuccess) {
-        DigitPlan dp{};
-        dp.passes = 1;
-        dp.width[0] = dp.max_width = kPlanClassBits;
-        e = radix_sort_begin(L.keys, N_dst, dp, L.sc, s);
-    }
-    if (e == hipSuccess) {
-        RadixPass rp{};
-        rp.keys_in = L.keys;
-        rp.a_out = L.rowlist;  // payload = row id
-        rp.n = N_dst;
-        rp.pass = 0;
-        rp.shift = 0;
-        rp.bits = kPlanClassBits;
-        rp.sc = L.sc;
-        e = radix_sort_pass(rp, s);
-    }
-    if (e == hipSuccess)
-        e = launch_plan_rows(rowptr, rp64, L.rowlist, N_dst, p->hub_min, p->chunk_min, L.rowbeg,
-                             L.rowend, L.chunk_off, s);
-    // only hub rows have chunks, and they end the class-sorted list: the
-    // entries before the hub class's start are zero
-    if (e == hipSuccess)
-        e = exclusive_scan_u32(L.chunk_off, N_dst + 1, L.scan_ws, s, L.sc.gbase + kClassHub);
-    const int nclass = kClassHub + 1;
-    if (e == hipSuccess)
-        e = launch_plan_header(L.sc.gbase, nclass, L.chunk_off, N_dst, L.sc.err, L.header, s);
-    uint32_t h[64] = {0};
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(h, L.header, sizeof(uint32_t) * (nclass + 3), hipMemcpyDeviceToHost, s);
+    hipError_t e = launch_plan(PlanParams{rowptr, rp64, N_dst, p->small_max, p->hub_min,
+                                          p->chunk_min, L.tile_cnt, L.rowlist, L.rowbeg, L.rowend,
+                                          L.chunk_off, L.header},
+                               s);
+    uint32_t h[kPlanClasses + 2] = {0};
+    if (e == hipSuccess) e = hipMemcpyAsync(h, L.header, sizeof(h), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess || h[nclass + 2] != 0) {
+    if (e != hipSuccess) {
         delete p;
-        return e != hipSuccess ? MP_ERR_HIP : MP_ERR_SORT;
+        return MP_ERR_HIP;
     }
     p->mid_base = h[kClassMid];
     p->hub_base = h[kClassHub];
@@ -668,7 +638,7 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
     p->n_tiny = h[kTinyClassEnd] < (uint32_t)p->mid_base ? h[kTinyClassEnd] : p->mid_base;
     p->n_mid = p->hub_base - p->mid_base;
     p->n_hub = N_dst - p->hub_base;
-    p->n_chunks = h[nclass + 1];
+    p->n_chunks = h[kPlanClasses + 1];
     *out = p;
     return MP_OK;
 }

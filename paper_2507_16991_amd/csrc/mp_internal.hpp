@@ -59,16 +59,32 @@ inline DigitPlan digit_plan(int bits) {
     return d;
 }
 
-// ---- exclusive scan of uint32 (scan.hip) -----------------------------------
-constexpr int kScanBlock = 256;
-constexpr int kScanItems = 16;
-constexpr int kScanTile = kScanBlock * kScanItems;
-size_t scan_workspace_bytes(int64_t n);
-// In-place exclusive scan of data[0..n); returns the hipError of the launches.
-// zero_below (device word, or nullptr): the caller guarantees data[i] = 0 for
-// i < *zero_below, and the tiles wholly below it are skipped.
-hipError_t exclusive_scan_u32(uint32_t* data, int64_t n, void* ws, hipStream_t s,
-                              const uint32_t* zero_below = nullptr);
+// ---- wave-level multisplit -------------------------------------------------
+// Lanes of the wavefront that hold a valid key with the same digit as this
+// lane: one ballot per digit bit; a lane differs from this one where the
+// ballot's bit differs from this lane's own bit (sign-extended to a full
+// word, so that one XOR per half-mask finds those lanes).  The bits are
+// unrolled up to MAXBITS under a wave-uniform test.
+template <int MAXBITS>
+__device__ inline uint64_t digit_peers(bool ok, uint32_t d, int bits = MAXBITS) {
+    uint32_t dlo = 0, dhi = 0;  // lanes whose digit differs in some bit
+#pragma unroll
+    for (int b = 0; b < MAXBITS; ++b) {
+        if (b < bits) {
+            const int32_t sb = (int32_t)(d << (31 - b)) >> 31;  // 0 or -1
+            const uint64_t bal = __ballot(sb != 0);
+            dlo |= (uint32_t)bal ^ (uint32_t)sb;
+            dhi |= (uint32_t)(bal >> 32) ^ (uint32_t)sb;
+        }
+    }
+    return __ballot(ok) & ~(((uint64_t)dhi << 32) | dlo);
+}
+
+// Set bits of m below this lane.
+__device__ inline uint32_t count_below(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
 
 // ---- stable LSD radix sort, one sweep per digit (sort.hip) ----------------
 //
@@ -89,7 +105,7 @@ RadixScratch radix_scratch(void* base, int64_t n);
 
 struct RadixPass {
     const uint32_t* keys_in;  // [n]
-    const int32_t* a_in;      // [n] or nullptr: payload a = element index
+    const int32_t* a_in;      // [n]
     const int32_t* b_in;      // [n] or nullptr: payload b = element index
     uint32_t* keys_out;       // [n] or nullptr
     int32_t* a_out;           // [n] or nullptr
@@ -151,7 +167,8 @@ Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align);
 constexpr int kSmallClasses = 16;       // class c < 16: small row, deg < 2^c ... see plan
 constexpr int kClassMid = kSmallClasses;
 constexpr int kClassHub = kSmallClasses + 1;
-constexpr int kPlanClassBits = 5;       // 32 buckets (18 used)
+constexpr int kPlanClasses = kClassHub + 1;
+constexpr int kPlanClassBits = 5;       // of a class
 constexpr int kMaxChunksPerHub = 2048;  // hub rows are split into <= this many chunks
 constexpr int kTinyDeg = 7;             // rows of at most this many edges: tiny-row kernel
 constexpr int kTinyClassEnd = 4;        // classes 0..3 (bit length <= 3) are tiny
@@ -319,16 +336,25 @@ int64_t gmm_tile_cols();
 hipError_t launch_spmm(const SpmmParams& p, int x_dtype, int epl, hipStream_t s);
 hipError_t launch_spmm_tiny(const SpmmParams& p, int x_dtype, int epl, hipStream_t s);
 hipError_t launch_spmm_fixup(const SpmmParams& p, hipStream_t s);
-hipError_t launch_plan_classes(const void* rowptr, int rp64, int64_t N, int64_t small_max,
-                               int64_t hub_min, uint32_t* keys, hipStream_t s);
-// per rowlist entry: row range and hub chunk count (nch[N] = 0)
-hipError_t launch_plan_rows(const void* rowptr, int rp64, const int32_t* rowlist, int64_t N,
-                            int64_t hub_min, int chunk_min, int32_t* rowbeg, int32_t* rowend,
-                            uint32_t* nch, hipStream_t s);
-// header[c] = first rowlist position of class c (c < nclass, from the class
-// sort's exclusive digit starts), header[nclass] = N, header[nclass+1] = chunks
-hipError_t launch_plan_header(const uint32_t* class_start, int nclass, const uint32_t* chunk_off,
-                              int64_t N, const uint32_t* sort_err, uint32_t* header, hipStream_t s);
+
+// ---- plan (scan.hip) -----------------------------------------------------------
+constexpr int64_t kPlanSingleRows = 16384;  // up to here one workgroup builds the plan
+struct PlanParams {
+    const void* rowptr;
+    int rp64;
+    int64_t N;
+    int64_t small_max, hub_min;
+    int chunk_min;
+    uint32_t* tile_cnt;   // [plan_tile_counts(N)]
+    int32_t* rowlist;     // [N] rows by class, then by id
+    int32_t* rowbeg;      // [N] their ranges
+    int32_t* rowend;      // [N]
+    uint32_t* chunk_off;  // [N + 1] first chunk of every hub row's entry; [N]: all chunks
+    // first row-list position of every class, N, the number of chunks
+    uint32_t* header;     // [kPlanClasses + 2]
+};
+int64_t plan_tile_counts(int64_t N);
+hipError_t launch_plan(const PlanParams& p, hipStream_t s);
 
 // ---- edge-materialized messages (messages.hip) ----------------------------------
 struct MessageGather {

@@ -38,31 +38,6 @@ __device__ inline uint64_t desc_make(uint64_t flag, uint32_t tag, uint64_t v) {
     return flag | ((uint64_t)tag << 56) | v;
 }
 
-// Lanes of the wavefront that hold a valid key with the same digit as this
-// lane: one ballot per digit bit; a lane differs from this one where the
-// ballot's bit differs from this lane's own bit (sign-extended to a full
-// word, so that one XOR per half-mask finds those lanes).  The bits are
-// unrolled up to kSortMaxBits under a wave-uniform test.
-__device__ inline uint64_t digit_peers(bool ok, uint32_t d, int bits) {
-    uint32_t dlo = 0, dhi = 0;  // lanes whose digit differs in some bit
-#pragma unroll
-    for (int b = 0; b < kSortMaxBits; ++b) {
-        if (b < bits) {
-            const int32_t sb = (int32_t)(d << (31 - b)) >> 31;  // 0 or -1
-            const uint64_t bal = __ballot(sb != 0);
-            dlo |= (uint32_t)bal ^ (uint32_t)sb;
-            dhi |= (uint32_t)(bal >> 32) ^ (uint32_t)sb;
-        }
-    }
-    return __ballot(ok) & ~(((uint64_t)dhi << 32) | dlo);
-}
-
-// Set bits of m below this lane.
-__device__ inline uint32_t count_below(uint64_t m) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
 __global__ __launch_bounds__(256) void radix_clear(uint64_t* __restrict__ desc, int64_t ndesc,
                                                    uint32_t* __restrict__ gbase,
                                                    uint32_t* __restrict__ counter,
@@ -202,7 +177,7 @@ void radix_onesweep(RadixPass p) {
             va[k] = (int32_t)(uint32_t)kv;
         } else {
             key[k] = ok ? __builtin_nontemporal_load(p.keys_in + i) : 0u;
-            va[k] = p.a_in ? (ok ? __builtin_nontemporal_load(p.a_in + i) : 0) : (int32_t)i;
+            va[k] = ok ? __builtin_nontemporal_load(p.a_in + i) : 0;
         }
         if constexpr (HAS_B) vb[k] = p.b_in ? (ok ? __builtin_nontemporal_load(p.b_in + i) : 0) : (int32_t)i;
     }
@@ -210,7 +185,7 @@ void radix_onesweep(RadixPass p) {
     for (int k = 0; k < kSortItems; ++k) {
         const bool ok = wbase + (int64_t)k * kWave + lane < p.n;
         const uint32_t d = (key[k] >> p.shift) & (uint32_t)(R - 1);
-        const uint64_t peers = digit_peers(ok, d, p.bits);
+        const uint64_t peers = digit_peers<kSortMaxBits>(ok, d, p.bits);
         const uint32_t below = count_below(peers);
         const uint32_t base = s_cnt[wv][d];
         rank[k] = base + below;

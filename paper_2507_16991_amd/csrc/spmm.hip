@@ -1,5 +1,5 @@
 // Segmented aggregation over the destination-major CSR (the AGGREGATION step
-// of Eq. (1) in PyG 2.0, with message w * x[src]), and its degree-binned plan.
+// of Eq. (1) in PyG 2.0, with message w * x[src]).
 //
 // Work is split three ways by in-degree (Sec. 2.2: a destination-sorted layout
 // lets the aggregation run in parallel over rows), all inside ONE launch whose wavefronts take, in
@@ -1571,65 +1571,6 @@ __global__ __launch_bounds__(kFixWaves * kWave) void spmm_fixup(SpmmParams P) {
     }
 }
 
-// ---- plan kernels -------------------------------------------------------------
-
-// class of row i: small rows by bit length of the degree (0 for an empty
-// row), then mid, then hub.
-__global__ __launch_bounds__(256) void plan_classes(const void* rowptr, int rp64, int64_t N,
-                                                    int64_t small_max, int64_t hub_min,
-                                                    uint32_t* __restrict__ keys) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= N) return;
-    const int64_t d = load_rp(rowptr, rp64, i + 1) - load_rp(rowptr, rp64, i);
-    uint32_t c;
-    if (d > hub_min) c = kClassHub;
-    else if (d > small_max) c = kClassMid;
-    else c = d == 0 ? 0u : (uint32_t)(64 - __clzll((unsigned long long)d));
-    keys[i] = c;
-}
-
-// Per rowlist entry k: the row's range (rowbeg, rowend) and its chunk count
-// (0 unless the row is a hub); entry N gets 0 chunks, so that the scan of
-// the counts ends in the total.  One read of the row's two rowptr entries.
-__global__ __launch_bounds__(256) void plan_rows(const void* rowptr, int rp64,
-                                                 const int32_t* __restrict__ rowlist, int64_t N,
-                                                 int64_t hub_min, int chunk_min,
-                                                 int32_t* __restrict__ rowbeg,
-                                                 int32_t* __restrict__ rowend,
-                                                 uint32_t* __restrict__ nch) {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k > N) return;
-    if (k == N) { nch[k] = 0; return; }
-    const int64_t row = rowlist[k];
-    const int64_t b = load_rp(rowptr, rp64, row);
-    const int64_t e = load_rp(rowptr, rp64, row + 1);
-    rowbeg[k] = (int32_t)b;
-    rowend[k] = (int32_t)e;
-    const int64_t d = e - b;
-    uint32_t c = 0;
-    if (d > hub_min) {
-        int64_t csz = (d + kMaxChunksPerHub - 1) / kMaxChunksPerHub;
-        if (csz < chunk_min) csz = chunk_min;
-        c = (uint32_t)((d + csz - 1) / csz);
-    }
-    nch[k] = c;
-}
-
-// header[c] = start of class c in rowlist (c < nclass), header[nclass] = N,
-// header[nclass + 1] = total hub chunks
-// header: class starts, N, the chunk count and the sort's error word
-__global__ void plan_header(const uint32_t* __restrict__ class_start, int nclass,
-                            const uint32_t* __restrict__ chunk_off, int64_t N,
-                            const uint32_t* __restrict__ sort_err, uint32_t* __restrict__ header) {
-    const int c = threadIdx.x;
-    if (c < nclass) header[c] = class_start[c];
-    if (c == 0) {
-        header[nclass] = (uint32_t)N;
-        header[nclass + 1] = chunk_off[N];
-        header[nclass + 2] = *sort_err;
-    }
-}
-
 // masked sum: the gradient of max
 template <typename TX, int EPL, bool O32>
 hipError_t launch_masked(const SpmmParams& p, unsigned grid, hipStream_t s) {
@@ -1788,29 +1729,6 @@ hipError_t launch_spmm_fixup(const SpmmParams& p, hipStream_t s) {
     else if (hs && hm) hipLaunchKernelGGL((spmm_fixup<true, true, false>), g, b, 0, s, p);
     else if (hm) hipLaunchKernelGGL((spmm_fixup<false, true, false>), g, b, 0, s, p);
     else hipLaunchKernelGGL((spmm_fixup<true, false, false>), g, b, 0, s, p);
-    return hipGetLastError();
-}
-
-hipError_t launch_plan_classes(const void* rowptr, int rp64, int64_t N, int64_t small_max,
-                               int64_t hub_min, uint32_t* keys, hipStream_t s) {
-    if (N <= 0) return hipSuccess;
-    hipLaunchKernelGGL(plan_classes, dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, s, rowptr,
-                       rp64, N, small_max, hub_min, keys);
-    return hipGetLastError();
-}
-
-hipError_t launch_plan_rows(const void* rowptr, int rp64, const int32_t* rowlist, int64_t N,
-                            int64_t hub_min, int chunk_min, int32_t* rowbeg, int32_t* rowend,
-                            uint32_t* nch, hipStream_t s) {
-    hipLaunchKernelGGL(plan_rows, dim3((unsigned)ceil_div(N + 1, 256)), dim3(256), 0, s, rowptr,
-                       rp64, rowlist, N, hub_min, chunk_min, rowbeg, rowend, nch);
-    return hipGetLastError();
-}
-
-hipError_t launch_plan_header(const uint32_t* class_start, int nclass, const uint32_t* chunk_off,
-                              int64_t N, const uint32_t* sort_err, uint32_t* header, hipStream_t s) {
-    hipLaunchKernelGGL(plan_header, dim3(1), dim3(64), 0, s, class_start, nclass, chunk_off, N,
-                       sort_err, header);
     return hipGetLastError();
 }
 

@@ -1,0 +1,51 @@
+"""The plan's counting sort at the sizes where its launches change: one
+workgroup up to 16384 rows, tiles of 4096 rows up to 4M, of 16384 beyond.
+Every row must be aggregated exactly once, whatever its class: integer
+features, so that sums are exact, against numpy's segment sums; and the hub
+rows' chunks are counted through the workspace they need."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_16991_amd as mp
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+@pytest.fixture(autouse=True)
+def _announce(request):
+    sys.stderr.write(f"\n[gpu-case] {request.node.nodeid}\n")
+    sys.stderr.flush()
+    yield
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("N", [1, 63, 1024, 1025, 16383, 16384, 16385, 20480, 300_001, 4_194_304,
+                               4_194_305])
+@pytest.mark.parametrize("itype", [torch.int32, torch.int64])
+def test_every_row_once(N, itype):
+    F = 4
+    rng = np.random.default_rng(N)
+    deg = np.minimum(rng.zipf(1.6 if N < 1_000_000 else 2.5, N) - 1, 3000)
+    if N > 1000:
+        deg[[0, N // 2, N - 1]] = [2500, 700, 4100]
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    E = int(rp[-1])
+    x = rng.integers(-3, 4, (64, F)).astype(np.float32)
+    col = rng.integers(0, 64, E).astype(np.int32)
+    rp_d = torch.from_numpy(rp).to(DEV, itype)
+    small, hub, chunk = 32, 200, 64
+    plan = mp.Plan(rp_d, E, F, opts=(small, hub, chunk))
+    hubs = deg[deg > hub]
+    size = np.maximum((hubs + 2047) // 2048, chunk)
+    chunks = int(((hubs + size - 1) // size).sum())
+    ws = plan.workspace(mp.MP_SUM)
+    assert (0 if ws is None else ws.numel()) == (chunks * F * 4 + 255) // 256 * 256
+    col_d = torch.from_numpy(col if E else np.zeros(1, np.int32)).to(DEV)
+    out = torch.full((N, F), float("nan"), device=DEV)
+    mp.spmm(rp_d, col_d, torch.from_numpy(x).to(DEV), mp.MP_SUM, plan=plan, out=out)
+    sums = np.concatenate([np.zeros((1, F)), np.cumsum(x[col], axis=0, dtype=np.float64)])
+    assert np.array_equal(out.cpu().numpy(), (sums[rp[1:]] - sums[rp[:-1]]).astype(np.float32))
