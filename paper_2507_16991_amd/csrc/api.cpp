@@ -42,21 +42,14 @@ bool valid_reduce(int r) {
 
 // ---- COO -> CSR workspace layout ---------------------------------------------
 
-// With more than one pass, the passes before the last write (key, src)
-// packed in 8-byte words, ping-ponging between kv[0] and kv[1]; the last pass
-// writes the keys into the buffer it does not read and src into col.  The
-// COO-id payload, when asked for, ping-pongs as a 4-byte array that ends in
-// perm.  (With one pass, keys and payloads go straight to their outputs.)
-#ifndef MP_SORT_PACK
-#define MP_SORT_PACK 1
-#endif
-
+// The passes before the last write 8-byte words, ping-ponging between kv[0]
+// and kv[1]; the last writes src into col.  The COO-id payload, when asked for,
+// travels in the words, or where their bits do not suffice (which the device
+// finds out) as a 4-byte array ping-ponging between eid_tmp and the output.
 struct CsrLayout {
     DigitPlan dp;
-    int passes;
-    bool packed;
-    uint32_t *kA, *kB;
-    int32_t *src_tmp, *eid_tmp, *eid_final;
+    int key_bits;
+    int32_t *eid_tmp, *eid_final;
     uint64_t* kv[2];
     RadixScratch sc;
     size_t bytes;
@@ -64,25 +57,16 @@ struct CsrLayout {
 
 CsrLayout csr_layout(void* ws, int64_t E, int64_t N, int with_payload) {
     CsrLayout L{};
-    L.dp = digit_plan(key_bits(N));
-    L.passes = L.dp.passes;
+    L.key_bits = key_bits(N);
+    L.dp = digit_plan(L.key_bits);
     Carver c(ws);
     const size_t e = (size_t)(E > 0 ? E : 1);
-    L.packed = MP_SORT_PACK && L.passes > 1;
-    if (L.packed) {
-        L.kv[0] = c.take<uint64_t>(e);
-        L.kv[1] = c.take<uint64_t>(e);
-        // pass passes-1 reads kv[(passes-2) % 2]
-        L.kA = reinterpret_cast<uint32_t*>(L.kv[(L.passes - 1) % 2]);
-    } else {
-        L.kA = c.take<uint32_t>(e);
-        L.kB = L.passes > 1 ? c.take<uint32_t>(e) : nullptr;
-        L.src_tmp = L.passes > 1 ? c.take<int32_t>(e) : nullptr;
-    }
-    L.eid_tmp = (with_payload && L.passes > 1) ? c.take<int32_t>(e) : nullptr;
+    L.kv[0] = L.dp.passes > 1 ? c.take<uint64_t>(e) : nullptr;
+    L.kv[1] = L.dp.passes > 2 ? c.take<uint64_t>(e) : nullptr;
+    L.eid_tmp = (with_payload && L.dp.passes > 1) ? c.take<int32_t>(e) : nullptr;
     L.eid_final = with_payload ? c.take<int32_t>(e) : nullptr;
-    char* scratch = c.take<char>(radix_scratch_bytes(E));
-    if (ws) L.sc = radix_scratch(scratch, E);
+    char* scratch = c.take<char>(radix_scratch_bytes(E, N));
+    if (ws) L.sc = radix_scratch(scratch, E, N);
     L.bytes = c.off;
     return L;
 }
@@ -92,75 +76,56 @@ int check_csr_sizes(int64_t E, int64_t N) {
     return MP_OK;
 }
 
+// a_bits: bits of every src (0: not known).
 int coo_to_csr_impl(const int32_t* src, const int32_t* dst, int64_t E, int64_t N, void* rowptr,
                     int itype, int32_t* col, int32_t* perm, const float* val_in, float* val_out,
-                    void* ws, size_t ws_bytes, int32_t* status, hipStream_t s) {
+                    int a_bits, void* ws, size_t ws_bytes, int32_t* status, hipStream_t s) {
     const int rp64 = itype == MP_I64;
     if (E == 0) {
         hipError_t e = launch_fill_rowptr_zero(N, rowptr, rp64, s);
-        if (e == hipSuccess) e = launch_sort_status(nullptr, status, s);
+        if (e == hipSuccess) e = launch_status_ok(status, s);
         return hip_status(e);
     }
     const int payload = (perm != nullptr || val_out != nullptr) ? 1 : 0;
     CsrLayout L = csr_layout(ws, E, N, payload);
     if (ws_bytes < L.bytes) return MP_ERR_WORKSPACE;
     int32_t* eid_final = perm ? perm : L.eid_final;
+    const int passes = L.dp.passes;
 
-    const uint32_t* keys_in = reinterpret_cast<const uint32_t*>(dst);
-    if (radix_sort_begin(keys_in, E, L.dp, L.sc, s) != hipSuccess) return MP_ERR_HIP;
-    const int32_t* a_in = src;
-    const int32_t* b_in = nullptr;  // COO id = element index in the first pass
-    for (int p = 0; p < L.passes && L.packed; ++p) {
-        const bool last_parity = ((L.passes - 1 - p) % 2) == 0;  // lands where the final pass writes
+    const uint32_t* keys = reinterpret_cast<const uint32_t*>(dst);
+    const int32_t* measure = payload && !a_bits ? src : nullptr;
+    if (radix_sort_begin(keys, measure, E, N, L.dp, L.sc, s) != hipSuccess) return MP_ERR_HIP;
+    for (int p = 0; p < passes; ++p) {
+        const bool last_parity = ((passes - 1 - p) % 2) == 0;  // lands where the final pass writes
         RadixPass rp{};
         if (p == 0) {
-            rp.keys_in = keys_in;
-            rp.a_in = a_in;
+            rp.keys_in = keys;
+            rp.a_in = src;
         } else {
             rp.kv_in = L.kv[(p - 1) % 2];
+            rp.b_in = payload ? (last_parity ? L.eid_tmp : eid_final) : nullptr;
+            rp.prev_shift = L.dp.shift[p - 1];
+            rp.prev_bits = L.dp.width[p - 1];
         }
-        if (p < L.passes - 1) {
-            rp.kv_out = L.kv[p % 2];
-        } else {
-            rp.keys_out = L.kA;
-            rp.a_out = col;
-        }
-        rp.b_in = b_in;
+        if (p < passes - 1) rp.kv_out = L.kv[p % 2];
+        else rp.a_out = col;
         rp.b_out = payload ? (last_parity ? eid_final : L.eid_tmp) : nullptr;
-        b_in = rp.b_out;
         rp.n = E;
+        rp.rows = N;
         rp.pass = p;
         rp.shift = L.dp.shift[p];
         rp.bits = L.dp.width[p];
+        rp.key_bits = L.key_bits;
+        rp.a_bits = a_bits;
+        rp.b_bits = key_bits(E);
+        rp.min_width = L.dp.min_width;
+        rp.max_width = L.dp.max_width;
         rp.sc = L.sc;
         if (radix_sort_pass(rp, s) != hipSuccess) return MP_ERR_HIP;
     }
-    for (int p = 0; p < L.passes && !L.packed; ++p) {
-        const bool last_parity = ((L.passes - 1 - p) % 2) == 0;  // lands where the final pass writes
-        RadixPass rp{};
-        rp.keys_in = keys_in;
-        rp.a_in = a_in;
-        rp.b_in = b_in;
-        rp.keys_out = last_parity ? L.kA : L.kB;
-        rp.a_out = last_parity ? col : L.src_tmp;
-        rp.b_out = payload ? (last_parity ? eid_final : L.eid_tmp) : nullptr;
-        rp.n = E;
-        rp.pass = p;
-        rp.shift = L.dp.shift[p];
-        rp.bits = L.dp.width[p];
-        rp.sc = L.sc;
-        if (radix_sort_pass(rp, s) != hipSuccess) return MP_ERR_HIP;
-        keys_in = rp.keys_out;
-        a_in = rp.a_out;
-        b_in = rp.b_out;
-    }
-    hipError_t e = launch_rowptr_from_sorted(L.kA, E, N, rowptr, rp64, L.sc.err, s);
-    if (e != hipSuccess) return MP_ERR_HIP;
-    if (val_in && val_out) {
-        e = launch_gather_f32(val_in, eid_final, E, val_out, s);
-        if (e != hipSuccess) return MP_ERR_HIP;
-    }
-    return hip_status(launch_sort_status(&L.sc, status, s));
+    hipError_t e = launch_rowptr_from_starts(L.sc, E, N, rowptr, rp64, status, s);
+    if (e == hipSuccess && val_in && val_out) e = launch_gather_f32(val_in, eid_final, E, val_out, s);
+    return hip_status(e);
 }
 
 // ---- plan --------------------------------------------------------------------
@@ -537,7 +502,7 @@ int mp_coo_to_csr(const int32_t* src, const int32_t* dst, int64_t E, int64_t N, 
     if (E > 0 && (val_in == nullptr) != (val_out == nullptr)) return MP_ERR_NULL;
     if ((uintptr_t)rowptr % (rowptr_itype == MP_I64 ? 8 : 4) || (uintptr_t)status % 4)
         return MP_ERR_ALIGN;
-    return coo_to_csr_impl(src, dst, E, N, rowptr, rowptr_itype, col, perm, val_in, val_out, ws,
+    return coo_to_csr_impl(src, dst, E, N, rowptr, rowptr_itype, col, perm, val_in, val_out, 0, ws,
                            ws_bytes, status, as_stream(stream));
 }
 
@@ -797,7 +762,7 @@ int mp_csr_transpose(const void* rowptr, int rowptr_itype, const int32_t* col, i
     hipStream_t s = as_stream(stream);
     if (E == 0) {
         hipError_t e = launch_fill_rowptr_zero(N_src, rowptrT, rowptrT_itype == MP_I64, s);
-        if (e == hipSuccess) e = launch_sort_status(nullptr, status, s);
+        if (e == hipSuccess) e = launch_status_ok(status, s);
         return hip_status(e);
     }
     size_t need = 0;
@@ -810,7 +775,8 @@ int mp_csr_transpose(const void* rowptr, int rowptr_itype, const int32_t* col, i
     if (launch_rows_of_edges(rowptr, rowptr_itype == MP_I64, N_dst, E, row, s) != hipSuccess)
         return MP_ERR_HIP;
     return coo_to_csr_impl(row, col, E, N_src, rowptrT, rowptrT_itype, colT, posT, val_in,
-                           val_out, static_cast<char*>(ws) + c.off, ws_bytes - c.off, status, s);
+                           val_out, key_bits(N_dst), static_cast<char*>(ws) + c.off,
+                           ws_bytes - c.off, status, s);
 }
 
 // Extra workspace of mp_spmm_backward_x beyond the aggregation's own: the
@@ -1347,7 +1313,7 @@ int mp_hetero_build(int n_types, const int64_t* N_per_type, int n_rel, const mp_
         off += R.E;
     }
     return coo_to_csr_impl(src_g, dst_c, E_T, N_rows, rowptr, rowptr_itype, col, nullptr,
-                           nullptr, nullptr, c.base + c.off, ws_bytes - c.off, status, s);
+                           nullptr, nullptr, 0, c.base + c.off, ws_bytes - c.off, status, s);
 }
 
 int mp_hetero_spmm(int n_types, const int64_t* N_per_type, const void* const* x_per_type,

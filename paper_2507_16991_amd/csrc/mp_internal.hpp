@@ -44,10 +44,11 @@ inline int key_bits(int64_t n) {
 struct DigitPlan {
     int passes;
     int shift[4], width[4];
-    int max_width;
+    int min_width, max_width;
 };
 inline DigitPlan digit_plan(int bits) {
     DigitPlan d{};
+    d.min_width = kSortMaxBits;
     d.passes = (bits + kSortMaxBits - 1) / kSortMaxBits;
     const int base = bits / d.passes, extra = bits % d.passes;
     for (int p = 0, s = 0; p < d.passes; ++p) {
@@ -55,6 +56,7 @@ inline DigitPlan digit_plan(int bits) {
         d.shift[p] = s;
         s += d.width[p];
         if (d.width[p] > d.max_width) d.max_width = d.width[p];
+        if (d.width[p] < d.min_width) d.min_width = d.width[p];
     }
     return d;
 }
@@ -89,46 +91,56 @@ __device__ inline uint32_t count_below(uint64_t m) {
 // ---- stable LSD radix sort, one sweep per digit (sort.hip) ----------------
 //
 // radix_sort_begin() computes the global digit histogram of every pass in one
-// read of the keys (and clears the look-back descriptors); then each
-// radix_sort_pass() ranks, offsets and scatters in a single kernel, getting
-// the offsets of earlier tiles by decoupled look-back.
+// read of the keys (and clears the scratch); then each radix_sort_pass()
+// ranks, offsets and scatters in a single kernel, getting the offsets of
+// earlier tiles by decoupled look-back.
 constexpr int kMaxPasses = 4;  // keys of at most 31 bits, digits of at most 9 bits
 
 struct RadixScratch {
     uint64_t* desc;     // [tiles * R] look-back descriptors (R = 2^bits <= 512)
-    uint32_t* gbase;    // [kMaxPasses * 512] global digit histogram -> exclusive starts
+    uint32_t* ghist;    // [kMaxPasses * 512] global digit histograms
     uint32_t* counter;  // [kMaxPasses] dynamic tile ids
     uint32_t* err;      // nonzero: a look-back wait gave up (the result is invalid)
+    uint32_t* a_or;     // the OR of payload a (where it was asked for)
+    uint32_t* starts;   // [N] first position of every row that has edges
+    uint32_t* first;    // [tiles of N + 1 rows] scratch of rowptr
+    size_t bytes;
 };
-size_t radix_scratch_bytes(int64_t n);
-RadixScratch radix_scratch(void* base, int64_t n);
+// n keys below N; base may be nullptr (sizes only)
+size_t radix_scratch_bytes(int64_t n, int64_t N);
+RadixScratch radix_scratch(void* base, int64_t n, int64_t N);
 
 struct RadixPass {
+    // the first pass reads keys_in and a_in (b is the element's index), the
+    // others kv_in (and b_in, where words have no room for b)
     const uint32_t* keys_in;  // [n]
     const int32_t* a_in;      // [n]
-    const int32_t* b_in;      // [n] or nullptr: payload b = element index
-    uint32_t* keys_out;       // [n] or nullptr
-    int32_t* a_out;           // [n] or nullptr
-    int32_t* b_out;           // [n] or nullptr
-    // packed (key << 32 | payload a) words in place of keys_in and a_in
-    // (kv_in) or keys_out and a_out (kv_out)
-    const uint64_t* kv_in;    // [n] or nullptr
-    uint64_t* kv_out;         // [n] or nullptr
-    int64_t n;
+    const uint64_t* kv_in;    // [n]
+    const int32_t* b_in;      // [n], with b_out
+    // the last pass writes a_out (and b_out) and the rows' starts, the others
+    // kv_out (and b_out)
+    int32_t* a_out;           // [n]
+    int32_t* b_out;           // [n], or nullptr: b is not carried
+    uint64_t* kv_out;         // [n]
+    int64_t n, rows;          // keys lie below rows
     int pass, shift, bits;
+    int prev_shift, prev_bits;  // the digit of the pass before
+    // with b: bits of a key, of a (0: as many as sc.a_or says) and of b, and
+    // the narrowest and widest digit of the passes
+    int key_bits, a_bits, b_bits, min_width, max_width;
     RadixScratch sc;
 };
-hipError_t radix_sort_begin(const uint32_t* keys, int64_t n, const DigitPlan& dp,
-                            const RadixScratch& sc, hipStream_t s);
+// a: nullptr, or the payload whose bits sc.a_or collects
+hipError_t radix_sort_begin(const uint32_t* keys, const int32_t* a, int64_t n, int64_t N,
+                            const DigitPlan& dp, const RadixScratch& sc, hipStream_t s);
 hipError_t radix_sort_pass(const RadixPass& p, hipStream_t s);
 
-// Write the caller's status word (nullptr: nothing) from the error word of
-// the sort that used sc (sc nullptr: no sort ran, MP_OK).
-hipError_t launch_sort_status(const RadixScratch* sc, int32_t* status, hipStream_t s);
-// rowptr of keys sorted by a radix sort whose error word is sort_err (the
-// kernel does nothing when the sort failed); nullptr: no such word
-hipError_t launch_rowptr_from_sorted(const uint32_t* keys, int64_t E, int64_t N, void* rowptr,
-                                     int rp64, const uint32_t* sort_err, hipStream_t s);
+// Write MP_OK into the caller's status word (nullptr: nothing).
+hipError_t launch_status_ok(int32_t* status, hipStream_t s);
+// After the last pass: rowptr (left alone if the sort failed) and the
+// caller's status word (nullptr: not wanted).
+hipError_t launch_rowptr_from_starts(const RadixScratch& sc, int64_t E, int64_t N, void* rowptr,
+                                     int rp64, int32_t* status, hipStream_t s);
 // rowptr of keys sorted by the caller, by binary search (bounded work for
 // any order of keys)
 hipError_t launch_rowptr_by_search(const uint32_t* keys, int64_t E, int64_t N, void* rowptr,

@@ -1,5 +1,5 @@
 // Stable LSD radix sort of COO edges by destination, and the small kernels
-// around it (rowptr from the sorted keys, payload gather, validation).
+// around it (rowptr, payload gather, validation).
 //
 // The sort is one-sweep: radix_ghist counts the digits of every pass in one
 // read of the keys; then each pass is ONE kernel, radix_onesweep, in which a
@@ -13,10 +13,21 @@
 // ascending COO id within a destination (the order the CSR of Sec. 2.2 must
 // have to be unique).  Only integer arithmetic: the result is bit-exact.
 //
+// Between passes an element is one 8-byte word, so that a digit run is one
+// stretch of memory: (key, src), or with the COO-id payload (key, src, id)
+// packed where their bits fit 64.  To make them fit, a word leaves out the
+// digit its pass has just sorted by: the element's place says it, and the
+// next pass puts it back (124M edges, 2.4M rows: 15 + 22 + 27 bits).  The last
+// pass writes src and id alone; rowptr comes from where it sees each row
+// start.  (Carrying id as a third array and keeping the sorted keys for rowptr
+// cost 80 bytes of traffic per edge where this takes 56 to 60: passes of 790,
+// 880 and 898 us on 124M edges -> 601, 663 and 800, rowptr 155 -> 27; CSR with
+// ids and transpose together 6.05 -> 4.85 ms.)
+//
 // The look-back only waits on tiles that started earlier (their ids were
 // taken first), so it always ends; its wait is nevertheless bounded, and a
 // tile that gives up records it in an error word that the caller turns into
-// MP_ERR_SORT (radix_status) instead of hanging the device.
+// MP_ERR_SORT instead of hanging the device.
 #include "mp_internal.hpp"
 
 namespace mp {
@@ -26,9 +37,12 @@ constexpr int kSortWaves = kSortBlock / kWave;
 constexpr int kWaveKeys = kWave * kSortItems;  // keys per wavefront per tile
 constexpr int kMaxBuckets = 1 << kSortMaxBits;
 
-constexpr int kGhistBlock = 256;
+constexpr int kGhistBlock = 1024;
 constexpr int kGhistItems = 8;
+constexpr int kGhistCopies = 4;     // LDS copies of the histogram, four wavefronts each
+constexpr int kGhistMaxGrid = 512;  // two workgroups per CU
 constexpr uint32_t kSpinLimit = 1u << 20;
+constexpr uint32_t kNoStart = 0xFFFFFFFFu;  // a row no edge of which has been seen
 
 // look-back descriptor: flag (bits 63..62: 1 tile count, 2 inclusive prefix),
 // pass tag (bits 61..56, pass + 1), value (bits 55..0)
@@ -38,72 +52,141 @@ __device__ inline uint64_t desc_make(uint64_t flag, uint32_t tag, uint64_t v) {
     return flag | ((uint64_t)tag << 56) | v;
 }
 
-__global__ __launch_bounds__(256) void radix_clear(uint64_t* __restrict__ desc, int64_t ndesc,
-                                                   uint32_t* __restrict__ gbase,
-                                                   uint32_t* __restrict__ counter,
-                                                   uint32_t* __restrict__ err) {
+__global__ __launch_bounds__(256) void radix_clear(RadixScratch sc, int64_t ndesc, int64_t nstarts) {
     const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    for (int64_t i = i0; i < ndesc; i += (int64_t)gridDim.x * 256) desc[i] = 0;
-    if (i0 < kMaxPasses * kMaxBuckets) gbase[i0] = 0;
-    if (i0 < kMaxPasses) counter[i0] = 0;
-    if (i0 == 0) *err = 0;
+    const int64_t step = (int64_t)gridDim.x * 256;
+    for (int64_t i = i0; i < ndesc; i += step) sc.desc[i] = 0;
+    for (int64_t i = i0; i < nstarts; i += step) sc.starts[i] = kNoStart;
+    if (i0 < kMaxPasses * kMaxBuckets) sc.ghist[i0] = 0;
+    if (i0 < kMaxPasses) sc.counter[i0] = 0;
+    if (i0 == 0) {
+        *sc.err = 0;
+        *sc.a_or = 0;
+    }
 }
 
 // Global histogram of every pass's digit.  Counts do not depend on order, so
-// each wavefront adds into its own LDS copy with integer atomics (no ranking
-// needed), then one integer atomic per (pass, digit) per workgroup.
-// shifts and widths: one byte per pass (pass p in bits 8p..8p+7).
+// the wavefronts add into LDS copies with integer atomics (no ranking
+// needed), then one integer atomic per (pass, digit) per workgroup.  Few,
+// large workgroups: with 2048 of 256 threads the additions to the same 1536
+// words were most of the time of a 20M-edge sort's histogram (52 us).
+// shifts and widths: one byte per pass (pass p in bits 8p..8p+7).  With a, the
+// bits of that payload are collected too.
 __global__ __launch_bounds__(kGhistBlock) void radix_ghist(const uint32_t* __restrict__ keys,
+                                                           const int32_t* __restrict__ a,
                                                            int64_t n, int passes, uint32_t shifts,
-                                                           uint32_t widths,
-                                                           uint32_t* __restrict__ ghist) {
-    constexpr int W = kGhistBlock / kWave;
-    __shared__ uint32_t h[W][kMaxPasses][kMaxBuckets];
-    for (int i = threadIdx.x; i < W * kMaxPasses * kMaxBuckets; i += kGhistBlock)
+                                                           uint32_t widths, RadixScratch sc) {
+    __shared__ uint32_t h[kGhistCopies][kMaxPasses][kMaxBuckets];
+    for (int i = threadIdx.x; i < kGhistCopies * kMaxPasses * kMaxBuckets; i += kGhistBlock)
         (&h[0][0][0])[i] = 0;
     __syncthreads();
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wv = threadIdx.x / kWave;
-    const int64_t stride = (int64_t)gridDim.x * W * kWave * kGhistItems;
-    for (int64_t base = ((int64_t)blockIdx.x * W + wv) * kWave * kGhistItems; base < n;
-         base += stride) {
+    uint32_t(*const my)[kMaxBuckets] = h[(threadIdx.x / kWave) % kGhistCopies];
+    uint32_t bits = 0;
+    const int64_t tile = (int64_t)kGhistBlock * kGhistItems;
+    for (int64_t base = blockIdx.x * tile; base < n; base += gridDim.x * tile) {
         uint32_t key[kGhistItems];
 #pragma unroll
         for (int k = 0; k < kGhistItems; ++k) {
-            const int64_t i = base + (int64_t)k * kWave + lane;
+            const int64_t i = base + k * kGhistBlock + threadIdx.x;
             key[k] = i < n ? __builtin_nontemporal_load(keys + i) : 0u;
+            if (a) bits |= i < n ? (uint32_t)__builtin_nontemporal_load(a + i) : 0u;
         }
 #pragma unroll
         for (int k = 0; k < kGhistItems; ++k) {
-            if (base + (int64_t)k * kWave + lane >= n) continue;
+            if (base + k * kGhistBlock + threadIdx.x >= n) continue;
             for (int p = 0; p < passes; ++p) {
                 const uint32_t sh = (shifts >> (8 * p)) & 255u;
                 const uint32_t mask = (1u << ((widths >> (8 * p)) & 255u)) - 1u;
-                atomicAdd(&h[wv][p][(key[k] >> sh) & mask], 1u);
+                atomicAdd(&my[p][(key[k] >> sh) & mask], 1u);
             }
         }
+    }
+    if (a) {
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) bits |= __shfl_xor(bits, off);
+        if ((threadIdx.x & (kWave - 1)) == 0 && bits) atomicOr(sc.a_or, bits);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < passes * kMaxBuckets; i += kGhistBlock) {
         uint32_t t = 0;
 #pragma unroll
-        for (int w = 0; w < W; ++w) t += (&h[w][0][0])[i];
-        if (t) atomicAdd(&ghist[i], t);
+        for (int c = 0; c < kGhistCopies; ++c) t += (&h[c][0][0])[i];
+        if (t) atomicAdd(&sc.ghist[i], t);
     }
 }
 
-// In place: per pass, exclusive scan over its digit counts (the counts of
-// digits beyond a pass's width are zero).
-__global__ void radix_gscan(uint32_t* __restrict__ g, int passes) {
-    const int p = threadIdx.x;
-    if (p >= passes) return;
-    uint32_t run = 0;
-    for (int d = 0; d < kMaxBuckets; ++d) {
-        const uint32_t c = g[p * kMaxBuckets + d];
-        g[p * kMaxBuckets + d] = run;
-        run += c;
+// Exclusive scan over N values of LDS or global memory by one wavefront
+// (lane l takes N / 64 consecutive ones), to LDS.
+template <int N>
+__device__ inline void wave_exclusive(const uint32_t* in, int n, uint32_t* out, int lane) {
+    constexpr int PER = N / kWave;
+    uint32_t t[PER];
+    uint32_t sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int d = lane * PER + k;
+        t[k] = d < n ? in[d] : 0u;
+        sum += t[k];
+    }
+    uint32_t inc = sum;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t o = __shfl_up(inc, off, kWave);
+        if (lane >= off) inc += o;
+    }
+    uint32_t run = inc - sum;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int d = lane * PER + k;
+        if (d < n) out[d] = run;
+        run += t[k];
     }
 }
+
+// How the passes carry (key, a, b) between them: kWide, a (key << 32 | a) word
+// and a 4-byte array of b; kKeep, one word of the key, a and b; kDrop, one
+// word of the key without the digit just sorted by, a and b.  Decided on the
+// device, from the bits a really has.
+constexpr int kWide = 0, kKeep = 1, kDrop = 2;
+__device__ inline int word_format(const RadixPass& p, int abits) {
+    if (p.key_bits + abits + p.b_bits <= 64) return kKeep;
+    // (a staged word without its digit needs the digit map, which has bytes)
+    if (p.max_width <= 8 && p.key_bits - p.min_width + abits + p.b_bits <= 64) return kDrop;
+    return kWide;
+}
+
+// key (at most 31 bits) without the digit at [shift, shift + width), and back
+__device__ inline uint32_t drop_digit(uint32_t key, int shift, int width) {
+    return ((key >> (shift + width)) << shift) | (key & ((1u << shift) - 1u));
+}
+__device__ inline uint32_t put_digit(uint32_t rest, uint32_t d, int shift, int width) {
+    return ((rest >> shift) << (shift + width)) | (d << shift) | (rest & ((1u << shift) - 1u));
+}
+
+// A packed word: b in the low bb bits, a in the next ab, the key above, in
+// 32-bit operations on its halves (1 <= ab <= 32, 1 <= bb <= 31).
+struct WordBits {
+    int ab, bb;
+    __device__ inline void pack(uint32_t key, uint32_t a, uint32_t b, uint32_t& hi, uint32_t& lo) const {
+        lo = b | (a << bb);
+        hi = a >> (32 - bb);
+        const int kb = ab + bb;  // the key's place
+        if (kb >= 32) {
+            hi |= key << (kb - 32);
+        } else {
+            lo |= key << kb;
+            hi |= key >> (32 - kb);
+        }
+    }
+    __device__ inline uint32_t key(uint32_t hi, uint32_t lo) const {
+        const int kb = ab + bb;
+        return kb >= 32 ? hi >> (kb - 32) : __builtin_amdgcn_alignbit(hi, lo, kb);
+    }
+    __device__ inline int32_t a(uint32_t hi, uint32_t lo) const {
+        return (int32_t)(__builtin_amdgcn_alignbit(hi, lo, bb) & (0xFFFFFFFFu >> (32 - ab)));
+    }
+    __device__ inline int32_t b(uint32_t lo) const { return (int32_t)(lo & ((1u << bb) - 1u)); }
+};
 
 // One LSD pass: rank the tile's keys stably (wave-level multisplit, per-wave
 // LDS counters), publish the tile's digit counts, stage the tile in LDS in
@@ -114,42 +197,31 @@ __global__ void radix_gscan(uint32_t* __restrict__ g, int passes) {
 // registers of the keys while the tile waits on its predecessors, so the
 // look-back can keep kLookWindow descriptor loads in flight.  Descriptors of
 // a pass over R = 2^bits digits lie R apart per tile.
-//   HAS_B: the second payload is carried.
+//   HAS_B: the COO-id payload b is carried (b = the element index on FIRST).
 //   WIDE:  digits of up to 9 bits (512 buckets: twice the per-wave counters).
-//   PIN, POUT: the keys and payload a are read (written) as one array of
-//          (key << 32 | a) words instead of two arrays; between passes this
-//          makes each digit run one contiguous stretch of memory of twice the
-//          length rather than two, which the scattered writes of a pass
-//          favour.  A pass that stages one array at a time (ONEBUF) writes a
-//          word's two halves in turn, the key with the keys and a with the
-//          payload, to the same lines shortly apart.
-// A tile's arrays are staged in LDS all at once where they fit beside the
-// counters (one payload); otherwise (ONEBUF) the keys and then each payload
-// go through one staging buffer in turn: keys before the look-back, each
-// payload after the previous array is written.
+//   FIRST: keys and a are read as given; otherwise as words (word_format).
+//   LAST:  a (and b) are written alone, and where the tile first sees a row,
+//          starts[row] takes the place (the least over all tiles: a row's
+//          edges lie together, in tile order); otherwise words are written.
+// A tile's words are staged in LDS as two halves at once (128 KB); in kWide
+// with b, the keys, a and b go through one staging buffer in turn, the keys
+// before the look-back and the others after the previous array is written.
+// In kDrop, as a staged word has no digit, a byte per slot keeps it.
 constexpr int kLookWindow = 4;
-// tiles resident per CU, as the LDS allows: two of 512 threads or one of 1024
-constexpr int kSortTilesPerCU = kSortBlock >= 1024 ? 1 : 2;
-constexpr int kMaxLdsBytes = 160 * 1024;  // LDS of one workgroup on gfx950
 
-template <bool HAS_B, bool WIDE, bool PIN, bool POUT>
-__global__ __launch_bounds__(kSortBlock)
-__attribute__((amdgpu_waves_per_eu(HAS_B ? 1 : kSortTilesPerCU * kSortBlock / 256)))
-void radix_onesweep(RadixPass p) {
+template <bool HAS_B, bool WIDE, bool FIRST, bool LAST>
+__global__ __launch_bounds__(kSortBlock) void radix_onesweep(RadixPass p) {
     static_assert(kSortTile <= 65536, "16-bit counters and staged slots");
     constexpr int NB = WIDE ? kMaxBuckets : kMaxBuckets / 2;  // buckets this variant handles
     // per-wave digit counts, then each wave's run start inside its digit
     using cnt_t = uint16_t;
-    // all arrays staged at once where they fit in LDS, else one at a time
-    constexpr int kFixedLds = kSortWaves * NB * (int)sizeof(cnt_t) + 3 * NB * 4 + 16;
-    constexpr bool ONEBUF = (HAS_B ? 3 : 2) * kSortTile * 4 + kFixedLds > kMaxLdsBytes;
-    constexpr int NSTAGE = ONEBUF ? 1 : (HAS_B ? 3 : 2);  // staging arrays
-    __shared__ uint32_t s_stage[NSTAGE][kSortTile];
-    __shared__ uint16_t s_lp[ONEBUF ? kSortTile : 1];  // ONEBUF: staged slot of every key
+    __shared__ uint32_t s_stage[2][kSortTile];
+    __shared__ uint8_t s_dig[HAS_B && !WIDE ? kSortTile : 1];  // kDrop: digit of every slot
     __shared__ cnt_t s_cnt[kSortWaves][NB];
     __shared__ uint32_t s_tcnt[NB];   // the tile's count of each digit
     __shared__ uint32_t s_start[NB];  // ... and its exclusive scan
-    __shared__ uint32_t s_gbase[NB];
+    __shared__ uint32_t s_gbase[NB];  // global start of each digit, then of the tile's run
+    __shared__ uint32_t s_prev[HAS_B && !FIRST && !WIDE ? NB : 1];  // kDrop: the last pass's digit starts
     __shared__ uint32_t s_tile;
 
     const int R = 1 << p.bits;
@@ -157,6 +229,17 @@ void radix_onesweep(RadixPass p) {
     const int wv = threadIdx.x / kWave;
     for (int i = threadIdx.x; i < kSortWaves * NB; i += kSortBlock) (&s_cnt[0][0])[i] = 0;
     if (threadIdx.x == 0) s_tile = atomicAdd(&p.sc.counter[p.pass], 1u);
+    int abits = 0, fmt = kWide;
+    if constexpr (HAS_B) {
+        abits = p.a_bits ? p.a_bits : 32 - __clz((int)(*p.sc.a_or | 1u));
+        fmt = word_format(p, abits);
+    }
+    const WordBits word{abits, p.b_bits};
+    const bool drop = HAS_B && !WIDE && fmt == kDrop;
+    if constexpr (HAS_B && !FIRST && !WIDE) {
+        if (wv == 1 && fmt == kDrop)
+            wave_exclusive<NB>(p.sc.ghist + (p.pass - 1) * kMaxBuckets, 1 << p.prev_bits, s_prev, lane);
+    }
     __syncthreads();
     const int64_t tile = s_tile;
     uint64_t* const desc = p.sc.desc + tile * R;
@@ -165,21 +248,70 @@ void radix_onesweep(RadixPass p) {
     const int64_t wbase = tbase + (int64_t)wv * kWaveKeys;
 
     uint32_t key[kSortItems];
-    int32_t va[kSortItems], vb[kSortItems];
+    int32_t va[kSortItems], vb[HAS_B ? kSortItems : 1];
     uint32_t rank[kSortItems];
+    if constexpr (FIRST) {
 #pragma unroll
-    for (int k = 0; k < kSortItems; ++k) {
-        const int64_t i = wbase + (int64_t)k * kWave + lane;
-        const bool ok = i < p.n;
-        if constexpr (PIN) {
-            const uint64_t kv = ok ? __builtin_nontemporal_load(p.kv_in + i) : 0ull;
-            key[k] = (uint32_t)(kv >> 32);
-            va[k] = (int32_t)(uint32_t)kv;
-        } else {
+        for (int k = 0; k < kSortItems; ++k) {
+            const int64_t i = wbase + (int64_t)k * kWave + lane;
+            const bool ok = i < p.n;
             key[k] = ok ? __builtin_nontemporal_load(p.keys_in + i) : 0u;
             va[k] = ok ? __builtin_nontemporal_load(p.a_in + i) : 0;
+            if constexpr (HAS_B) vb[k] = (int32_t)i;
         }
-        if constexpr (HAS_B) vb[k] = p.b_in ? (ok ? __builtin_nontemporal_load(p.b_in + i) : 0) : (int32_t)i;
+    } else {
+        uint64_t w[kSortItems];
+#pragma unroll
+        for (int k = 0; k < kSortItems; ++k) {
+            const int64_t i = wbase + (int64_t)k * kWave + lane;
+            w[k] = i < p.n ? __builtin_nontemporal_load(p.kv_in + i) : 0ull;
+        }
+        if (!HAS_B || fmt == kWide) {
+#pragma unroll
+            for (int k = 0; k < kSortItems; ++k) {
+                key[k] = (uint32_t)(w[k] >> 32);
+                va[k] = (int32_t)(uint32_t)w[k];
+                if constexpr (HAS_B) {
+                    const int64_t i = wbase + (int64_t)k * kWave + lane;
+                    vb[k] = i < p.n ? __builtin_nontemporal_load(p.b_in + i) : 0;
+                }
+            }
+        } else if constexpr (HAS_B) {
+#pragma unroll
+            for (int k = 0; k < kSortItems; ++k) {
+                const uint32_t hi = (uint32_t)(w[k] >> 32), lo = (uint32_t)w[k];
+                key[k] = word.key(hi, lo);
+                va[k] = word.a(hi, lo);
+                vb[k] = word.b(lo);
+            }
+            if constexpr (!WIDE) {
+                if (drop) {
+                    // the digit of the last pass, from the place: the last d
+                    // whose run starts at or before it.  A wavefront's places
+                    // mostly lie in one run.
+                    const int PR = 1 << p.prev_bits;
+                    auto count_le = [&](int64_t pos) {  // run starts at or before pos
+                        int c = 0;
+                        for (int d = 0; d < PR; d += kWave)
+                            c += __popcll(__ballot(d + lane < PR && (int64_t)s_prev[d + lane] <= pos));
+                        return c;
+                    };
+                    const int64_t last = wbase + kWaveKeys - 1 < p.n ? wbase + kWaveKeys - 1 : p.n - 1;
+                    const int dA = count_le(wbase) - 1;
+                    const int dB = last > wbase ? count_le(last) - 1 : dA;
+#pragma unroll
+                    for (int k = 0; k < kSortItems; ++k) {
+                        const int64_t i = wbase + (int64_t)k * kWave + lane;
+                        int lo = dA, hi = dB;
+                        while (lo < hi) {
+                            const int mid = (lo + hi + 1) >> 1;
+                            if ((int64_t)s_prev[mid] <= i) lo = mid; else hi = mid - 1;
+                        }
+                        key[k] = put_digit(key[k], (uint32_t)lo, p.prev_shift, p.prev_bits);
+                    }
+                }
+            }
+        }
     }
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
@@ -212,48 +344,34 @@ void radix_onesweep(RadixPass p) {
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    // exclusive scan of the tile's digit counts (R <= NB) by wavefront 0
-    if (wv == 0) {
-        constexpr int PER = NB / kWave;
-        uint32_t t[PER];
-        uint32_t sum = 0;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            int d = lane * PER + k;
-            t[k] = d < R ? s_tcnt[d] : 0u;
-            sum += t[k];
-        }
-        uint32_t inc = sum;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            uint32_t o = __shfl_up(inc, off, kWave);
-            if (lane >= off) inc += o;
-        }
-        uint32_t run = inc - sum;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            int d = lane * PER + k;
-            if (d < R) s_start[d] = run;
-            run += t[k];
-        }
-    }
+    // exclusive scans of the tile's digit counts and of the global ones
+    if (wv == 0) wave_exclusive<NB>(s_tcnt, R, s_start, lane);
+    if (wv == kSortWaves - 1)
+        wave_exclusive<NB>(p.sc.ghist + p.pass * kMaxBuckets, R, s_gbase, lane);
     __syncthreads();
 
-    // stage the tile in LDS in digit order (tile-local positions only): all
-    // arrays, or with ONEBUF the keys alone (each key's slot is kept in LDS
-    // for the payloads)
+    // stage the tile in LDS in digit order (tile-local positions only)
+    uint16_t* const s_lp = reinterpret_cast<uint16_t*>(s_stage[1]);  // kWide with b: slot of every key
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
         const int64_t i = wbase + (int64_t)k * kWave + lane;
         const uint32_t d = (key[k] >> p.shift) & (uint32_t)(R - 1);
         const uint32_t lp = s_start[d] + s_cnt[wv][d] + rank[k];
         if (i < p.n) {
-            s_stage[0][lp] = key[k];
-            if constexpr (ONEBUF) {
-                s_lp[k * kSortBlock + threadIdx.x] = (uint16_t)lp;
-            } else {
+            if (!HAS_B) {
+                s_stage[0][lp] = key[k];
                 s_stage[1][lp] = (uint32_t)va[k];
-                if constexpr (HAS_B) s_stage[2][lp] = (uint32_t)vb[k];
+            } else if (fmt == kWide) {
+                s_stage[0][lp] = key[k];
+                s_lp[k * kSortBlock + threadIdx.x] = (uint16_t)lp;
+            } else if constexpr (HAS_B) {
+                uint32_t hi, lo;
+                word.pack(drop ? drop_digit(key[k], p.shift, p.bits) : key[k], (uint32_t)va[k],
+                          (uint32_t)vb[k], hi, lo);
+                s_stage[0][lp] = hi;
+                s_stage[1][lp] = lo;
+                if constexpr (!WIDE)
+                    if (drop) s_dig[lp] = (uint8_t)d;
             }
         }
     }
@@ -301,108 +419,185 @@ void radix_onesweep(RadixPass p) {
             __hip_atomic_store(desc + d, desc_make(kFlagPre, tag, excl + s_tcnt[d]),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        s_gbase[d] = p.sc.gbase[p.pass * kMaxBuckets + d] + (uint32_t)excl;
+        s_gbase[d] += (uint32_t)excl;
     }
     __syncthreads();
 
     // write the digit runs: thread t takes staged slots t, t + kSortBlock, ...
-    const int64_t nvalid = (p.n - tbase) < kSortTile ? (p.n - tbase) : kSortTile;
-    int32_t pos[ONEBUF ? kSortItems : 1];
+    // (a staged row start also gives rowptr: the first slot of a run, whose
+    // row an earlier tile may have seen too, or a slot after another row's)
+    const int nvalid = (int)(p.n - tbase < kSortTile ? p.n - tbase : kSortTile);
+    if (!HAS_B || fmt == kWide) {
+        int32_t pos[HAS_B ? kSortItems : 1];
 #pragma unroll
-    for (int k = 0; k < kSortItems; ++k) {
-        const int i = (int)threadIdx.x + k * kSortBlock;
-        if constexpr (ONEBUF) pos[k] = -1;
-        if (i < nvalid) {
-            const uint32_t kk = s_stage[0][i];
-            const uint32_t d = (kk >> p.shift) & (uint32_t)(R - 1);
-            const int64_t q = (int64_t)s_gbase[d] + (i - (int64_t)s_start[d]);
-            if (q < p.n) {  // cannot fail for consistent counts; never write past n
-                if constexpr (ONEBUF) pos[k] = (int32_t)q;
-                if constexpr (POUT && ONEBUF) {
-                    // the word's key half now, its payload half with the payload
-                    reinterpret_cast<uint32_t*>(p.kv_out)[2 * q + 1] = kk;
-                } else if constexpr (POUT) {
-                    p.kv_out[q] = ((uint64_t)kk << 32) | s_stage[1][i];
-                } else if (p.keys_out) {
-                    p.keys_out[q] = kk;
+        for (int k = 0; k < kSortItems; ++k) {
+            const int i = (int)threadIdx.x + k * kSortBlock;
+            if constexpr (HAS_B) pos[k] = -1;
+            if (i < nvalid) {
+                const uint32_t kk = s_stage[0][i];
+                const uint32_t d = (kk >> p.shift) & (uint32_t)(R - 1);
+                const uint32_t run = s_start[d];
+                const int64_t q = (int64_t)s_gbase[d] + (i - (int64_t)run);
+                if (q < p.n) {  // cannot fail for consistent counts; never write past n
+                    if constexpr (HAS_B) pos[k] = (int32_t)q;
+                    if constexpr (LAST) {
+                        if ((i == (int)run || kk != s_stage[0][i > 0 ? i - 1 : 0]) &&
+                            (int64_t)kk < p.rows)
+                            atomicMin(p.sc.starts + kk, (uint32_t)q);
+                        if constexpr (!HAS_B) p.a_out[q] = (int32_t)s_stage[1][i];
+                    } else if constexpr (HAS_B) {
+                        // the word's key half now, its payload half with the payload
+                        reinterpret_cast<uint32_t*>(p.kv_out)[2 * q + 1] = kk;
+                    } else {
+                        p.kv_out[q] = ((uint64_t)kk << 32) | s_stage[1][i];
+                    }
                 }
-                if constexpr (!ONEBUF && !POUT) {
-                    if (p.a_out) p.a_out[q] = (int32_t)s_stage[1][i];
-                    if constexpr (HAS_B) {
-                        if (p.b_out) p.b_out[q] = (int32_t)s_stage[2][i];
+            }
+        }
+        if constexpr (HAS_B) {
+            // a and b, one at a time through the same buffer
+            for (int which = 0; which < 2; ++which) {
+                // a of a word: the low halves
+                const bool half = !LAST && which == 0;
+                int32_t* out = half ? reinterpret_cast<int32_t*>(p.kv_out)
+                                    : (which == 0 ? p.a_out : p.b_out);
+                __syncthreads();  // every read of the buffer's previous contents is done
+#pragma unroll
+                for (int k = 0; k < kSortItems; ++k) {
+                    const int64_t i = wbase + (int64_t)k * kWave + lane;
+                    if (i < p.n)
+                        s_stage[0][s_lp[k * kSortBlock + threadIdx.x]] =
+                            (uint32_t)(which == 0 ? va[k] : vb[k]);
+                }
+                __syncthreads();
+#pragma unroll
+                for (int k = 0; k < kSortItems; ++k)
+                    if (pos[k] >= 0)
+                        out[half ? 2 * (int64_t)pos[k] : (int64_t)pos[k]] =
+                            (int32_t)s_stage[0][threadIdx.x + k * kSortBlock];
+            }
+        }
+    } else if constexpr (HAS_B) {
+        const bool key_hi = abits + p.b_bits >= 32;  // the key lies in a word's high half alone
+#pragma unroll
+        for (int k = 0; k < kSortItems; ++k) {
+            const int i = (int)threadIdx.x + k * kSortBlock;
+            if (i < nvalid) {
+                const uint32_t hi = s_stage[0][i], lo = s_stage[1][i];
+                const uint32_t kk = word.key(hi, lo);
+                uint32_t d = (kk >> p.shift) & (uint32_t)(R - 1);
+                if constexpr (!WIDE)
+                    if (drop) d = s_dig[i];
+                const uint32_t run = s_start[d];
+                const int64_t q = (int64_t)s_gbase[d] + (i - (int64_t)run);
+                if (q < p.n) {  // cannot fail for consistent counts; never write past n
+                    if constexpr (LAST) {
+                        // within a run the keys differ exactly where the words' do
+                        const int j = i > 0 ? i - 1 : 0;
+                        const uint32_t kb = word.key(s_stage[0][j], key_hi ? 0u : s_stage[1][j]);
+                        if (i == (int)run || kk != kb) {
+                            const uint32_t v = drop ? put_digit(kk, d, p.shift, p.bits) : kk;
+                            if ((int64_t)v < p.rows) atomicMin(p.sc.starts + v, (uint32_t)q);
+                        }
+                        p.a_out[q] = word.a(hi, lo);
+                        p.b_out[q] = word.b(lo);
+                    } else {
+                        p.kv_out[q] = ((uint64_t)hi << 32) | lo;
                     }
                 }
             }
         }
     }
-    if constexpr (ONEBUF) {
-        // the payloads, one at a time through the same buffer
-        for (int which = 0; which < (HAS_B ? 2 : 1); ++which) {
-            // payload a of a packed write: the low halves of the words
-            const bool half = POUT && which == 0;
-            int32_t* out = half ? reinterpret_cast<int32_t*>(p.kv_out)
-                                : (which == 0 ? p.a_out : p.b_out);
-            __syncthreads();  // every read of the buffer's previous contents is done
+}
+
+// The caller's status word: MP_OK where no sort ran.
+__global__ void status_ok(int32_t* __restrict__ status) {
+    if (threadIdx.x == 0) *status = (int32_t)MP_OK;
+}
+
+// rowptr from the rows' first positions (kNoStart: an empty row, whose start
+// is that of the next row that has one, E after the last): a suffix minimum,
+// as the starts ascend.  rows_first finds the least start of every tile of
+// kFirstTile rows; rows_finish looks for the next tile that has one, then
+// scans its own tile from the end.
+constexpr int kFirstTile = 8192;
+constexpr int kFirstBlock = 1024;
+
+__global__ __launch_bounds__(kFirstBlock) void rows_first(const uint32_t* __restrict__ starts,
+                                                          int64_t N, uint32_t* __restrict__ first) {
+    __shared__ uint32_t s_min[kFirstBlock / kWave];
+    uint32_t m = kNoStart;
 #pragma unroll
-            for (int k = 0; k < kSortItems; ++k) {
-                const int64_t i = wbase + (int64_t)k * kWave + lane;
-                if (i < p.n)
-                    s_stage[0][s_lp[k * kSortBlock + threadIdx.x]] =
-                        (uint32_t)(which == 0 ? va[k] : vb[k]);
-            }
-            __syncthreads();
-            if (!out) continue;
+    for (int k = 0; k < kFirstTile / kFirstBlock; ++k) {
+        const int64_t v = (int64_t)blockIdx.x * kFirstTile + k * kFirstBlock + threadIdx.x;
+        const uint32_t s = v < N ? starts[v] : kNoStart;
+        m = s < m ? s : m;
+    }
 #pragma unroll
-            for (int k = 0; k < kSortItems; ++k)
-                if (pos[k] >= 0)
-                    out[half ? 2 * (int64_t)pos[k] : (int64_t)pos[k]] =
-                        (int32_t)s_stage[0][threadIdx.x + k * kSortBlock];
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t o = __shfl_xor(m, off);
+        m = o < m ? o : m;
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) s_min[threadIdx.x / kWave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kFirstBlock / kWave; ++w) m = s_min[w] < m ? s_min[w] : m;
+        first[blockIdx.x] = m;
+    }
+}
+
+// Also the caller's status word (nullptr: not wanted); with the sort's error
+// word set, rowptr is left alone.
+template <typename RP>
+__global__ __launch_bounds__(kFirstBlock) void rows_finish(const uint32_t* __restrict__ starts,
+                                                           int64_t N, int64_t E,
+                                                           const uint32_t* __restrict__ first,
+                                                           const uint32_t* __restrict__ err,
+                                                           int32_t* __restrict__ status,
+                                                           RP* __restrict__ rowptr) {
+    constexpr int PER = kFirstTile / kFirstBlock;  // consecutive rows per thread
+    __shared__ uint32_t s_min[kFirstBlock / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const bool failed = *err != 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && status)
+        *status = failed ? (int32_t)MP_ERR_SORT : (int32_t)MP_OK;
+    if (failed) return;
+    // the least start of the later tiles: that of the next tile that has any
+    uint32_t after = (uint32_t)E;
+    for (int64_t t = (int64_t)blockIdx.x + 1; t < gridDim.x; t += kWave) {
+        const uint32_t f = t + lane < gridDim.x ? first[t + lane] : kNoStart;
+        const uint64_t some = __ballot(f != kNoStart);
+        if (some) {
+            after = __shfl(f, __ffsll((unsigned long long)some) - 1);
+            break;
         }
     }
-}
-
-// The caller's status word: MP_ERR_SORT if any look-back of the sort gave up,
-// else MP_OK (err NULL: no sort ran).
-__global__ void radix_status(const uint32_t* __restrict__ err, int32_t* __restrict__ status) {
-    if (threadIdx.x == 0) *status = (err && *err) ? (int32_t)MP_ERR_SORT : (int32_t)MP_OK;
-}
-
-// rowptr[v] = first CSR position whose key is >= v, from the sorted keys:
-// position p writes every v in (keys[p-1], keys[p]] (keys[-1] = -1,
-// keys[E] = N), so each of the N+1 entries is written exactly once.  Each
-// thread covers kRowptrItems consecutive positions.
-constexpr int kRowptrItems = 8;
-
-template <typename RP, bool VEC>
-__global__ __launch_bounds__(256) void rowptr_from_sorted(const uint32_t* __restrict__ keys,
-                                                          int64_t E, int64_t N, RP* __restrict__ rowptr,
-                                                          const uint32_t* __restrict__ sort_err) {
-    static_assert(kRowptrItems == 8, "two 16-byte loads per thread");
-    const int64_t p0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * kRowptrItems;
-    if (p0 > E) return;
-    // keys left unsorted by a failed sort would make the fills below run
-    // over up to N rows per thread; the caller gets MP_ERR_SORT instead
-    if (sort_err && *sort_err) return;
-    uint32_t k8[kRowptrItems];
-    if (VEC && p0 + kRowptrItems <= E) {
-        // VEC: keys is 16-byte aligned and p0 a multiple of 8, so the loads are aligned
-        const uint4 a = reinterpret_cast<const uint4*>(keys + p0)[0];
-        const uint4 b = reinterpret_cast<const uint4*>(keys + p0)[1];
-        k8[0] = a.x; k8[1] = a.y; k8[2] = a.z; k8[3] = a.w;
-        k8[4] = b.x; k8[5] = b.y; k8[6] = b.z; k8[7] = b.w;
-    } else {
+    const int64_t v0 = (int64_t)blockIdx.x * kFirstTile + (int64_t)threadIdx.x * PER;
+    uint32_t s[PER];
+    uint32_t m = kNoStart;
 #pragma unroll
-        for (int k = 0; k < kRowptrItems; ++k) k8[k] = p0 + k < E ? keys[p0 + k] : 0u;
+    for (int k = PER - 1; k >= 0; --k) {
+        s[k] = v0 + k < N ? starts[v0 + k] : kNoStart;
+        m = s[k] < m ? s[k] : m;
     }
-    int64_t prev = p0 == 0 ? -1 : (int64_t)keys[p0 - 1];
+    // least start of the threads after this one
+    uint32_t inc = m;
 #pragma unroll
-    for (int k = 0; k < kRowptrItems; ++k) {
-        const int64_t p = p0 + k;
-        if (p > E) break;
-        int64_t cur = p == E ? N : (int64_t)k8[k];
-        if (cur > N) cur = N;  // keys are < N for valid input; stay inside rowptr regardless
-        for (int64_t v = prev + 1; v <= cur; ++v) rowptr[v] = (RP)p;
-        if (cur > prev) prev = cur;
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t o = __shfl_down(inc, off, kWave);
+        if (lane + off < kWave && o < inc) inc = o;
+    }
+    if (lane == 0) s_min[wv] = inc;
+    __syncthreads();
+    uint32_t run = __shfl_down(inc, 1, kWave);
+    if (lane == kWave - 1) run = kNoStart;
+    for (int w = wv + 1; w < kFirstBlock / kWave; ++w) run = s_min[w] < run ? s_min[w] : run;
+    if (after < run) run = after;
+#pragma unroll
+    for (int k = PER - 1; k >= 0; --k) {
+        run = s[k] < run ? s[k] : run;
+        if (v0 + k < N) rowptr[v0 + k] = (RP)run;
+        if (v0 + k == N) rowptr[N] = (RP)E;
     }
 }
 
@@ -496,28 +691,33 @@ inline unsigned grid_for(int64_t n, int per_block) {
 
 }  // namespace
 
-size_t radix_scratch_bytes(int64_t n) {
-    const int64_t tiles = ceil_div(n > 0 ? n : 1, kSortTile);
-    return align_up((size_t)tiles * kMaxBuckets * sizeof(uint64_t), 256) +
-           align_up(kMaxPasses * kMaxBuckets * sizeof(uint32_t), 256) + 256 + 256;
+size_t radix_scratch_bytes(int64_t n, int64_t N) {
+    return radix_scratch(nullptr, n, N).bytes;
 }
 
-RadixScratch radix_scratch(void* base, int64_t n) {
+RadixScratch radix_scratch(void* base, int64_t n, int64_t N) {
     const int64_t tiles = ceil_div(n > 0 ? n : 1, kSortTile);
     char* b = static_cast<char*>(base);
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        char* q = b ? b + off : nullptr;
+        off += align_up(bytes, 256);
+        return q;
+    };
     RadixScratch sc;
-    sc.desc = reinterpret_cast<uint64_t*>(b);
-    b += align_up((size_t)tiles * kMaxBuckets * sizeof(uint64_t), 256);
-    sc.gbase = reinterpret_cast<uint32_t*>(b);
-    b += align_up(kMaxPasses * kMaxBuckets * sizeof(uint32_t), 256);
-    sc.counter = reinterpret_cast<uint32_t*>(b);
-    b += 256;
-    sc.err = reinterpret_cast<uint32_t*>(b);
+    sc.desc = reinterpret_cast<uint64_t*>(take((size_t)tiles * kMaxBuckets * sizeof(uint64_t)));
+    sc.ghist = reinterpret_cast<uint32_t*>(take(kMaxPasses * kMaxBuckets * sizeof(uint32_t)));
+    sc.counter = reinterpret_cast<uint32_t*>(take(kMaxPasses * sizeof(uint32_t)));
+    sc.err = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t)));
+    sc.a_or = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t)));
+    sc.starts = reinterpret_cast<uint32_t*>(take((size_t)N * sizeof(uint32_t)));
+    sc.first = reinterpret_cast<uint32_t*>(take((size_t)ceil_div(N + 1, kFirstTile) * sizeof(uint32_t)));
+    sc.bytes = off;
     return sc;
 }
 
-hipError_t radix_sort_begin(const uint32_t* keys, int64_t n, const DigitPlan& dp,
-                            const RadixScratch& sc, hipStream_t s) {
+hipError_t radix_sort_begin(const uint32_t* keys, const int32_t* a, int64_t n, int64_t N,
+                            const DigitPlan& dp, const RadixScratch& sc, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     if (dp.passes < 1 || dp.passes > kMaxPasses) return hipErrorInvalidValue;
     uint32_t shifts = 0, widths = 0;
@@ -531,29 +731,27 @@ hipError_t radix_sort_begin(const uint32_t* keys, int64_t n, const DigitPlan& dp
     const int64_t tiles = ceil_div(n, kSortTile);
     // a pass over R = 2^width digits uses R descriptors per tile
     const int64_t ndesc = tiles * ((int64_t)1 << dp.max_width);
-    unsigned g = grid_for(ndesc, 256);
+    unsigned g = grid_for(ndesc > N ? ndesc : N, 256);
     if (g > 8192) g = 8192;
     // every histogram word needs a thread, however few descriptors there are
     if (g < (unsigned)ceil_div(kMaxPasses * kMaxBuckets, 256)) g = (unsigned)ceil_div(kMaxPasses * kMaxBuckets, 256);
-    hipLaunchKernelGGL(radix_clear, dim3(g), dim3(256), 0, s, sc.desc, ndesc, sc.gbase,
-                       sc.counter, sc.err);
-    const int64_t per_block = (int64_t)kGhistBlock * kGhistItems;
-    unsigned gh = grid_for(n, (int)per_block);
-    if (gh > 2048) gh = 2048;
-    hipLaunchKernelGGL(radix_ghist, dim3(gh), dim3(kGhistBlock), 0, s, keys, n, dp.passes, shifts,
-                       widths, sc.gbase);
-    hipLaunchKernelGGL(radix_gscan, dim3(1), dim3(kWave), 0, s, sc.gbase, dp.passes);
+    hipLaunchKernelGGL(radix_clear, dim3(g), dim3(256), 0, s, sc, ndesc, N);
+    unsigned gh = grid_for(n, kGhistBlock * kGhistItems);
+    if (gh > kGhistMaxGrid) gh = kGhistMaxGrid;
+    hipLaunchKernelGGL(radix_ghist, dim3(gh), dim3(kGhistBlock), 0, s, keys, a, n, dp.passes, shifts,
+                       widths, sc);
     return hipGetLastError();
 }
 
 template <bool HAS_B, bool WIDE>
 void launch_onesweep(const RadixPass& p, int64_t tiles, hipStream_t s) {
     const dim3 g((unsigned)tiles), b(kSortBlock);
-    if (p.kv_in && p.kv_out)
+    const bool first = p.keys_in != nullptr, last = p.a_out != nullptr;
+    if (first && last)
         hipLaunchKernelGGL((radix_onesweep<HAS_B, WIDE, true, true>), g, b, 0, s, p);
-    else if (p.kv_in)
+    else if (first)
         hipLaunchKernelGGL((radix_onesweep<HAS_B, WIDE, true, false>), g, b, 0, s, p);
-    else if (p.kv_out)
+    else if (last)
         hipLaunchKernelGGL((radix_onesweep<HAS_B, WIDE, false, true>), g, b, 0, s, p);
     else
         hipLaunchKernelGGL((radix_onesweep<HAS_B, WIDE, false, false>), g, b, 0, s, p);
@@ -573,29 +771,24 @@ hipError_t radix_sort_pass(const RadixPass& p, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_sort_status(const RadixScratch* sc, int32_t* status, hipStream_t s) {
+hipError_t launch_status_ok(int32_t* status, hipStream_t s) {
     if (!status) return hipSuccess;
-    hipLaunchKernelGGL(radix_status, dim3(1), dim3(64), 0, s, sc ? sc->err : nullptr, status);
+    hipLaunchKernelGGL(status_ok, dim3(1), dim3(64), 0, s, status);
     return hipGetLastError();
 }
 
-hipError_t launch_rowptr_from_sorted(const uint32_t* keys, int64_t E, int64_t N, void* rowptr,
-                                     int rp64, const uint32_t* sort_err, hipStream_t s) {
-    const unsigned g = grid_for(ceil_div(E + 1, kRowptrItems), 256);
-    const bool vec = reinterpret_cast<uintptr_t>(keys) % 16 == 0;
-    if (rp64) {
-        auto* rp = static_cast<int64_t*>(rowptr);
-        if (vec)
-            hipLaunchKernelGGL((rowptr_from_sorted<int64_t, true>), dim3(g), dim3(256), 0, s, keys, E, N, rp, sort_err);
-        else
-            hipLaunchKernelGGL((rowptr_from_sorted<int64_t, false>), dim3(g), dim3(256), 0, s, keys, E, N, rp, sort_err);
-    } else {
-        auto* rp = static_cast<int32_t*>(rowptr);
-        if (vec)
-            hipLaunchKernelGGL((rowptr_from_sorted<int32_t, true>), dim3(g), dim3(256), 0, s, keys, E, N, rp, sort_err);
-        else
-            hipLaunchKernelGGL((rowptr_from_sorted<int32_t, false>), dim3(g), dim3(256), 0, s, keys, E, N, rp, sort_err);
-    }
+hipError_t launch_rowptr_from_starts(const RadixScratch& sc, int64_t E, int64_t N, void* rowptr,
+                                     int rp64, int32_t* status, hipStream_t s) {
+    const int64_t tiles = ceil_div(N + 1, kFirstTile);
+    const dim3 g((unsigned)tiles), b(kFirstBlock);
+    // (a single tile has no later ones)
+    if (tiles > 1) hipLaunchKernelGGL(rows_first, g, b, 0, s, sc.starts, N, sc.first);
+    if (rp64)
+        hipLaunchKernelGGL(rows_finish<int64_t>, g, b, 0, s, sc.starts, N, E, sc.first, sc.err, status,
+                           static_cast<int64_t*>(rowptr));
+    else
+        hipLaunchKernelGGL(rows_finish<int32_t>, g, b, 0, s, sc.starts, N, E, sc.first, sc.err, status,
+                           static_cast<int32_t*>(rowptr));
     return hipGetLastError();
 }
 
