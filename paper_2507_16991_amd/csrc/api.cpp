@@ -263,7 +263,6 @@ int fill_multi_outputs(int n_out, const mp_aggr_out* outs, int64_t rows, SpmmPar
     if (n_out < 1 || n_out > 6) return MP_ERR_SIZE;
     if (!outs) return MP_ERR_NULL;
     int seen = 0;
-    uintptr_t all = 0;
     for (int k = 0; k < n_out; ++k) {
         const mp_aggr_out& o = outs[k];
         const int a = o.aggr;
@@ -272,7 +271,6 @@ int fill_multi_outputs(int n_out, const mp_aggr_out* outs, int64_t rows, SpmmPar
         const bool has_arg = a == MP_MAX || a == MP_MIN;
         if (rows > 0 && (!o.out || (has_arg && !o.arg))) return MP_ERR_NULL;
         if ((uintptr_t)o.out % 4 || (uintptr_t)o.arg % 4) return MP_ERR_ALIGN;
-        all |= (uintptr_t)o.out | (has_arg ? (uintptr_t)o.arg : 0);
         switch (a) {
             case MP_SUM: P.o_sum = o.out; break;
             case MP_MEAN: P.o_mean = o.out; break;
@@ -284,7 +282,6 @@ int fill_multi_outputs(int n_out, const mp_aggr_out* outs, int64_t rows, SpmmPar
     }
     P.stats = 1;
     P.reduce = MP_SUM | MP_MAX;
-    P.vec_store = (all % 16) == 0;
     return MP_OK;
 }
 
@@ -308,7 +305,9 @@ int multi_impl(const mp_plan* plan, const void* rowptr, int rowptr_itype, const 
         (uintptr_t)col % 4 || (uintptr_t)w % 4)
         return MP_ERR_ALIGN;
     if (N_dst == 0) return MP_OK;
-    Geometry g = make_geometry(F, x_dtype, (uintptr_t)x | (uintptr_t)(ldx * eb));
+    const uintptr_t align = (uintptr_t)x | (uintptr_t)(ldx * eb);
+    Geometry g = make_geometry(F, x_dtype, align, wide_rows(kUseStats, F, x_dtype, align, N_dst,
+                                                           plan ? plan->E : 0));
     P.rowptr = rowptr;
     P.rp64 = rowptr_itype == MP_I64;
     P.col = col;
@@ -382,7 +381,10 @@ int spmm_check(const SpmmCall& c) {
 int spmm_launch(const SpmmCall& c, hipStream_t s) {
     if (c.N_dst == 0) return MP_OK;
     const int eb = c.x_dtype == MP_BF16 ? 2 : 4;
-    Geometry g = make_geometry(c.F, c.x_dtype, (uintptr_t)c.x | (uintptr_t)(c.ldx * eb));
+    const uintptr_t align = (uintptr_t)c.x | (uintptr_t)(c.ldx * eb);
+    Geometry g = make_geometry(c.F, c.x_dtype, align,
+                               wide_rows(kUseAggregate, c.F, c.x_dtype, align, c.N_dst,
+                                         c.plan ? c.plan->E : 0));
     SpmmParams P{};
     P.rowptr = c.rowptr;
     P.rp64 = c.rowptr_itype == MP_I64;
@@ -400,7 +402,6 @@ int spmm_launch(const SpmmCall& c, hipStream_t s) {
     P.out_max = c.out_max;
     P.max_bf16 = c.max_dtype == MP_BF16;
     P.argout = c.argout;
-    P.vec_store = (((uintptr_t)c.out | (uintptr_t)c.out_max | (uintptr_t)c.argout) % 16) == 0;
     return run_spmm(c.plan, P, g, c.x_dtype, c.N_dst, c.ws, c.ws_bytes, s);
 }
 
@@ -567,7 +568,8 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
     p->F = F;
     p->x_dtype = x_dtype;
     // rows of up to 16 edges per slot get one slot; longer rows a wavefront
-    const Geometry geo = make_geometry(F, x_dtype, 16);
+    const Geometry geo = make_geometry(F, x_dtype, 16,
+                                       wide_rows(kUseAggregate, F, x_dtype, 16, N_dst, E));
     p->small_max = o.small_max > 0 ? o.small_max : 16 * (int64_t)geo.S;
     if (p->small_max > 16383) p->small_max = 16383;
     // a wavefront takes S * U edges per step; rows longer than 32 steps are
@@ -876,7 +878,11 @@ int mp_spmm_backward_x(const mp_plan* planT, const void* rowptrT, int rowptrT_it
             return MP_ERR_HIP;
         }
     }
-    Geometry g = make_geometry(F, t_dtype, (uintptr_t)table);
+    // (a lane's win-mask bits must lie in one word)
+    const bool masked = reduce == MP_MAX && !records;
+    Geometry g = make_geometry(
+        F, t_dtype, (uintptr_t)table,
+        !masked && wide_rows(kUseAggregate, F, t_dtype, (uintptr_t)table, N_src, E));
     SpmmParams P{};
     P.rowptr = rowptrT;
     P.rp64 = rowptrT_itype == MP_I64;
@@ -889,7 +895,6 @@ int mp_spmm_backward_x(const mp_plan* planT, const void* rowptrT, int rowptrT_it
     P.reduce = MP_SUM;
     P.out = grad_x;
     P.out_bf16 = out_dtype == MP_BF16;
-    P.vec_store = ((uintptr_t)grad_x % 16) == 0;
     if (records) {
         P.ekey = posT;
         P.recs = mbits;
@@ -940,7 +945,7 @@ int mp_spmm_backward_w(const void* rowptr, int rowptr_itype, const int32_t* col,
     uintptr_t al = (uintptr_t)x;
     al |= eg == ex ? (uintptr_t)grad_out : (eg > ex ? (uintptr_t)grad_out >> 1 : (uintptr_t)grad_out << 1);
     if (reduce == MP_MAX) al |= ex == 4 ? (uintptr_t)argout : (uintptr_t)argout >> 1;
-    Geometry g = make_geometry(F, x_dtype, al);
+    Geometry g = make_geometry(F, x_dtype, al, wide_rows(kUseDot, F, x_dtype, al, N_dst, E));
     GradWParams P{};
     P.rowptr = rowptr;
     P.rp64 = rowptr_itype == MP_I64;
@@ -1090,7 +1095,8 @@ int mp_edge_dot(const void* a, int a_dtype, const void* b, int b_dtype, const in
     // chunk aligned too (a's address scaled to b's element size)
     uintptr_t al = (uintptr_t)b;
     al |= ea == eb ? (uintptr_t)a : (ea > eb ? (uintptr_t)a >> 1 : (uintptr_t)a << 1);
-    Geometry g = make_geometry(F, b_dtype, al);
+    // (tables of one row per edge: no row's chunks are shared)
+    Geometry g = make_geometry(F, b_dtype, al, wide_rows(kUseDot, F, b_dtype, al, 0, E));
     GradWParams P{};
     P.col = bidx;
     P.row = nullptr;
@@ -1340,7 +1346,8 @@ int mp_hetero_spmm(int n_types, const int64_t* N_per_type, const void* const* x_
     if ((uintptr_t)out % (out_dtype == MP_BF16 ? 2 : 4) || (uintptr_t)col % 4 ||
         (uintptr_t)rowptr % (rowptr_itype == MP_I64 ? 8 : 4))
         return MP_ERR_ALIGN;
-    Geometry g = make_geometry(F, x_dtype, xa);
+    Geometry g = make_geometry(F, x_dtype, xa,
+                               wide_rows(kUseAggregate, F, x_dtype, xa, N_dst, plan ? plan->E : 0));
     SpmmParams P{};
     P.rowptr = rowptr;
     P.rp64 = rowptr_itype == MP_I64;
@@ -1364,7 +1371,6 @@ int mp_hetero_spmm(int n_types, const int64_t* N_per_type, const void* const* x_
     P.reduce = reduce;
     P.out = out;
     P.out_bf16 = out_dtype == MP_BF16;
-    P.vec_store = ((uintptr_t)out % 16) == 0;
     return run_spmm(plan, P, g, x_dtype, N_dst, ws, ws_bytes, as_stream(stream));
 }
 

@@ -45,13 +45,13 @@ __device__ inline int64_t rp_at(const void* rp, int rp64, int64_t i) {
 
 // row[p] = the v with rowptr[v] <= p < rowptr[v+1].  Bound by the 4-byte
 // stores (and, where rows are few next to positions, nothing else is read
-// more than once).  Each wavefront takes kRowsSpan consecutive POSITIONS
+// more than once).  Each wavefront takes SPAN consecutive POSITIONS
 // rather than consecutive rows, so a hub row is shared by many wavefronts: 64
 // rows per wavefront took 240 us on a power-law graph of 1.2M edges whose
 // largest row has 36k, all of it one wavefront's serial stores (now 12 us;
 // 124M edges of even rows 227 -> 180 us).  A wavefront finds the row of its first position by a
 // 64-way search (64 bounds per round trip, 4 rounds for 2.4M rows), then
-// stages the next kRowsBatch bounds in LDS, relative to its span, and each
+// stages the next SPAN / 4 bounds in LDS, relative to its span, and each
 // lane searches them once per four consecutive positions, which it stores
 // together.  A batch without a single position of the span (empty rows) is
 // followed by another search instead of the next batch, so runs of empty rows
@@ -60,18 +60,21 @@ __device__ inline int64_t rp_at(const void* rp, int rp64, int64_t i) {
 // Bounds are read as 0 for row 0 and E for row N and clamped to [0, E], and
 // every position of the span is written, with a row id below N, whatever the
 // input (an inconsistent rowptr only makes ids wrong).
-constexpr int kRowsSpan = 1024;   // positions per wavefront
-constexpr int kRowsBatch = 256;   // row bounds staged at a time
+// Spans are long where they are many (the search is paid per span) and short
+// where 1024 positions a wavefront would leave most of the card idle (a call
+// of 1.2M edges 9.6 us by 1024, 8.4 by 256; 10M edges 22 and 26).
+constexpr int64_t kRowsLongEdges = int64_t(1) << 22;
 
-template <typename IT, bool VEC>
+template <typename IT, bool VEC, int SPAN>
 __global__ __launch_bounds__(kBlock) void rows_of_edges(const IT* __restrict__ rowptr, int64_t N,
                                                         int64_t E, int32_t* __restrict__ row) {
+    constexpr int kRowsBatch = SPAN / 4;  // row bounds staged at a time
     __shared__ int32_t s_b[kWavesPerBlock][kRowsBatch];
     const int lane = threadIdx.x & (kWave - 1);
     const int wl = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    const int64_t p0 = ((int64_t)blockIdx.x * kWavesPerBlock + wl) * kRowsSpan;
+    const int64_t p0 = ((int64_t)blockIdx.x * kWavesPerBlock + wl) * SPAN;
     if (p0 >= E) return;  // uniform per wavefront
-    const int span = (int)(E - p0 < kRowsSpan ? E - p0 : kRowsSpan);
+    const int span = (int)(E - p0 < SPAN ? E - p0 : SPAN);
     int32_t* const bnd = s_b[wl];
     int at = 0;  // positions p0 .. p0 + at - 1 are written
     int64_t r = row_of_position(rowptr, N, E, p0, lane);
@@ -642,19 +645,27 @@ __global__ __launch_bounds__(kBlock) void win_gather(SpmmParams P, int fp) {
     }
 }
 
-// EPL consecutive values of a fp32 or bf16 row, widened to fp32; p is aligned
-// to min(16, EPL * sizeof(T)) bytes.
+typedef float f32x4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2e __attribute__((ext_vector_type(2), aligned(4)));
+typedef int32_t i32x4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t i32x2e __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x4h __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2h __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32h __attribute__((aligned(2)));
+
+// EPL consecutive values of a fp32 or bf16 row, widened to fp32 (wide loads at
+// any element).
 template <typename T, int EPL>
 __device__ inline void load_vals(const T* p, float (&v)[EPL]) {
     if constexpr (std::is_same<T, float>::value) {
         if constexpr (EPL >= 4) {
 #pragma unroll
             for (int q = 0; q < EPL / 4; ++q) {
-                const float4 a = reinterpret_cast<const float4*>(p)[q];
+                const f32x4e a = reinterpret_cast<const f32x4e*>(p)[q];
                 v[4 * q + 0] = a.x; v[4 * q + 1] = a.y; v[4 * q + 2] = a.z; v[4 * q + 3] = a.w;
             }
         } else if constexpr (EPL == 2) {
-            const float2 a = *reinterpret_cast<const float2*>(p);
+            const f32x2e a = *reinterpret_cast<const f32x2e*>(p);
             v[0] = a.x; v[1] = a.y;
         } else {
             v[0] = *p;
@@ -662,13 +673,13 @@ __device__ inline void load_vals(const T* p, float (&v)[EPL]) {
     } else {
         uint32_t u[(EPL + 1) / 2];
         if constexpr (EPL == 8) {
-            const uint4 a = *reinterpret_cast<const uint4*>(p);
+            const u32x4h a = *reinterpret_cast<const u32x4h*>(p);
             u[0] = a.x; u[1] = a.y; u[2] = a.z; u[3] = a.w;
         } else if constexpr (EPL == 4) {
-            const uint2 a = *reinterpret_cast<const uint2*>(p);
+            const u32x2h a = *reinterpret_cast<const u32x2h*>(p);
             u[0] = a.x; u[1] = a.y;
         } else if constexpr (EPL == 2) {
-            u[0] = *reinterpret_cast<const uint32_t*>(p);
+            u[0] = *reinterpret_cast<const u32h*>(p);
         } else {
             u[0] = *reinterpret_cast<const uint16_t*>(p);
         }
@@ -683,11 +694,11 @@ __device__ inline void load_ints(const int32_t* p, int32_t (&v)[EPL]) {
     if constexpr (EPL >= 4) {
 #pragma unroll
         for (int q = 0; q < EPL / 4; ++q) {
-            const int4 a = reinterpret_cast<const int4*>(p)[q];
+            const i32x4e a = reinterpret_cast<const i32x4e*>(p)[q];
             v[4 * q + 0] = a.x; v[4 * q + 1] = a.y; v[4 * q + 2] = a.z; v[4 * q + 3] = a.w;
         }
     } else if constexpr (EPL == 2) {
-        const int2 a = *reinterpret_cast<const int2*>(p);
+        const i32x2e a = *reinterpret_cast<const i32x2e*>(p);
         v[0] = a.x; v[1] = a.y;
     } else {
         v[0] = *p;
@@ -723,6 +734,7 @@ __global__ __launch_bounds__(kBlock) void spmm_grad_w(GradWParams P) {
     }
     // values per lane left by the slot reduction (L < U), and the lane
     // stride between the holders of consecutive edges (L >= U)
+    const bool ragged = P.F % EPL != 0;
     const int nv = U > L ? U / L : 1;
     const int hstride = U > L ? 1 : L / U;
 
@@ -735,7 +747,14 @@ __global__ __launch_bounds__(kBlock) void spmm_grad_w(GradWParams P) {
         for (int ft = 0; ft < P.FT; ++ft) {
             const int64_t chunk = (int64_t)ft * kWave + j;
             const bool feat_ok = slot_ok && chunk < P.ltot;
-            const int64_t fe = chunk * EPL;
+            // a row's last chunk may begin inside the one before it: the
+            // elements that both hold count in the earlier chunk
+            int64_t fe = chunk * EPL;
+            int skip = 0;
+            if (EPL == 4 && ragged && fe > P.F - EPL) {
+                skip = feat_ok ? (int)(fe - (P.F - EPL)) : 0;
+                fe = P.F - EPL;
+            }
             float xv[U][EPL], gv[U][EPL];
             int32_t mv[MODE == kMax ? U : 1][EPL];
             bool ok[U], fresh[U];
@@ -754,6 +773,10 @@ __global__ __launch_bounds__(kBlock) void spmm_grad_w(GradWParams P) {
                     load_vals<TX, EPL>(reinterpret_cast<const TX*>(P.x) + (int64_t)c * P.F + fe, xv[u]);
                     if (fresh[u]) {
                         load_vals<TG, EPL>(reinterpret_cast<const TG*>(P.g) + (int64_t)v * P.F + fe, gv[u]);
+                        if (EPL == 4 && ragged) {
+#pragma unroll
+                            for (int k = 0; k < EPL; ++k) gv[u][k] = k < skip ? 0.f : gv[u][k];
+                        }
                         if constexpr (MODE == kMax) load_ints<EPL>(P.argout + (int64_t)v * P.F + fe, mv[u]);
                     }
                 }
@@ -851,21 +874,29 @@ hipError_t launch_gw_epl(const GradWParams& p, int epl, unsigned grid, hipStream
     }
 }
 
+template <typename IT, int SPAN>
+void rows_vec(const IT* rp, int64_t N, int64_t E, int32_t* row, hipStream_t s) {
+    const dim3 g((unsigned)ceil_div(ceil_div(E, SPAN), kWavesPerBlock)), b(kBlock);
+    if ((uintptr_t)row % 16 == 0)  // four ids per store
+        hipLaunchKernelGGL((rows_of_edges<IT, true, SPAN>), g, b, 0, s, rp, N, E, row);
+    else
+        hipLaunchKernelGGL((rows_of_edges<IT, false, SPAN>), g, b, 0, s, rp, N, E, row);
+}
+
+template <typename IT>
+hipError_t rows_span(const IT* rp, int64_t N, int64_t E, int32_t* row, hipStream_t s) {
+    if (E < kRowsLongEdges) rows_vec<IT, 256>(rp, N, E, row, s);
+    else rows_vec<IT, 1024>(rp, N, E, row, s);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_rows_of_edges(const void* rowptr, int rp64, int64_t N, int64_t E, int32_t* row,
                                 hipStream_t s) {
     if (E <= 0 || N <= 0) return hipSuccess;
-    const unsigned grid = (unsigned)ceil_div(ceil_div(E, kRowsSpan), kWavesPerBlock);
-    const bool vec = (uintptr_t)row % 16 == 0;  // four ids per store
-    const int64_t* r8 = static_cast<const int64_t*>(rowptr);
-    const int32_t* r4 = static_cast<const int32_t*>(rowptr);
-    const dim3 g(grid), b(kBlock);
-    if (rp64 && vec) hipLaunchKernelGGL((rows_of_edges<int64_t, true>), g, b, 0, s, r8, N, E, row);
-    else if (rp64) hipLaunchKernelGGL((rows_of_edges<int64_t, false>), g, b, 0, s, r8, N, E, row);
-    else if (vec) hipLaunchKernelGGL((rows_of_edges<int32_t, true>), g, b, 0, s, r4, N, E, row);
-    else hipLaunchKernelGGL((rows_of_edges<int32_t, false>), g, b, 0, s, r4, N, E, row);
-    return hipGetLastError();
+    return rp64 ? rows_span(static_cast<const int64_t*>(rowptr), N, E, row, s)
+                : rows_span(static_cast<const int32_t*>(rowptr), N, E, row, s);
 }
 
 hipError_t launch_win_masks(const void* rowptr, int rp64, const int32_t* argout, int64_t N,

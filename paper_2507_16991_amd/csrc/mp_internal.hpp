@@ -172,8 +172,15 @@ struct Geometry {
     int L, S, FT;    // lanes per slot, slots per wave, feature tiles
 };
 // x_align: the feature pointer value(s) and row strides in bytes, OR-ed
-// (only the low bits matter).
-Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align);
+// (only the low bits matter).  wide: rows that only narrow loads divide (an odd
+// F, or a table that starts anywhere) are cut into chunks of four elements too,
+// whose last may begin inside the one before it (wide_rows); otherwise chunks
+// divide the row and are aligned.
+Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align, bool wide);
+// Whether rows that only narrow loads divide are better cut into wide chunks,
+// by what is done with them, over `rows` rows of `edges` edges in all.
+enum RowUse { kUseAggregate, kUseStats, kUseDot };
+bool wide_rows(RowUse use, int64_t F, int x_dtype, uintptr_t x_align, int64_t rows, int64_t edges);
 
 // Degree classes of the plan (keys of the row sort).
 constexpr int kSmallClasses = 16;       // class c < 16: small row, deg < 2^c ... see plan
@@ -216,7 +223,6 @@ struct SpmmParams {
     void* out_max;
     int max_bf16;
     int32_t* argout;
-    int vec_store;  // 1: out, out_max and argout are 16-byte aligned
     // masked sum (gradient of max): edge t contributes feature f only where
     // bit f of the win mask of forward position ekey[t] is set (word
     // mbits[ekey[t] * mw + f / 32], bit f % 32); both nullptr otherwise.

@@ -85,13 +85,29 @@ constexpr int unroll_of() {
 
 template <typename TX, int EPL>
 struct RawVec;
-template <> struct RawVec<float, 4> { using T = float4; };
-template <> struct RawVec<float, 2> { using T = float2; };
+// (vector types aligned to one element: make_geometry also cuts rows that no
+// vector width divides into wide loads, which the hardware takes at any
+// element; the instructions are those of aligned types)
+typedef float f32x4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2e __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x4h __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2h __attribute__((ext_vector_type(2), aligned(2)));
+template <> struct RawVec<float, 4> { using T = f32x4e; };
+template <> struct RawVec<float, 2> { using T = f32x2e; };
 template <> struct RawVec<float, 1> { using T = float; };
-template <> struct RawVec<uint16_t, 8> { using T = uint4; };
-template <> struct RawVec<uint16_t, 4> { using T = uint2; };
+template <> struct RawVec<uint16_t, 8> { using T = u32x4h; };
+template <> struct RawVec<uint16_t, 4> { using T = u32x2h; };
 template <> struct RawVec<uint16_t, 2> { using T = uint32_t; };
 template <> struct RawVec<uint16_t, 1> { using T = uint16_t; };
+
+// First element of lane-chunk j of a row: the last chunk of a row that its
+// width does not divide ends with the row, over elements that the chunk before
+// it holds too (both lanes compute and store the same values).
+template <int EPL>
+__device__ inline int64_t chunk_begin(int64_t j, int64_t F) {
+    const int64_t fe = j * EPL;
+    return fe < F - EPL ? fe : F - EPL;
+}
 
 // Byte offset of element fe of row c from the table's base when the table is
 // addressed with 32-bit offsets (O32): the table spans under 4 GiB, has at
@@ -391,48 +407,43 @@ using AccFor = Acc<EPL, HS, HM, MODE == kModeStats,
 template <typename TX, bool HS, bool HM>
 constexpr bool kSelectTail = HS ? !HM : sizeof(TX) == 4;
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4e __attribute__((ext_vector_type(4), aligned(4)));
 
-// Store EPL consecutive 4-byte values; 16-byte stores when allowed.
+// Store EPL consecutive 4-byte values (16-byte stores at any element).
 template <int EPL, typename T>
-__device__ inline void store4(T* out, const T (&v)[EPL], bool vec) {
+__device__ inline void store4(T* out, const T (&v)[EPL]) {
     static_assert(sizeof(T) == 4, "4-byte elements");
     if constexpr (EPL == 4 || EPL == 8) {
-        if (vec) {
 #pragma unroll
-            for (int q = 0; q < EPL / 4; ++q) {
-                u32x4 u;
-                u.x = __builtin_bit_cast(uint32_t, v[4 * q + 0]);
-                u.y = __builtin_bit_cast(uint32_t, v[4 * q + 1]);
-                u.z = __builtin_bit_cast(uint32_t, v[4 * q + 2]);
-                u.w = __builtin_bit_cast(uint32_t, v[4 * q + 3]);
-                __builtin_nontemporal_store(u, reinterpret_cast<u32x4*>(out) + q);
-            }
-            return;
+        for (int q = 0; q < EPL / 4; ++q) {
+            u32x4e u;
+            u.x = __builtin_bit_cast(uint32_t, v[4 * q + 0]);
+            u.y = __builtin_bit_cast(uint32_t, v[4 * q + 1]);
+            u.z = __builtin_bit_cast(uint32_t, v[4 * q + 2]);
+            u.w = __builtin_bit_cast(uint32_t, v[4 * q + 3]);
+            __builtin_nontemporal_store(u, reinterpret_cast<u32x4e*>(out) + q);
         }
-    }
+    } else {
 #pragma unroll
-    for (int k = 0; k < EPL; ++k) out[k] = v[k];
+        for (int k = 0; k < EPL; ++k) out[k] = v[k];
+    }
 }
 
-// Store EPL consecutive bf16 values (as bits); 8/16-byte stores when allowed.
+// Store EPL consecutive bf16 values (as bits), 8 bytes at a time.
 template <int EPL>
-__device__ inline void store2(uint16_t* out, const uint16_t (&b)[EPL], bool vec) {
+__device__ inline void store2(uint16_t* out, const uint16_t (&b)[EPL]) {
     if constexpr (EPL == 4 || EPL == 8) {
-        if (vec) {
 #pragma unroll
-            for (int q = 0; q < EPL / 4; ++q) {
-                u32x2 u;
-                u.x = (uint32_t)b[4 * q + 0] | ((uint32_t)b[4 * q + 1] << 16);
-                u.y = (uint32_t)b[4 * q + 2] | ((uint32_t)b[4 * q + 3] << 16);
-                __builtin_nontemporal_store(u, reinterpret_cast<u32x2*>(out) + q);
-            }
-            return;
+        for (int q = 0; q < EPL / 4; ++q) {
+            u32x2h u;
+            u.x = (uint32_t)b[4 * q + 0] | ((uint32_t)b[4 * q + 1] << 16);
+            u.y = (uint32_t)b[4 * q + 2] | ((uint32_t)b[4 * q + 3] << 16);
+            __builtin_nontemporal_store(u, reinterpret_cast<u32x2h*>(out) + q);
         }
-    }
+    } else {
 #pragma unroll
-    for (int k = 0; k < EPL; ++k) out[k] = b[k];
+        for (int k = 0; k < EPL; ++k) out[k] = b[k];
+    }
 }
 
 template <int EPL>
@@ -440,7 +451,6 @@ __device__ inline void store_row(const SpmmParams& P, int64_t row, int64_t fe, i
                                  const float (&s)[EPL], const float (&m)[EPL],
                                  const int32_t (&idx)[EPL], bool hs, bool hm) {
     const int64_t o = row * P.F + fe;
-    const bool vec = P.vec_store != 0;
     if (hs) {
         float v[EPL];
         const bool mean = (P.reduce & kMean) != 0;
@@ -452,9 +462,9 @@ __device__ inline void store_row(const SpmmParams& P, int64_t row, int64_t fe, i
             uint16_t b[EPL];
 #pragma unroll
             for (int k = 0; k < EPL; ++k) b[k] = to_bf16(v[k]);
-            store2<EPL>(static_cast<uint16_t*>(P.out) + o, b, vec);
+            store2<EPL>(static_cast<uint16_t*>(P.out) + o, b);
         } else {
-            store4<EPL>(static_cast<float*>(P.out) + o, v, vec);
+            store4<EPL>(static_cast<float*>(P.out) + o, v);
         }
     }
     if (hm) {
@@ -466,11 +476,11 @@ __device__ inline void store_row(const SpmmParams& P, int64_t row, int64_t fe, i
             uint16_t b[EPL];
 #pragma unroll
             for (int k = 0; k < EPL; ++k) b[k] = (uint16_t)(__float_as_uint(mv[k]) >> 16);
-            store2<EPL>(static_cast<uint16_t*>(P.out_max) + o, b, vec);
+            store2<EPL>(static_cast<uint16_t*>(P.out_max) + o, b);
         } else {
-            store4<EPL>(static_cast<float*>(P.out_max) + o, mv, vec);
+            store4<EPL>(static_cast<float*>(P.out_max) + o, mv);
         }
-        store4<EPL>(P.argout + o, idx, vec);
+        store4<EPL>(P.argout + o, idx);
     }
 }
 
@@ -486,7 +496,7 @@ __device__ inline void store_stats(const SpmmParams& P, int64_t row, int64_t fe,
                                    const float (&s)[EPL], const float (&d)[EPL],
                                    const float (&q)[EPL], const float (&m)[EPL],
                                    const int32_t (&im)[EPL], const float (&n)[EPL],
-                                   const int32_t (&in)[EPL], bool vec) {
+                                   const int32_t (&in)[EPL]) {
     const int64_t o = row * P.F + fe;
     const float dv = (float)deg;
     const float inv = deg > 0 ? 1.f / dv : 0.f;
@@ -501,12 +511,12 @@ __device__ inline void store_stats(const SpmmParams& P, int64_t row, int64_t fe,
         mx[k] = im[k] < 0 ? 0.f : m[k];
         mn[k] = in[k] < 0 ? 0.f : n[k];
     }
-    if (P.o_sum) store4<EPL>(P.o_sum + o, s, vec);
-    if (P.o_mean) store4<EPL>(P.o_mean + o, mean, vec);
-    if (P.o_max) { store4<EPL>(P.o_max + o, mx, vec); store4<EPL>(P.o_amax + o, im, vec); }
-    if (P.o_min) { store4<EPL>(P.o_min + o, mn, vec); store4<EPL>(P.o_amin + o, in, vec); }
-    if (P.o_var) store4<EPL>(P.o_var + o, var, vec);
-    if (P.o_std) store4<EPL>(P.o_std + o, sd, vec);
+    if (P.o_sum) store4<EPL>(P.o_sum + o, s);
+    if (P.o_mean) store4<EPL>(P.o_mean + o, mean);
+    if (P.o_max) { store4<EPL>(P.o_max + o, mx); store4<EPL>(P.o_amax + o, im); }
+    if (P.o_min) { store4<EPL>(P.o_min + o, mn); store4<EPL>(P.o_amin + o, in); }
+    if (P.o_var) store4<EPL>(P.o_var + o, var);
+    if (P.o_std) store4<EPL>(P.o_std + o, sd);
 }
 
 // Column of CSR position p: col[p], or p itself when col is absent (a
@@ -1145,7 +1155,7 @@ void spmm_main(SpmmParams P) {
         const int ft = (int)(local - item * P.FT);
         const int64_t chunk_j = ft * (int64_t)kWave + j;  // lane-chunk index in the row
         const bool feat_ok = slot_ok && chunk_j < P.ltot;
-        const int64_t fe = chunk_j * EPL;
+        const int64_t fe = chunk_begin<EPL>(chunk_j, P.F);
         int U = unroll_of<MODE, HS, HM>();
         if (S * U > kWave) U = kWave / S;
 
@@ -1214,7 +1224,7 @@ void spmm_main(SpmmParams P) {
                 }
             } else if constexpr (HX) {
                 store_stats<EPL>(P, row, fe, e1 - e0, acc.s[0], acc.d[0], acc.q[0], acc.m[0],
-                                 acc.i[0], acc.n[0], acc.j[0], P.vec_store != 0);
+                                 acc.i[0], acc.n[0], acc.j[0]);
             } else {
                 store_row<EPL>(P, row, fe, e1 - e0, acc.s[0], acc.m[0], acc.i[0], HS, HM);
             }
@@ -1231,7 +1241,7 @@ void spmm_main(SpmmParams P) {
     const int64_t k_row = group * S + slot;
     const bool row_ok = slot_ok && k_row < P.n_small;
     const bool feat_ok = row_ok && chunk_j < P.ltot;
-    const int64_t fe = chunk_j * EPL;
+    const int64_t fe = chunk_begin<EPL>(chunk_j, P.F);
     int64_t row = 0, e0 = 0, e1 = 0;
     if (row_ok) {
         row = P.rowlist[P.small_base + k_row];
@@ -1267,7 +1277,7 @@ void spmm_main(SpmmParams P) {
     if (feat_ok) {
         if constexpr (HX)
             store_stats<EPL>(P, row, fe, e1 - e0, acc.s[0], acc.d[0], acc.q[0], acc.m[0],
-                             acc.i[0], acc.n[0], acc.j[0], P.vec_store != 0);
+                             acc.i[0], acc.n[0], acc.j[0]);
         else
             store_row<EPL>(P, row, fe, e1 - e0, acc.s[0], acc.m[0], acc.i[0], HS, HM);
     }
@@ -1331,7 +1341,7 @@ __global__ __launch_bounds__(kBlock) void spmm_tiny(SpmmParams P) {
         const int ft = (int)(it % P.FT);
         const int64_t chunk_j = ft * (int64_t)kWave + j;
         const bool feat_ok = row >= 0 && chunk_j < P.ltot;
-        const int64_t fe = chunk_j * EPL;
+        const int64_t fe = chunk_begin<EPL>(chunk_j, P.F);
         R raw[kTinyDeg];
         uint32_t mb[MK ? kTinyDeg : 1];
         bool ok[kTinyDeg];
@@ -1402,7 +1412,7 @@ __global__ __launch_bounds__(kBlock) void spmm_tiny(SpmmParams P) {
         if (feat_ok) {
             if constexpr (HX)
                 store_stats<EPL>(P, row, fe, deg, acc.s[0], acc.d[0], acc.q[0], acc.m[0],
-                                 acc.i[0], acc.n[0], acc.j[0], P.vec_store != 0);
+                                 acc.i[0], acc.n[0], acc.j[0]);
             else
                 store_row<EPL>(P, row, fe, deg, acc.s[0], acc.m[0], acc.i[0], HS, HM);
         }
@@ -1490,7 +1500,7 @@ struct FixAcc {
             const float sum1[1] = {sum}, dsum1[1] = {dsum}, sq1[1] = {sq};
             const float mx[1] = {m}, nn[1] = {mn};
             const int32_t im[1] = {mi}, in[1] = {ni};
-            store_stats<1>(P, row, f, deg, sum1, dsum1, sq1, mx, im, nn, in, false);
+            store_stats<1>(P, row, f, deg, sum1, dsum1, sq1, mx, im, nn, in);
             return;
         }
         if constexpr (HS) {
@@ -1631,14 +1641,17 @@ hipError_t launch_typed(const SpmmParams& p, unsigned grid, hipStream_t s) {
 
 }  // namespace
 
-Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align) {
+Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align, bool wide) {
     Geometry g;
     g.elem_bytes = x_dtype == MP_BF16 ? 2 : 4;
     const int64_t row_bytes = F * g.elem_bytes;
     int vec = 16;
     while (vec > g.elem_bytes && (row_bytes % vec != 0 || x_align % vec != 0)) vec >>= 1;
     g.epl = vec / g.elem_bytes;
-    g.ltot = row_bytes / vec;
+    // four elements a lane all the same, the last chunk moved back to end with
+    // the row
+    if (wide && g.epl < 4 && F >= 4) g.epl = 4;
+    g.ltot = ceil_div(F, g.epl);
     if (g.ltot <= kWave) {
         g.L = (int)g.ltot;
         g.S = kWave / g.L;
@@ -1649,6 +1662,36 @@ Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align) {
         g.FT = (int)ceil_div(g.ltot, kWave);
     }
     return g;
+}
+
+// Wide chunks (loads and stores of 16 bytes at any element, where the aligned
+// cut has 4 or 8 bytes a lane, or 2) need a quarter of the instructions and
+// put more rows into a wavefront; but a load that crosses lines costs up to a
+// tenth of a gather that the memory bounds.  Measured, us of a call, narrow ->
+// wide:
+//   * few edges a row (bound by instructions and latency): F = 75, 4 edges:
+//     fp32 286 -> 130, bf16 287 -> 99; F = 13: 55 -> 45; F = 253, 16 edges:
+//     287 -> 259;
+//   * 30 to 50 edges a row, fp32: F = 47 88 -> 93, F = 50 90 -> 96, F = 253
+//     424 -> 443, where narrow rows fill a wavefront's lanes; but F = 75 154 ->
+//     137 and F = 361 692 -> 606, where they leave a partly filled tile, and
+//     F = 9 37 -> 29;
+//   * the same in bf16: F = 47 63 -> 57, F = 253 240 -> 227, F = 50 (4-byte
+//     loads) 53 -> 55;
+//   * statistics: F = 75 198 -> 165, but F = 22 54 -> 78 (fewer than eight
+//     lanes a row take the slow forms), and F = 47 112 -> 155 on a plan whose
+//     classes are for narrow chunks, so otherwise as the aggregations;
+//   * per-edge dots: F = 75 299 -> 162; with four edges a row, which share
+//     their gradient chunks in fewer slots, F = 22 59 -> 68, F = 75 176 -> 137.
+bool wide_rows(RowUse use, int64_t F, int x_dtype, uintptr_t x_align, int64_t rows, int64_t edges) {
+    const Geometry g = make_geometry(F, x_dtype, x_align, false);
+    if (g.epl >= 4 || F < 4) return false;
+    if (use == kUseStats && F < 32) return false;
+    if (use == kUseDot) return edges >= 8 * rows || (g.epl == 1 && F >= 32);
+    if (edges < 24 * rows) return true;
+    if (x_dtype == MP_BF16) return g.epl == 1 || F >= 64;
+    const bool full = 10 * g.ltot >= 9 * (int64_t)kWave * g.FT;
+    return F < 32 || (g.FT > 1 && !(full && F <= 256));
 }
 
 hipError_t launch_spmm(const SpmmParams& p, int x_dtype, int epl, hipStream_t s) {
