@@ -1430,8 +1430,8 @@ __global__ __launch_bounds__(kBlock) void spmm_tiny(SpmmParams P) {
 
 // Combine the chunk partials of every hub row, in a fixed order, and write
 // the row.  Lane = one feature of a (hub row, 64-feature tile) item.  Bound by
-// the latency of its loads.  A wavefront combines an item of up to kFixSplit
-// chunks by itself; longer ones are combined by the whole workgroup, wavefront
+// the latency of its loads.  A wavefront combines an item of up to kFixRounds
+// rounds of loads by itself; longer ones are combined by the whole workgroup, wavefront
 // w taking the w-th of kFixWaves equal ranges of the chunks, and the ranges'
 // results added through LDS in range order.  (One wavefront per item took
 // 503 us for a hub of 7M edges in its 2048 chunks, a tenth of that graph's
@@ -1441,7 +1441,7 @@ __global__ __launch_bounds__(kBlock) void spmm_tiny(SpmmParams P) {
 // HX: the stats partials too (the shifted sums and sums of squares, all
 // chunks of a row using the same shift, and min with its position).
 constexpr int kFixWaves = 8;
-constexpr int kFixSplit = 64;
+constexpr int kFixRounds = 4;
 constexpr int64_t kFixMaxGrid = 1 << 20;
 
 template <bool HS, bool HM, bool HX>
@@ -1453,9 +1453,10 @@ struct FixAcc {
         sum = dsum = sq = m = mn = 0.f;
         mi = ni = -1;
     }
+    static constexpr int A = HX ? 4 : 8;  // chunks in flight (a round)
+
     // the partials of chunks [c0, c1) of feature f
     __device__ inline void add_chunks(const SpmmParams& P, int64_t c0, int64_t c1, int64_t f) {
-        constexpr int A = HX ? 4 : 8;  // chunks in flight
         constexpr int AS = 4;          // running sums
         float s[AS] = {0.f, 0.f, 0.f, 0.f};
         float ds[AS] = {0.f, 0.f, 0.f, 0.f};
@@ -1537,7 +1538,7 @@ __global__ __launch_bounds__(kFixWaves * kWave) void spmm_fixup(SpmmParams P) {
             const int64_t h = mine / ftiles;
             const int64_t f = (mine - h * ftiles) * kWave + lane;
             const int64_t c0 = P.chunk_off[P.hub_base + h], c1 = P.chunk_off[P.hub_base + h + 1];
-            split = c1 - c0 > kFixSplit;
+            split = c1 - c0 > kFixRounds * Part::A;
             if (!split && f < P.F) {
                 Part a;
                 a.init();

@@ -95,9 +95,10 @@ def test_message_gradient(name, reduce, F):
 @pytest.mark.parametrize("F", [64, 70])  # one and two 64-feature tiles
 def test_hub_rows_of_few_and_many_chunks(F):
     """Hub rows of one edge per chunk, their chunk counts on both sides of the
-    64 that one wavefront combines and at the 2048 of the longest rows.
+    16 (statistics) and 32 that one wavefront combines and at the 2048 of the
+    longest rows.
     Integer features: sums are exact in any order."""
-    deg = np.array([2, 63, 64, 65, 0, 66, 512, 2047, 2048, 5000, 1, 130])
+    deg = np.array([2, 16, 17, 32, 33, 63, 64, 65, 0, 66, 512, 2047, 2048, 5000, 1, 130])
     rp, rp_d = rowptr_of(deg, torch.int32)
     E, N = int(rp[-1]), len(deg)
     rng = np.random.default_rng(9)
