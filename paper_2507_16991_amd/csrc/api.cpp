@@ -205,7 +205,6 @@ int run_spmm(const mp_plan* plan, SpmmParams& P, const Geometry& g, int x_dtype,
         P.rowend = plan->rowend;
         P.chunk_off = plan->chunk_off;
         P.chunk_min = plan->chunk_min;
-        // tiny rows go to their own kernel when slots are wide enough
         P.n_tiny = tiny ? plan->n_tiny : 0;
         P.small_base = P.n_tiny;
         P.n_small = plan->n_small - P.n_tiny;
@@ -524,7 +523,7 @@ int mp_sorted_coo_to_csr(const int32_t* src, const int32_t* dst, int64_t E, int6
     // a binary search per row keeps the work bounded if dst is not sorted
     hipError_t e = launch_rowptr_by_search(reinterpret_cast<const uint32_t*>(dst), E, N,
                                            rowptr, rp64, s);
-    if (e == hipSuccess) e = launch_offset_copy(src, E, 0, col, s);
+    if (e == hipSuccess) e = launch_copy_i32(src, E, col, s);
     if (e == hipSuccess && perm) e = launch_iota(E, perm, s);
     if (e == hipSuccess && val_in) e = launch_copy_f32(val_in, E, val_out, s);
     return hip_status(e);
@@ -1313,16 +1312,26 @@ int mp_hetero_build(int n_types, const int64_t* N_per_type, int n_rel, const mp_
     int32_t* dst_c = c.take<int32_t>(e);
     int64_t off = 0;
     const bool all = dst_type == MP_ALL_TYPES;
+    ConcatParams q{};
+    q.src_out = src_g;
+    q.dst_out = dst_c;
     for (int r = 0; r < n_rel; ++r) {
         const mp_relation& R = rels[r];
         if ((!all && R.dst_type != dst_type) || R.E == 0) continue;
         // sources (and, over all types, destinations) as global node ids
-        hipError_t he = launch_offset_copy(R.src, R.E, (int32_t)offs[R.src_type], src_g + off, s);
-        if (he == hipSuccess)
-            he = launch_offset_copy(R.dst, R.E, all ? (int32_t)offs[R.dst_type] : 0, dst_c + off, s);
-        if (he != hipSuccess) return MP_ERR_HIP;
+        q.src[q.n] = R.src;
+        q.dst[q.n] = R.dst;
+        q.E[q.n] = R.E;
+        q.off[q.n] = off;
+        q.src_add[q.n] = (int32_t)offs[R.src_type];
+        q.dst_add[q.n] = all ? (int32_t)offs[R.dst_type] : 0;
         off += R.E;
+        if (++q.n == kConcatMax) {
+            if (launch_concat_relations(q, s) != hipSuccess) return MP_ERR_HIP;
+            q.n = 0;
+        }
     }
+    if (q.n > 0 && launch_concat_relations(q, s) != hipSuccess) return MP_ERR_HIP;
     return coo_to_csr_impl(src_g, dst_c, E_T, N_rows, rowptr, rowptr_itype, col, nullptr,
                            nullptr, nullptr, 0, c.base + c.off, ws_bytes - c.off, status, s);
 }

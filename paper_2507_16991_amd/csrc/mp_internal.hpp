@@ -152,8 +152,21 @@ hipError_t launch_validate_coo(const int32_t* src, const int32_t* dst, int64_t E
                                int64_t N_dst, int64_t* d_count, hipStream_t s);
 hipError_t launch_validate_csr(const void* rowptr, int rp64, const int32_t* col, int64_t N_dst,
                                int64_t N_src, int64_t E, int64_t* d_count, hipStream_t s);
-hipError_t launch_offset_copy(const int32_t* in, int64_t n, int32_t add, int32_t* out,
-                              hipStream_t s);
+hipError_t launch_copy_i32(const int32_t* in, int64_t n, int32_t* out, hipStream_t s);
+// Relations r < n listed one after another: src[r][i] + src_add[r] and dst[r][i]
+// + dst_add[r] at off[r] + i, for i < E[r].
+constexpr int kConcatMax = 32;
+struct ConcatParams {
+    int n;
+    const int32_t* src[kConcatMax];
+    const int32_t* dst[kConcatMax];
+    int64_t E[kConcatMax], off[kConcatMax];
+    int32_t src_add[kConcatMax], dst_add[kConcatMax];
+    int64_t block_off[kConcatMax];  // filled by the launch
+    int32_t* src_out;
+    int32_t* dst_out;
+};
+hipError_t launch_concat_relations(ConcatParams p, hipStream_t s);
 hipError_t launch_iota(int64_t n, int32_t* out, hipStream_t s);
 hipError_t launch_copy_f32(const float* in, int64_t n, float* out, hipStream_t s);
 hipError_t launch_validate_sorted(const int32_t* dst, int64_t E, int64_t* d_count, hipStream_t s);
@@ -191,6 +204,7 @@ constexpr int kPlanClassBits = 5;       // of a class
 constexpr int kMaxChunksPerHub = 2048;  // hub rows are split into <= this many chunks
 constexpr int kTinyDeg = 7;             // rows of at most this many edges: tiny-row kernel
 constexpr int kTinyClassEnd = 4;        // classes 0..3 (bit length <= 3) are tiny
+constexpr int64_t kTinyWaves = 4096;    // persistent wavefronts of the tiny-row kernel
 
 struct SpmmParams {
     const void* rowptr;

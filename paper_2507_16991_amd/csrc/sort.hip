@@ -631,10 +631,39 @@ __global__ __launch_bounds__(256) void gather_f32(const float* __restrict__ in,
     if (i < n) out[i] = in[idx[i]];
 }
 
-__global__ __launch_bounds__(256) void offset_copy(const int32_t* __restrict__ in, int64_t n,
-                                                   int32_t add, int32_t* __restrict__ out) {
+__global__ __launch_bounds__(256) void copy_i32(const int32_t* __restrict__ in, int64_t n,
+                                                int32_t* __restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) out[i] = in[i] + add;
+    if (i < n) out[i] = in[i];
+}
+
+// The relations' edges one after another, as global (source) and row
+// (destination) ids.  Bound by its 16 bytes of traffic per edge: a block takes
+// kConcatItems edges per thread of one relation, all loads before all stores.
+// (A launch per relation and array, one edge per thread, took 110 us for the
+// typed graph's 20.6M edges; now 54 us.)
+constexpr int kConcatItems = 8;
+
+__global__ __launch_bounds__(256) void concat_relations(ConcatParams P) {
+    int r = 0;
+    while (r + 1 < P.n && (int64_t)blockIdx.x >= P.block_off[r + 1]) ++r;
+    const int64_t base = ((int64_t)blockIdx.x - P.block_off[r]) * 256 * kConcatItems + threadIdx.x;
+    const int64_t E = P.E[r], to = P.off[r];
+    int32_t a[kConcatItems], b[kConcatItems];
+#pragma unroll
+    for (int k = 0; k < kConcatItems; ++k) {
+        const int64_t i = base + k * 256;
+        a[k] = i < E ? __builtin_nontemporal_load(P.src[r] + i) : 0;
+        b[k] = i < E ? __builtin_nontemporal_load(P.dst[r] + i) : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < kConcatItems; ++k) {
+        const int64_t i = base + k * 256;
+        if (i < E) {
+            P.src_out[to + i] = a[k] + P.src_add[r];
+            P.dst_out[to + i] = b[k] + P.dst_add[r];
+        }
+    }
 }
 
 __global__ __launch_bounds__(256) void iota_i32(int64_t n, int32_t* __restrict__ out) {
@@ -824,10 +853,20 @@ hipError_t launch_gather_f32(const float* in, const int32_t* idx, int64_t n, flo
     return hipGetLastError();
 }
 
-hipError_t launch_offset_copy(const int32_t* in, int64_t n, int32_t add, int32_t* out,
-                              hipStream_t s) {
+hipError_t launch_copy_i32(const int32_t* in, int64_t n, int32_t* out, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(offset_copy, dim3(grid_for(n, 256)), dim3(256), 0, s, in, n, add, out);
+    hipLaunchKernelGGL(copy_i32, dim3(grid_for(n, 256)), dim3(256), 0, s, in, n, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_concat_relations(ConcatParams p, hipStream_t s) {
+    int64_t blocks = 0;
+    for (int r = 0; r < p.n; ++r) {
+        p.block_off[r] = blocks;
+        blocks += ceil_div(p.E[r], 256 * kConcatItems);
+    }
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(concat_relations, dim3((unsigned)blocks), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 

@@ -1746,7 +1746,7 @@ hipError_t launch_tiny_typed(const SpmmParams& p, unsigned grid, hipStream_t s) 
 hipError_t launch_spmm_tiny(const SpmmParams& p, int x_dtype, int epl, hipStream_t s) {
     if (p.n_tiny <= 0) return hipSuccess;
     const int64_t items = ceil_div(p.n_tiny, p.S) * p.FT;
-    const int64_t waves = items < 4096 ? items : 4096;
+    const int64_t waves = items < kTinyWaves ? items : kTinyWaves;
     const unsigned grid = (unsigned)ceil_div(waves, kWavesPerBlock);
     if (x_dtype == MP_F32) {
         switch (epl) {
