@@ -233,25 +233,55 @@ __global__ __launch_bounds__(kThreads) void gmm_tn_partial(GmmParams P) {
 }
 
 // dW[t][i] = sum over the chunks of segment t of Part[chunk][i], in a fixed
-// order: eight running sums over chunks c = 8q + s, then a fixed tree.  Eight
-// independent loads per iteration keep the long sums from waiting on each
-// load in turn.
-__global__ __launch_bounds__(256) void reduce_partials(GmmParams P, float* __restrict__ dW) {
+// order.  Bound by the latency of its loads where a segment has many chunks: a
+// wavefront takes 64 consecutive elements and, with W wavefronts to them, the
+// w-th of W equal ranges of the chunks, eight running sums over chunks c = 8q +
+// s (eight independent loads in flight), then a fixed tree, and the ranges are
+// added through LDS in order.  (One thread per element over all chunks took
+// 87 us for 928 + 360 + 5 chunks of 128 x 128; 19 us with W = 8.)
+constexpr int kRedWaves = 8;
+constexpr int64_t kRedMaxGrid = 1 << 20;
+
+template <int W>
+__global__ __launch_bounds__(kRedWaves * kWave) void reduce_partials(GmmParams P,
+                                                                     float* __restrict__ dW) {
+    __shared__ float s_sum[W > 1 ? kRedWaves : 1][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = threadIdx.x / kWave;
     const int64_t mn = P.M * P.N;
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g >= (int64_t)P.T * mn) return;
-    const int t = (int)(g / mn);
-    const int64_t i = g - (int64_t)t * mn;
-    const int64_t c0 = P.tile_off[t], c1 = P.tile_off[t + 1];
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int64_t c = c0; c < c1; c += 8) {
-        float v[8];
+    const int64_t total = (int64_t)P.T * mn;
+    constexpr int G = kRedWaves / W;  // groups of 64 elements per workgroup
+    const int64_t groups = (total + kWave - 1) / kWave;
+    const int w = wv % W;
+    for (int64_t g0 = (int64_t)blockIdx.x * G; g0 < groups; g0 += (int64_t)gridDim.x * G) {
+        const int64_t e = (g0 + wv / W) * kWave + lane;
+        const bool ok = e < total;
+        const int t = ok ? (int)(e / mn) : 0;
+        const int64_t i = e - (int64_t)t * mn;
+        const int64_t n = ok ? P.tile_off[t + 1] - P.tile_off[t] : 0;
+        const int64_t per = (n + W - 1) / W;
+        const int64_t c0 = P.tile_off[t] + (w * per < n ? w * per : n);
+        const int64_t c1 = P.tile_off[t] + ((w + 1) * per < n ? (w + 1) * per : n);
+        float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int64_t c = c0; c < c1; c += 8) {
+            float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = c + u < c1 ? P.part[(c + u) * mn + i] : 0.f;
+            for (int u = 0; u < 8; ++u) v[u] = c + u < c1 ? P.part[(c + u) * mn + i] : 0.f;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s[u] += v[u];
+            for (int u = 0; u < 8; ++u) s[u] += v[u];
+        }
+        float r = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+        if constexpr (W > 1) {
+            s_sum[wv][lane] = r;
+            __syncthreads();
+            if (w == 0) {
+#pragma unroll
+                for (int k = 1; k < W; ++k) r += s_sum[wv + k][lane];
+            }
+            __syncthreads();  // the next group's sums come
+        }
+        if (w == 0 && ok) dW[e] = r;
     }
-    dW[g] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
 }
 
 // Wt[t][o][f] = W[t][f][o] (bf16).
@@ -277,8 +307,15 @@ hipError_t launch_gmm_nt(const GmmParams& p, int64_t tiles, hipStream_t s) {
 hipError_t launch_gmm_weight_grad(const GmmParams& p, int64_t chunks, float* dW, hipStream_t s) {
     const int64_t tiles = chunks * ((p.M + kBM - 1) / kBM) * ((p.N + kBN - 1) / kBN);
     if (tiles > 0) hipLaunchKernelGGL(gmm_tn_partial, dim3((unsigned)tiles), dim3(kThreads), 0, s, p);
-    const int64_t n = (int64_t)p.T * p.M * p.N;
-    hipLaunchKernelGGL(reduce_partials, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, p, dW);
+    // a segment of over 16 chunks is shared by the wavefronts of a workgroup
+    int64_t most = 0;
+    for (int t = 0; t < p.T; ++t)
+        if (p.tile_off[t + 1] - p.tile_off[t] > most) most = p.tile_off[t + 1] - p.tile_off[t];
+    const int64_t groups = ceil_div((int64_t)p.T * p.M * p.N, kWave);
+    const int64_t blocks = most > 16 ? groups : ceil_div(groups, kRedWaves);
+    const dim3 g((unsigned)(blocks < kRedMaxGrid ? blocks : kRedMaxGrid)), b(kRedWaves * kWave);
+    if (most > 16) hipLaunchKernelGGL(reduce_partials<kRedWaves>, g, b, 0, s, p, dW);
+    else hipLaunchKernelGGL(reduce_partials<1>, g, b, 0, s, p, dW);
     return hipGetLastError();
 }
 
