@@ -1089,20 +1089,20 @@ def _per_dispatch(rows, counter):
 def _segment_ops(dispatches):
     """Split one step's dispatches (in dispatch order) into its operations:
     everything before the first plan kernel is the COO->CSR, from there to
-    the plan header the plan, a row copy is a layout operation, and each
+    plan_scatter, its last kernel, the plan, a row copy is a layout operation, and each
     aggregation is [spmm_tiny] spmm_main [spmm_fixup].  Returns a list of
     (kind, [dispatch rows])."""
     segs = []
     phase = "csr"
     for d in dispatches:
         k = short_name(d["name"])
-        if phase == "csr" and k.startswith("plan_classes"):
+        if phase == "csr" and k.startswith("plan_"):
             phase = "plan"
         if phase in ("csr", "plan"):
             if not segs or segs[-1][0] != phase:
                 segs.append((phase, []))
             segs[-1][1].append(d)
-            if k.startswith("plan_header"):
+            if k.startswith("plan_scatter"):
                 phase = "ops"
             continue
         if k.startswith("copy_rows"):

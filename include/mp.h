@@ -362,7 +362,7 @@ int mp_csr_transpose(const void* rowptr, int rowptr_itype, const int32_t* col, i
  * MP_MAX also the wins of every edge: the win masks, ceil(F / 32) 32-bit words
  * per edge (bit f of the words of forward position p: argout[row(p), f] == p),
  * or, on larger graphs whose edges win few features, records of 32 bytes per
- * edge (at most 8 GiB). */
+ * edge (at most 8 GiB; with room for the masks only, the masks are used). */
 int mp_spmm_backward_x_workspace(const mp_plan* planT, int64_t N_dst, int64_t E, int64_t F,
                                  int reduce, size_t* bytes);
 

@@ -584,8 +584,15 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
     // down to 8 steps, for rows of more than two (power-law graph of 120k
     // edges, F = 75: fp32 sum 28 -> 20 us, max 35 -> 25)
     const int64_t step_edges = (int64_t)geo.S * (geo.S * 8 > 64 ? 64 / geo.S : 8);
+    // -- as far as the partials stay within mp_spmm_noalloc's scratch whatever the
+    // reduction (a hub's chunks are under twice its edges / chunk, a partial at
+    // most 12 bytes per feature); explicit thresholds go with 32 steps
+    const int64_t cells = MP_NOALLOC_SCRATCH_BYTES / 12 - 256;
     int64_t steps = E / (4096 * step_edges);
+    const int64_t steps_fit = E * F / (cells / 2 * step_edges) + 1;
+    if (steps < steps_fit) steps = steps_fit;
     steps = steps < 8 ? 8 : (steps > 32 ? 32 : steps);
+    if (o.hub_min > 0 || o.chunk_min > 0) steps = 32;
     p->hub_min = o.hub_min > 0 ? o.hub_min : (steps < 16 ? 2 * steps : 32) * step_edges;
     if (p->hub_min < p->small_max) p->hub_min = p->small_max;
     p->chunk_min = (int)(o.chunk_min > 0 ? o.chunk_min : steps * step_edges);
@@ -792,16 +799,17 @@ int mp_csr_transpose(const void* rowptr, int rowptr_itype, const int32_t* col, i
 }
 
 // Extra workspace of mp_spmm_backward_x beyond the aggregation's own: the
-// fp32 grad_out / in-degree table (mean) or the win masks or records (max).
+// fp32 grad_out / in-degree table (mean) or the win masks (max).
 size_t backward_x_extra(int64_t N_dst, int64_t E, int64_t F, int reduce) {
     if (reduce == MP_MEAN) return align_up((size_t)N_dst * (size_t)F * 4, 256);
-    if (reduce == MP_MAX && use_win_records(N_dst, E, F))
-        return align_up((size_t)E * kWinWords * 4, 256);
     // (at least one position's words: the gather may load word 0 unread)
     if (reduce == MP_MAX)
         return align_up((size_t)(E > 0 ? E : 1) * (size_t)win_mask_words(F) * 4, 256);
     return 0;
 }
+
+// The same for win records, never less than for the masks.
+size_t win_records_bytes(int64_t E) { return align_up((size_t)E * kWinWords * 4, 256); }
 
 int mp_spmm_backward_x_workspace(const mp_plan* planT, int64_t N_dst, int64_t E, int64_t F,
                                  int reduce, size_t* bytes) {
@@ -812,7 +820,9 @@ int mp_spmm_backward_x_workspace(const mp_plan* planT, int64_t N_dst, int64_t E,
     size_t b = 0;
     int st = mp_spmm_workspace(planT, MP_SUM, &b);
     if (st != MP_OK) return st;
-    const size_t extra = backward_x_extra(N_dst, E, F, reduce);
+    const size_t extra = reduce == MP_MAX && use_win_records(N_dst, E, F)
+                             ? win_records_bytes(E)
+                             : backward_x_extra(N_dst, E, F, reduce);
     if (extra) b = align_up(b, 256) + extra;
     *bytes = b;
     return MP_OK;
@@ -872,8 +882,10 @@ int mp_spmm_backward_x(const mp_plan* planT, const void* rowptrT, int rowptrT_it
         t_dtype = MP_F32;
     }
     uint32_t* mbits = nullptr;
-    // (records are written in 16-byte stores; the masks never need more room)
+    // (records are written in 16-byte stores; a workspace with room for the
+    // masks alone gets the masks)
     const bool records = reduce == MP_MAX && use_win_records(N_dst, E, F) &&
+                         ws_bytes >= part + win_records_bytes(E) &&
                          (uintptr_t)extra_buf % 16 == 0;
     if (reduce == MP_MAX) {
         // max: the wins of every forward position, then a sum over the

@@ -49,3 +49,28 @@ def test_every_row_once(N, itype):
     mp.spmm(rp_d, col_d, torch.from_numpy(x).to(DEV), mp.MP_SUM, plan=plan, out=out)
     sums = np.concatenate([np.zeros((1, F)), np.cumsum(x[col], axis=0, dtype=np.float64)])
     assert np.array_equal(out.cpu().numpy(), (sums[rp[1:]] - sums[rp[:-1]]).astype(np.float32))
+
+
+@pytest.mark.parametrize("rows,deg,F", [(128, 2048, 2048), (1024, 257, 2048), (96, 1500, 4096),
+                                        (128, 1024, 700)])
+def test_short_chunks_fit_the_static_scratch(rows, deg, F):
+    """Hub chunks are shortened on small graphs only as far as the partials of
+    sum and max together stay within mp_spmm_noalloc's scratch."""
+    E = rows * deg
+    rp = torch.arange(rows + 1, dtype=torch.int32, device=DEV) * deg
+    plan = mp.Plan(rp, E, F)
+    need = mp.mp_spmm_workspace(plan.handle, mp.MP_SUM | mp.MP_MAX)
+    assert 0 < need <= 64 << 20
+    rng = np.random.default_rng(F)
+    x = torch.from_numpy(rng.integers(-3, 4, (16, F)).astype(np.float32)).to(DEV)
+    col = torch.from_numpy(rng.integers(0, 16, E).astype(np.int32)).to(DEV)
+    out = torch.full((rows, F), float("nan"), device=DEV)
+    mx = torch.full((rows, F), float("nan"), device=DEV)
+    arg = torch.full((rows, F), -2, dtype=torch.int32, device=DEV)
+    mp.mp_spmm_noalloc(plan.handle, rp, mp.MP_I32, col, None, x, mp.MP_F32, 16, rows, F, F,
+                       mp.MP_SUM | mp.MP_MAX, out, mp.MP_F32, mx, mp.MP_F32, arg)
+    counts = np.stack([np.bincount(c, minlength=16) for c in col.cpu().numpy().reshape(rows, deg)])
+    xs = x.cpu().numpy().astype(np.float64)
+    assert np.array_equal(out.cpu().numpy(), (counts @ xs).astype(np.float32))
+    present = np.where(counts[:, :, None] > 0, xs[None], -np.inf)
+    assert np.array_equal(mx.cpu().numpy(), present.max(1).astype(np.float32))

@@ -33,7 +33,8 @@ def _announce(request):
     (130, torch.float32, False, "default", torch.int64),
     (256, torch.float32, True, "hubs", torch.int32),
 ])
-@pytest.mark.parametrize("shift", [0, 4])  # bytes the workspace is off its alignment
+# bytes the workspace is off its alignment; or room for the win masks alone
+@pytest.mark.parametrize("shift", [0, 4, "masks"])
 def test_max_gradient_by_records(F, gdtype, weighted, plan, itype, shift):
     rng = np.random.default_rng(F)
     n_dst = 2 * E_MIN // F  # two wins an edge
@@ -68,6 +69,9 @@ def test_max_gradient_by_records(F, gdtype, weighted, plan, itype, shift):
     nb = mp.mp_spmm_backward_x_workspace(h, n_dst, E, F, mp.MP_MAX)
     part = mp.mp_spmm_backward_x_workspace(h, n_dst, E, F, mp.MP_SUM)
     assert nb == (part + 255) // 256 * 256 + (32 * E + 255) // 256 * 256  # records
+    if shift == "masks":
+        nb = (part + 255) // 256 * 256 + (E * ((F + 31) // 32) * 4 + 255) // 256 * 256
+        shift = 0
     ws = torch.empty(nb + shift, dtype=torch.uint8, device=DEV)[shift:]
     g_d = torch.from_numpy(g).to(DEV, gdtype)
     out = torch.full((n_src, F), float("nan"), dtype=torch.float32, device=DEV)
