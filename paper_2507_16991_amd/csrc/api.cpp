@@ -89,6 +89,11 @@ int coo_to_csr_impl(const int32_t* src, const int32_t* dst, int64_t E, int64_t N
     const int payload = (perm != nullptr || val_out != nullptr) ? 1 : 0;
     CsrLayout L = csr_layout(ws, E, N, payload);
     if (ws_bytes < L.bytes) return MP_ERR_WORKSPACE;
+    if (E <= kSortSmall && N <= kSortSmall)
+        return hip_status(launch_sort_small(
+            SmallSort{reinterpret_cast<const uint32_t*>(dst), src, val_in, col, perm,
+                      val_in ? val_out : nullptr, rowptr, status, (int)E, (int)N, 0, 0},
+            L.key_bits, rp64, s));
     int32_t* eid_final = perm ? perm : L.eid_final;
     const int passes = L.dp.passes;
 

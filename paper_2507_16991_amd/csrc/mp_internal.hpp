@@ -135,6 +135,23 @@ hipError_t radix_sort_begin(const uint32_t* keys, const int32_t* a, int64_t n, i
                             const DigitPlan& dp, const RadixScratch& sc, hipStream_t s);
 hipError_t radix_sort_pass(const RadixPass& p, hipStream_t s);
 
+// The whole COO -> CSR of at most kSortSmall edges and rows by one workgroup.
+// perm, val_in and val_out, status: nullptr where not wanted.
+constexpr int kSortSmall = 16384;
+struct SmallSort {
+    const uint32_t* dst;
+    const int32_t* src;
+    const float* val_in;
+    int32_t* col;
+    int32_t* perm;
+    float* val_out;
+    void* rowptr;
+    int32_t* status;
+    int n, rows;
+    int passes, width;  // digits, and bits of each
+};
+hipError_t launch_sort_small(SmallSort p, int key_bits, int rp64, hipStream_t s);
+
 // Write MP_OK into the caller's status word (nullptr: nothing).
 hipError_t launch_status_ok(int32_t* status, hipStream_t s);
 // After the last pass: rowptr (left alone if the sort failed) and the

@@ -510,6 +510,154 @@ __global__ __launch_bounds__(kSortBlock) void radix_onesweep(RadixPass p) {
     }
 }
 
+// COO -> CSR of at most kSortSmall edges and rows, by one workgroup in one
+// launch: the keys are counted into LDS for rowptr, then sorted with their COO
+// ids by at most two stable passes between registers and LDS (wave-level
+// multisplit, as in radix_onesweep), and the payloads are gathered by the sorted
+// ids.  The look-back sort of so few edges is six to eight launches, each shorter
+// than the gap to the next: mp_coo_to_csr from Python 57 -> 45 us (1k edges, 300
+// rows), 72 -> 57 (10k, 2.7k), 88 -> 76 (16k, 16k), with ids and values 65 -> 50,
+// 84 -> 65, 104 -> 88.  What bounds it is the serial chain of one CU, which is
+// why it ends where radix_onesweep has more than one tile.
+constexpr int kSmallBits = 7;
+constexpr int kSmallBuckets = 1 << kSmallBits;
+static_assert(kSortSmall <= kSortTile && kSortSmall <= 1 << (2 * kSmallBits), "two digits");
+
+template <typename RP>
+__global__ __launch_bounds__(kSortBlock) void sort_small(SmallSort p) {
+    __shared__ uint32_t s_key[kSortSmall];  // the rows' counts, then keys in order
+    __shared__ uint16_t s_id[kSortSmall];
+    __shared__ uint16_t s_cnt[kSortWaves][kSmallBuckets];
+    __shared__ uint32_t s_tcnt[kSmallBuckets], s_start[kSmallBuckets];
+    __shared__ uint32_t s_wave[kSortWaves];
+    constexpr int ITEMS = kSortSmall / kSortBlock;
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int rounds = (p.n + kSortBlock - 1) / kSortBlock;
+    const int wbase = wv * rounds * kWave;  // a wavefront's keys are consecutive
+
+    for (int v = threadIdx.x; v < p.rows; v += kSortBlock) s_key[v] = 0;
+    uint32_t key[ITEMS], id[ITEMS], rank[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = wbase + k * kWave + lane;
+        id[k] = (uint32_t)i;
+        key[k] = k < rounds && i < p.n ? p.dst[i] : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k)
+        if (k < rounds && wbase + k * kWave + lane < p.n && key[k] < (uint32_t)p.rows)
+            atomicAdd(&s_key[key[k]], 1u);
+    __syncthreads();
+
+    // rowptr: exclusive scan of the counts, consecutive rows per thread
+    {
+        const int per = (p.rows + kSortBlock - 1) / kSortBlock;
+        const int v0 = threadIdx.x * per;
+        uint32_t c[ITEMS];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            c[k] = k < per && v0 + k < p.rows ? s_key[v0 + k] : 0u;
+            sum += c[k];
+        }
+        uint32_t inc = sum;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t o = __shfl_up(inc, off, kWave);
+            if (lane >= off) inc += o;
+        }
+        if (lane == kWave - 1) s_wave[wv] = inc;
+        __syncthreads();
+        uint32_t run = inc - sum;
+        for (int w = 0; w < wv; ++w) run += s_wave[w];
+        RP* const rowptr = static_cast<RP*>(p.rowptr);
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            if (k < per && v0 + k < p.rows) rowptr[v0 + k] = (RP)run;
+            run += c[k];
+        }
+        if (threadIdx.x == 0) {
+            rowptr[p.rows] = (RP)p.n;
+            if (p.status) *p.status = (int32_t)MP_OK;
+        }
+    }
+
+    const int R = 1 << p.width;
+    for (int pass = 0; pass < p.passes; ++pass) {
+        const int shift = pass * p.width;
+        for (int i = threadIdx.x; i < kSortWaves * kSmallBuckets; i += kSortBlock)
+            (&s_cnt[0][0])[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            if (k < rounds) {
+                const bool ok = wbase + k * kWave + lane < p.n;
+                const uint32_t d = (key[k] >> shift) & (uint32_t)(R - 1);
+                const uint64_t peers = digit_peers<kSmallBits>(ok, d, p.width);
+                const uint32_t below = count_below(peers);
+                const uint32_t base = s_cnt[wv][d];
+                rank[k] = base + below;
+                // (LDS operations of one wavefront run in order)
+                if (ok && below == 0) s_cnt[wv][d] = (uint16_t)(base + (uint32_t)__popcll(peers));
+            }
+        }
+        __syncthreads();
+        for (int d = threadIdx.x; d < R; d += kSortBlock) {
+            uint32_t run = 0;
+#pragma unroll
+            for (int w = 0; w < kSortWaves; ++w) {
+                const uint32_t c = s_cnt[w][d];
+                s_cnt[w][d] = (uint16_t)run;
+                run += c;
+            }
+            s_tcnt[d] = run;
+        }
+        __syncthreads();
+        if (wv == 0) wave_exclusive<kSmallBuckets>(s_tcnt, R, s_start, lane);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            if (k >= rounds || wbase + k * kWave + lane >= p.n) continue;
+            const uint32_t d = (key[k] >> shift) & (uint32_t)(R - 1);
+            const uint32_t lp = s_start[d] + s_cnt[wv][d] + rank[k];
+            s_key[lp] = key[k];
+            s_id[lp] = (uint16_t)id[k];
+        }
+        __syncthreads();
+        if (pass + 1 < p.passes) {
+#pragma unroll
+            for (int k = 0; k < ITEMS; ++k) {
+                const int i = wbase + k * kWave + lane;
+                if (k >= rounds || i >= p.n) continue;
+                key[k] = s_key[i];
+                id[k] = s_id[i];
+            }
+        }
+    }
+
+    // every payload is read before any is written
+    int32_t a[ITEMS];
+    float v[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = k * kSortBlock + threadIdx.x;
+        if (i >= p.n) continue;
+        id[k] = s_id[i];
+        a[k] = p.src[id[k]];
+        if (p.val_out) v[k] = p.val_in[id[k]];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = k * kSortBlock + threadIdx.x;
+        if (i >= p.n) continue;
+        p.col[i] = a[k];
+        if (p.perm) p.perm[i] = (int32_t)id[k];
+        if (p.val_out) p.val_out[i] = v[k];
+    }
+}
+
 // The caller's status word: MP_OK where no sort ran.
 __global__ void status_ok(int32_t* __restrict__ status) {
     if (threadIdx.x == 0) *status = (int32_t)MP_OK;
@@ -797,6 +945,14 @@ hipError_t radix_sort_pass(const RadixPass& p, hipStream_t s) {
         if (wide) launch_onesweep<false, true>(p, tiles, s);
         else launch_onesweep<false, false>(p, tiles, s);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_sort_small(SmallSort p, int key_bits, int rp64, hipStream_t s) {
+    p.passes = key_bits > kSmallBits ? 2 : 1;
+    p.width = (key_bits + p.passes - 1) / p.passes;
+    if (rp64) hipLaunchKernelGGL(sort_small<int64_t>, dim3(1), dim3(kSortBlock), 0, s, p);
+    else hipLaunchKernelGGL(sort_small<int32_t>, dim3(1), dim3(kSortBlock), 0, s, p);
     return hipGetLastError();
 }
 

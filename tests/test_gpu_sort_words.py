@@ -18,6 +18,9 @@ BIG = 2 ** 31 - 1
 
 # E, N, sources below: the words they give
 SIZES = [
+    (1, 1, 5), (64, 128, 9), (1_023, 129, 64), (1_025, 16_384, 300),  # one workgroup
+    (5_000, 1, 17), (16_384, 1_000, BIG), (16_384, 16_384, BIG),
+    (16_384, 16_385, BIG), (16_385, 16_384, BIG),  # just beyond
     (40_000, 300, BIG),        # one pass
     (16_385, 5_000, 1_000),    # two passes, packed whole (13 + 10 + 15 bits)
     (200_000, 200_000, 1 << 28),  # digits of 9 bits, whole (18 + 28 + 18 = 64)
