@@ -78,6 +78,7 @@ __global__ __launch_bounds__(kBlock) void rows_of_edges(const IT* __restrict__ r
     int32_t* const bnd = s_b[wl];
     int at = 0;  // positions p0 .. p0 + at - 1 are written
     int64_t r = row_of_position(rowptr, N, E, p0, lane);
+    bool looked = true;  // r is the row of position at, fresh from the search
     while (at < span) {
         // bnd[i] = where row r + i + 1 starts, relative to p0 and cut to the span
 #pragma unroll
@@ -120,14 +121,17 @@ __global__ __launch_bounds__(kBlock) void rows_of_edges(const IT* __restrict__ r
         if (end > at) {
             at = end;
             r = r + kRowsBatch < N ? r + kRowsBatch : N - 1;
-        } else {
+            looked = false;
+        } else if (!looked) {
             // a batch of rows that end before position at: look it up
             r = row_of_position(rowptr, N, E, p0 + at, lane);
-            if (row_bound(rowptr, N, E, r + 1) <= p0 + at) {
-                // only an inconsistent rowptr: finish the span with this id
-                for (int q = at + lane; q < span; q += kWave) row[p0 + q] = (int32_t)r;
-                at = span;
-            }
+            looked = true;
+        } else {
+            // the row of position at ends after it, so its batch does too unless
+            // rowptr decreases: finish the span with this id.  Every batch thus
+            // writes positions, is followed by a search or ends the loop.
+            for (int q = at + lane; q < span; q += kWave) row[p0 + q] = (int32_t)r;
+            at = span;
         }
     }
 }

@@ -67,6 +67,21 @@ def test_row_of_every_position(name, itype, shift):
     assert (got[:shift] == -7).all() and (got[shift + E:] == -7).all()
 
 
+@pytest.mark.parametrize("e", [20_000, (1 << 22) + 5])  # short and long ranges
+def test_row_of_every_position_ends_on_a_decreasing_rowptr(e):
+    """A rowptr that jumps up and down (a caller's broken promise): the ids are
+    unspecified but lie below the number of rows, and the call finishes, though
+    no batch of bounds may end after the position that it was looked up for."""
+    n = 3000
+    rp = np.where(np.arange(n + 1) % 64 == 0, 0, e)
+    rp[-1] = e
+    col = torch.zeros(e, dtype=torch.int32, device=DEV)  # one source row: positions stay in order
+    _, colT, posT, _ = mp.csr_transpose(torch.from_numpy(rp).to(DEV, torch.int32), col, 1)
+    rows = colT.cpu().numpy()
+    assert rows.min() >= 0 and rows.max() < n
+    assert np.array_equal(posT.cpu().numpy(), np.arange(e))
+
+
 @pytest.mark.parametrize("name", NAMES)
 @pytest.mark.parametrize("reduce", ["sum", "mean", "max"])
 @pytest.mark.parametrize("F", [8, 7])
