@@ -777,10 +777,6 @@ __global__ __launch_bounds__(kBlock) void spmm_grad_w(GradWParams P) {
                     load_vals<TX, EPL>(reinterpret_cast<const TX*>(P.x) + (int64_t)c * P.F + fe, xv[u]);
                     if (fresh[u]) {
                         load_vals<TG, EPL>(reinterpret_cast<const TG*>(P.g) + (int64_t)v * P.F + fe, gv[u]);
-                        if (EPL == 4 && ragged) {
-#pragma unroll
-                            for (int k = 0; k < EPL; ++k) gv[u][k] = k < skip ? 0.f : gv[u][k];
-                        }
                         if constexpr (MODE == kMax) load_ints<EPL>(P.argout + (int64_t)v * P.F + fe, mv[u]);
                     }
                 }
@@ -798,12 +794,20 @@ __global__ __launch_bounds__(kBlock) void spmm_grad_w(GradWParams P) {
             for (int u = 0; u < U; ++u) {
                 if (!ok[u]) continue;
                 const int32_t pos = (int32_t)(p0 + base + u * S + slot);
+                float t[EPL];
 #pragma unroll
                 for (int k = 0; k < EPL; ++k) {
-                    float t = gv[u][k] * xv[u][k];
-                    if constexpr (MODE == kMax) t = mv[u][k] == pos ? t : 0.f;
-                    dot[u] += t;
+                    t[k] = gv[u][k] * xv[u][k];
+                    if constexpr (MODE == kMax) t[k] = mv[u][k] == pos ? t[k] : 0.f;
                 }
+                // (the products are left out, not one factor set to 0: an
+                // infinite feature times 0 would be NaN)
+                if (EPL == 4 && ragged) {
+#pragma unroll
+                    for (int k = 0; k < EPL; ++k) t[k] = k < skip ? 0.f : t[k];
+                }
+#pragma unroll
+                for (int k = 0; k < EPL; ++k) dot[u] += t[k];
             }
         }
         // reduce the U dots over the slot's L lanes (L a power of two, slots

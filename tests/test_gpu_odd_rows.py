@@ -101,3 +101,39 @@ def test_all_outputs(F, dtype, deg_hi, shift, pad):
         np.add.at(want, col, g[row] * kept)
         gx = mp.spmm_backward_x(rpT, colT, g_d, reduce, posT=posT, rowptr=rp_d, argout=arg)
         assert np.array_equal(gx.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("F", [5, 6, 7, 75])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("back", [2, 3, 4])  # the infinite feature: F - back
+@pytest.mark.parametrize("inf", [float("inf"), float("-inf")])
+def test_infinite_features_in_two_chunks(F, dtype, back, inf):
+    """An infinite feature in the elements that a row's last chunk shares with
+    the one before it counts once, in the dots of sum, mean and max and in
+    edge_dot.  All other features and all gradients are small positive integers,
+    so that a dot is that infinity, or exact."""
+    rng = np.random.default_rng(F + back)
+    n_dst, n_src, deg = 20, 15, 40
+    rp = np.arange(n_dst + 1) * deg
+    E = n_dst * deg
+    row = np.repeat(np.arange(n_dst), deg)
+    col = rng.integers(0, n_src, E).astype(np.int32)
+    x = rng.integers(1, 9, (n_src, F)).astype(np.float32)
+    x[::2, F - back] = inf
+    g = rng.integers(1, 5, (n_dst, F)).astype(np.float32)
+    rp_d = torch.from_numpy(rp).to(DEV, torch.int32)
+    col_d, x_d, g_d = torch.from_numpy(col).to(DEV), torch.from_numpy(x).to(DEV, dtype), torch.from_numpy(g).to(DEV)
+    dots = (g[row] * x[col]).sum(1)
+    assert np.isinf(dots).any() and not np.isnan(dots).any()
+    assert np.array_equal(mp.spmm_backward_w(rp_d, col_d, x_d, g_d, mp.MP_SUM).cpu().numpy(), dots)
+    mean = mp.spmm_backward_w(rp_d, col_d, x_d, g_d, mp.MP_MEAN).cpu().numpy()
+    assert np.array_equal(mean, (dots / np.float32(deg)).astype(np.float32))
+    ed = mp.edge_dot(torch.from_numpy(g[row]).to(DEV, dtype), x_d, bidx=col_d)
+    assert np.array_equal(ed.cpu().numpy(), dots)
+    arg = (rp[:-1, None] + rng.integers(0, deg, (n_dst, F))).astype(np.int32)
+    arg[:, F - back] = rp[:-1] + np.array([np.isinf(x[col[rp[v]:rp[v + 1]], F - back]).argmax()
+                                           for v in range(n_dst)])
+    hit = arg[row] == np.arange(E)[:, None]
+    won = np.where(hit, g[row] * np.where(hit, x[col], 0), 0).sum(1)
+    got = mp.spmm_backward_w(rp_d, col_d, x_d, g_d, mp.MP_MAX, argout=torch.from_numpy(arg).to(DEV))
+    assert np.isinf(won).any() and np.array_equal(got.cpu().numpy(), won.astype(np.float32))
