@@ -3,8 +3,8 @@
 // builds once as a source-major CSR, the analogue of the cached CSC).
 //
 //   * rows_of_edges: the destination row of every forward CSR position (the
-//     keys the transposed CSR is sorted by carry it as payload), one
-//     wavefront per 1024 positions.
+//     keys the transposed CSR is sorted by carry it as payload), by merged
+//     ranges of rows and positions.
 //   * scale_inv_deg: grad_out / in-degree per destination row, the input of
 //     the gradient of mean.
 //   * spmm_grad_w: the gradient with respect to the edge weights, one dot
@@ -43,97 +43,31 @@ __device__ inline int64_t rp_at(const void* rp, int rp64, int64_t i) {
     return rp64 ? static_cast<const int64_t*>(rp)[i] : (int64_t) static_cast<const int32_t*>(rp)[i];
 }
 
-// row[p] = the v with rowptr[v] <= p < rowptr[v+1].  Bound by the 4-byte
-// stores (and, where rows are few next to positions, nothing else is read
-// more than once).  Each wavefront takes SPAN consecutive POSITIONS
-// rather than consecutive rows, so a hub row is shared by many wavefronts: 64
-// rows per wavefront took 240 us on a power-law graph of 1.2M edges whose
-// largest row has 36k, all of it one wavefront's serial stores (now 12 us;
-// 124M edges of even rows 227 -> 180 us).  A wavefront finds the row of its first position by a
-// 64-way search (64 bounds per round trip, 4 rounds for 2.4M rows), then
-// stages the next SPAN / 4 bounds in LDS, relative to its span, and each
-// lane searches them once per four consecutive positions, which it stores
-// together.  A batch without a single position of the span (empty rows) is
-// followed by another search instead of the next batch, so runs of empty rows
-// cost nothing.
-//
-// Bounds are read as 0 for row 0 and E for row N and clamped to [0, E], and
-// every position of the span is written, with a row id below N, whatever the
-// input (an inconsistent rowptr only makes ids wrong).
-// Spans are long where they are many (the search is paid per span) and short
-// where 1024 positions a wavefront would leave most of the card idle (a call
-// of 1.2M edges 9.6 us by 1024, 8.4 by 256; 10M edges 22 and 26).
-constexpr int64_t kRowsLongEdges = int64_t(1) << 22;
+// row[p] = the v with rowptr[v] <= p < rowptr[v+1]: the number of rows that end
+// at or before p.  Bound by the 4-byte stores and the 4 or 8 bytes of every
+// row's bound.  By merged ranges, as neither fixed rows nor fixed positions a
+// wavefront bound its work (us: 64 rows a wavefront; 256 or 1024 positions;
+// merged):
+//   124M edges over 2.4M rows      171   183   176
+//   power law, 1.2M, a row of 36k  240     8     9
+//   1M edges over 1M rows            8    18    12
+//   300k edges over 20k rows        11     6     7
+//   50k edges over 1M rows           7   484    10
+//   300 edges over 16k rows          5   883     9
+// What is left on small graphs is the searches' three round trips.
+// Bounds are clamped to [0, E], the last row's is E, so ids lie below N whatever
+// the input (an inconsistent rowptr only makes ids wrong).
+template <typename IT>
+struct RowEnds {
+    const IT* rowptr;
+    int64_t N, E;
+    __device__ inline int64_t operator()(int64_t i) const { return row_bound(rowptr, N, E, i + 1); }
+};
 
 template <typename IT, bool VEC, int SPAN>
-__global__ __launch_bounds__(kBlock) void rows_of_edges(const IT* __restrict__ rowptr, int64_t N,
-                                                        int64_t E, int32_t* __restrict__ row) {
-    constexpr int kRowsBatch = SPAN / 4;  // row bounds staged at a time
-    __shared__ int32_t s_b[kWavesPerBlock][kRowsBatch];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wl = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    const int64_t p0 = ((int64_t)blockIdx.x * kWavesPerBlock + wl) * SPAN;
-    if (p0 >= E) return;  // uniform per wavefront
-    const int span = (int)(E - p0 < SPAN ? E - p0 : SPAN);
-    int32_t* const bnd = s_b[wl];
-    int at = 0;  // positions p0 .. p0 + at - 1 are written
-    int64_t r = row_of_position(rowptr, N, E, p0, lane);
-    bool looked = true;  // r is the row of position at, fresh from the search
-    while (at < span) {
-        // bnd[i] = where row r + i + 1 starts, relative to p0 and cut to the span
-#pragma unroll
-        for (int k = 0; k < kRowsBatch / kWave; ++k) {
-            const int64_t b = row_bound(rowptr, N, E, r + 1 + k * kWave + lane) - p0;
-            bnd[k * kWave + lane] = (int32_t)(b < 0 ? 0 : (b > span ? span : b));
-        }
-        // the wavefront reads what its own lanes wrote: LDS operations of one
-        // wavefront complete in order
-        __builtin_amdgcn_wave_barrier();
-        const int end = __builtin_amdgcn_readfirstlane(bnd[kRowsBatch - 1]);
-        const int nr = (int)(N - r < kRowsBatch ? N - r : kRowsBatch);  // rows of this batch
-        constexpr int V = VEC ? 4 : 1;
-        for (int q = (at & ~3) + lane * V; q < end; q += kWave * V) {
-            int lo = 0, hi = nr - 1;  // the first row whose end lies after q
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (bnd[mid] > q) hi = mid; else lo = mid + 1;
-            }
-            if constexpr (VEC) {
-                int4 v;
-                int32_t* const e = &v.x;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    while (lo < nr - 1 && bnd[lo] <= q + i) ++lo;
-                    e[i] = (int32_t)(r + lo);
-                }
-                if (q >= at && q + 4 <= end) {
-                    *reinterpret_cast<int4*>(row + p0 + q) = v;
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (q + i >= at && q + i < end) row[p0 + q + i] = e[i];
-                }
-            } else if (q >= at) {
-                row[p0 + q] = (int32_t)(r + lo);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (end > at) {
-            at = end;
-            r = r + kRowsBatch < N ? r + kRowsBatch : N - 1;
-            looked = false;
-        } else if (!looked) {
-            // a batch of rows that end before position at: look it up
-            r = row_of_position(rowptr, N, E, p0 + at, lane);
-            looked = true;
-        } else {
-            // the row of position at ends after it, so its batch does too unless
-            // rowptr decreases: finish the span with this id.  Every batch thus
-            // writes positions, is followed by a search or ends the loop.
-            for (int q = at + lane; q < span; q += kWave) row[p0 + q] = (int32_t)r;
-            at = span;
-        }
-    }
+__global__ __launch_bounds__(kMergeBlock) void rows_of_edges(const IT* __restrict__ rowptr, int64_t N,
+                                                             int64_t E, int32_t* __restrict__ row) {
+    merge_counts<SPAN, VEC>(RowEnds<IT>{rowptr, N, E}, N - 1, E, row);
 }
 
 __device__ inline float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
@@ -884,7 +818,7 @@ hipError_t launch_gw_epl(const GradWParams& p, int epl, unsigned grid, hipStream
 
 template <typename IT, int SPAN>
 void rows_vec(const IT* rp, int64_t N, int64_t E, int32_t* row, hipStream_t s) {
-    const dim3 g((unsigned)ceil_div(ceil_div(E, SPAN), kWavesPerBlock)), b(kBlock);
+    const dim3 g((unsigned)ceil_div(N - 1 + E, SPAN)), b(kMergeBlock);
     if ((uintptr_t)row % 16 == 0)  // four ids per store
         hipLaunchKernelGGL((rows_of_edges<IT, true, SPAN>), g, b, 0, s, rp, N, E, row);
     else
@@ -893,8 +827,8 @@ void rows_vec(const IT* rp, int64_t N, int64_t E, int32_t* row, hipStream_t s) {
 
 template <typename IT>
 hipError_t rows_span(const IT* rp, int64_t N, int64_t E, int32_t* row, hipStream_t s) {
-    if (E < kRowsLongEdges) rows_vec<IT, 256>(rp, N, E, row, s);
-    else rows_vec<IT, 1024>(rp, N, E, row, s);
+    if (N + E < kMergeLong) rows_vec<IT, kMergeSpanShort>(rp, N, E, row, s);
+    else rows_vec<IT, kMergeSpanLong>(rp, N, E, row, s);
     return hipGetLastError();
 }
 

@@ -321,6 +321,127 @@ __device__ inline int64_t row_of_position(const IT* __restrict__ rowptr, int64_t
     return lo;
 }
 
+// ---- merged ranges -------------------------------------------------------------
+// out[q] = the number of values a(i) <= q, for q in [0, m), of n nondecreasing
+// values in [0, m]: the row of every position from the rows' ends, or every
+// row's start from sorted keys.  Values and outputs are taken in merged order
+// (value i before output q where a(i) <= q; value i is item a(i) + i), and each
+// workgroup takes SPAN consecutive ITEMS, so its work is the same where many
+// values lie between two outputs, and many outputs between two values.  Two
+// wavefronts find the ends of its range by 64-way searches (2.4M values: four
+// round trips), its values are staged in LDS and each lane searches them for
+// four consecutive outputs, which it stores together.
+//
+// Whatever the values, every output is written, with a count in [0, n], and the
+// work ends: the searches' rounds depend on n alone, and neighbouring
+// workgroups search for the same ends.
+
+// The number of values whose item lies before item d (the whole wavefront; all
+// lanes active).
+template <typename A>
+__device__ inline int64_t merge_search(const A& a, int64_t n, int64_t d, int lane) {
+    int64_t r = 0, c = n;  // the result is in [r, r + c]
+    while (c > 0) {
+        const int64_t step = (c + kWave - 1) / kWave;
+        const int64_t i = (int64_t)(lane + 1) * step - 1;
+        const bool before = i < c && a(r + i) + r + i < d;
+        const int64_t k = (int64_t)__popcll(__ballot(before)) * step;
+        r += k;
+        c = c - k < step ? c - k : step - 1;
+    }
+    return r;
+}
+
+// VEC: out is 16-byte aligned.  For a workgroup of kMergeBlock threads.
+constexpr int kMergeBlock = 256;
+
+template <int SPAN, bool VEC, typename OUT, typename A>
+__device__ inline void merge_counts(const A& a, int64_t n, int64_t m, OUT* __restrict__ out) {
+    __shared__ int32_t s[SPAN];
+    __shared__ int64_t s_end[2];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int64_t d0 = (int64_t)blockIdx.x * SPAN;
+    const int64_t d1 = d0 + SPAN < n + m ? d0 + SPAN : n + m;
+    if (wv < 2) {
+        const int64_t r = merge_search(a, n, wv == 0 ? d0 : d1, lane);
+        if (lane == 0) s_end[wv] = r;
+    }
+    __syncthreads();
+    const int64_t r0 = s_end[0], r1 = s_end[1];
+    int64_t q0 = d0 - r0, q1 = d1 - r1;
+    q0 = q0 < 0 ? 0 : (q0 > m ? m : q0);
+    q1 = q1 < 0 ? 0 : (q1 > m ? m : q1);
+    const int nr = (int)(r1 - r0 < 0 ? 0 : (r1 - r0 > SPAN ? SPAN : r1 - r0));
+    // values relative to q0, cut to the range
+    for (int i = threadIdx.x; i < nr; i += kMergeBlock) {
+        const int64_t v = a(r0 + i) - q0;
+        s[i] = (int32_t)(v < 0 ? 0 : (v > SPAN ? SPAN : v));
+    }
+    __syncthreads();
+    constexpr int V = VEC ? 4 : 1;
+    const int top = nr > 0 ? 1 << (31 - __clz(nr)) : 0;  // the largest power of two up to nr
+    for (int64_t q = q0 / V * V + (int)threadIdx.x * V; q < q1; q += kMergeBlock * V) {
+        // the first value beyond each output
+        OUT v[V];
+        if (nr > SPAN / 4) {
+            // the V searches side by side, their LDS reads in flight together
+            int lo[V] = {};
+            for (int step = top; step > 0; step >>= 1) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const int i = lo[e] + step - 1;
+                    if (i < nr && s[i] <= q + e - q0) lo[e] += step;
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = (OUT)(r0 + lo[e]);
+        } else {
+            // few values next to outputs: mostly that of the output before, or
+            // one close by
+            int lo = 0;
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const int64_t x = q + e - q0;
+                bool found = false;
+                if (e > 0) {
+#pragma unroll
+                    for (int near = 0; near < 4; ++near) {
+                        found = !(lo < nr && s[lo] <= x);
+                        if (found) break;
+                        ++lo;
+                    }
+                }
+                if (!found) {
+                    int hi = nr;
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        if (s[mid] <= x) lo = mid + 1; else hi = mid;
+                    }
+                }
+                v[e] = (OUT)(r0 + lo);
+            }
+        }
+        if constexpr (VEC) {
+            if (q >= q0 && q + V <= q1) {
+                struct alignas(16) Block { OUT x[V]; };
+                *reinterpret_cast<Block*>(out + q) = *reinterpret_cast<const Block*>(v);
+            } else {
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+                    if (q + e >= q0 && q + e < q1) out[q + e] = v[e];
+            }
+        } else {
+            out[q] = v[0];
+        }
+    }
+}
+
+// Items per workgroup: many where the ends' searches would be much of the
+// work, few where long ranges would leave most of the card idle.
+constexpr int64_t kMergeLong = int64_t(1) << 22;  // items from which ranges are long
+constexpr int kMergeSpanLong = 4096, kMergeSpanShort = 1024;
+
 // ---- backward (backward.hip) -----------------------------------------------
 struct GradWParams {
     const void* rowptr;

@@ -1,9 +1,9 @@
-"""Kernels that cut the edge list into ranges of positions, at the sizes where
-a range's ends fall inside hub rows, on row ends and among empty rows: the row
-of every position (1024 positions per wavefront, 256 row bounds at a time) and
-the gradient of materialized messages (a row's first 256 or 1024 edges, then
-parts of that many).  Integers and copies are exact; the mean's quotient is
-correctly rounded."""
+"""Kernels that cut the edge list into ranges, at the sizes where a range's ends
+fall inside hub rows, on row ends and among empty rows: the row of every
+position (256 or 1024 rows and positions per wavefront, in merged order) and the
+gradient of materialized messages (a row's first 256 or 1024 edges, then parts
+of that many).  Integers and copies are exact; the mean's quotient is correctly
+rounded."""
 import sys
 
 import numpy as np
@@ -38,13 +38,15 @@ def degrees(name):
         return d
     if name == "trailing empty rows":
         return np.concatenate([np.full(300, 4), np.zeros(70_000, dtype=np.int64)])
+    if name == "more rows than edges":
+        return np.bincount(rng.integers(0, 100_000, 5000), minlength=100_000)
     if name == "degree one":
         return np.ones(3000, dtype=np.int64)
     return np.minimum(rng.zipf(1.3, 20_000), 30_000)  # power law
 
 
 NAMES = ["one row", "one edge", "range ends", "hub among empty rows", "trailing empty rows",
-         "degree one", "power law"]
+         "degree one", "power law", "more rows than edges"]
 
 
 def rowptr_of(deg, dtype):
@@ -67,11 +69,27 @@ def test_row_of_every_position(name, itype, shift):
     assert (got[:shift] == -7).all() and (got[shift + E:] == -7).all()
 
 
+@pytest.mark.parametrize("name", ["range ends", "power law", "more rows than edges", "one row"])
+@pytest.mark.parametrize("itype", [torch.int32, torch.int64])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_row_of_every_position_in_long_ranges(name, itype, shift):
+    """1024 rows and positions a wavefront, from 4M of them on."""
+    deg = degrees(name)
+    deg = np.tile(deg, -(-((1 << 22) + 5) // (len(deg) + int(deg.sum()))))
+    rp, rp_d = rowptr_of(deg, itype)
+    E, N = int(rp[-1]), len(deg)
+    buf = torch.full((E + shift + 8,), -7, dtype=torch.int32, device=DEV)
+    mp.mp_csr_rows(rp_d, mp.MP_I32 if itype == torch.int32 else mp.MP_I64, N, E,
+                   buf[shift:shift + E])
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[shift:shift + E], np.repeat(np.arange(N), deg))
+    assert (got[:shift] == -7).all() and (got[shift + E:] == -7).all()
+
+
 @pytest.mark.parametrize("e", [20_000, (1 << 22) + 5])  # short and long ranges
 def test_row_of_every_position_ends_on_a_decreasing_rowptr(e):
     """A rowptr that jumps up and down (a caller's broken promise): the ids are
-    unspecified but lie below the number of rows, and the call finishes, though
-    no batch of bounds may end after the position that it was looked up for."""
+    unspecified but lie below the number of rows, and the call finishes."""
     n = 3000
     rp = np.where(np.arange(n + 1) % 64 == 0, 0, e)
     rp[-1] = e
