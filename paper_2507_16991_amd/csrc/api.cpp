@@ -128,7 +128,7 @@ int coo_to_csr_impl(const int32_t* src, const int32_t* dst, int64_t E, int64_t N
         rp.sc = L.sc;
         if (radix_sort_pass(rp, s) != hipSuccess) return MP_ERR_HIP;
     }
-    hipError_t e = launch_rowptr_from_starts(L.sc, E, N, rowptr, rp64, status, s);
+    hipError_t e = launch_rowptr(L.sc, L.key_bits, E, N, rowptr, rp64, status, s);
     if (e == hipSuccess && val_in && val_out) e = launch_gather_f32(val_in, eid_final, E, val_out, s);
     return hip_status(e);
 }

@@ -102,6 +102,8 @@ struct RadixScratch {
     uint32_t* counter;  // [kMaxPasses] dynamic tile ids
     uint32_t* err;      // nonzero: a look-back wait gave up (the result is invalid)
     uint32_t* a_or;     // the OR of payload a (where it was asked for)
+    // for rowptr: the sorted keys (rowptr_by_keys), or
+    uint32_t* keys;     // [n]
     uint32_t* starts;   // [N] first position of every row that has edges
     uint32_t* first;    // [tiles of N + 1 rows] scratch of rowptr
     size_t bytes;
@@ -156,8 +158,10 @@ hipError_t launch_sort_small(SmallSort p, int key_bits, int rp64, hipStream_t s)
 hipError_t launch_status_ok(int32_t* status, hipStream_t s);
 // After the last pass: rowptr (left alone if the sort failed) and the
 // caller's status word (nullptr: not wanted).
-hipError_t launch_rowptr_from_starts(const RadixScratch& sc, int64_t E, int64_t N, void* rowptr,
-                                     int rp64, int32_t* status, hipStream_t s);
+hipError_t launch_rowptr(const RadixScratch& sc, int key_bits, int64_t E, int64_t N, void* rowptr,
+                         int rp64, int32_t* status, hipStream_t s);
+// Whether rowptr comes from the sorted keys rather than from the rows' starts.
+bool rowptr_by_keys(int64_t E, int64_t N);
 // rowptr of keys sorted by the caller, by binary search (bounded work for
 // any order of keys)
 hipError_t launch_rowptr_by_search(const uint32_t* keys, int64_t E, int64_t N, void* rowptr,

@@ -19,7 +19,7 @@
 // digit its pass has just sorted by: the element's place says it, and the
 // next pass puts it back (124M edges, 2.4M rows: 15 + 22 + 27 bits).  The last
 // pass writes src and id alone; rowptr comes from where it sees each row
-// start.  (Carrying id as a third array and keeping the sorted keys for rowptr
+// start (or from the keys, where rows are many).  (Carrying id as a third array and keeping the sorted keys for rowptr
 // cost 80 bytes of traffic per edge where this takes 56 to 60: passes of 790,
 // 880 and 898 us on 124M edges -> 601, 663 and 800, rowptr 155 -> 27; CSR with
 // ids and transpose together 6.05 -> 4.85 ms.)
@@ -205,9 +205,10 @@ struct WordBits {
 //   HAS_B: the COO-id payload b is carried (b = the element index on FIRST).
 //   WIDE:  digits of up to 9 bits (512 buckets: twice the per-wave counters).
 //   FIRST: keys and a are read as given; otherwise as words (word_format).
-//   LAST:  a (and b) are written alone, and where the tile first sees a row,
-//          starts[row] takes the place (the least over all tiles: a row's
-//          edges lie together, in tile order); otherwise words are written.
+//   LAST:  a (and b) are written alone, and for rowptr the key too, or where
+//          the tile first sees a row, starts[row] takes the place (the least
+//          over all tiles: a row's edges lie together, in tile order);
+//          otherwise words are written.
 // A tile's words are staged in LDS as two halves at once (128 KB); in kWide
 // with b, the keys, a and b go through one staging buffer in turn, the keys
 // before the look-back and the others after the previous array is written.
@@ -446,8 +447,10 @@ __global__ __launch_bounds__(kSortBlock) void radix_onesweep(RadixPass p) {
                 if (q < p.n) {  // cannot fail for consistent counts; never write past n
                     if constexpr (HAS_B) pos[k] = (int32_t)q;
                     if constexpr (LAST) {
-                        if ((i == (int)run || kk != s_stage[0][i > 0 ? i - 1 : 0]) &&
-                            (int64_t)kk < p.rows)
+                        if (p.sc.keys)
+                            p.sc.keys[q] = kk;
+                        else if ((i == (int)run || kk != s_stage[0][i > 0 ? i - 1 : 0]) &&
+                                 (int64_t)kk < p.rows)
                             atomicMin(p.sc.starts + kk, (uint32_t)q);
                         if constexpr (!HAS_B) p.a_out[q] = (int32_t)s_stage[1][i];
                     } else if constexpr (HAS_B) {
@@ -497,12 +500,15 @@ __global__ __launch_bounds__(kSortBlock) void radix_onesweep(RadixPass p) {
                 const int64_t q = (int64_t)s_gbase[d] + (i - (int64_t)run);
                 if (q < p.n) {  // cannot fail for consistent counts; never write past n
                     if constexpr (LAST) {
-                        // within a run the keys differ exactly where the words' do
-                        const int j = i > 0 ? i - 1 : 0;
-                        const uint32_t kb = word.key(s_stage[0][j], key_hi ? 0u : s_stage[1][j]);
-                        if (i == (int)run || kk != kb) {
-                            const uint32_t v = drop ? put_digit(kk, d, p.shift, p.bits) : kk;
-                            if ((int64_t)v < p.rows) atomicMin(p.sc.starts + v, (uint32_t)q);
+                        const uint32_t v = drop ? put_digit(kk, d, p.shift, p.bits) : kk;
+                        if (p.sc.keys) {
+                            p.sc.keys[q] = v;
+                        } else {
+                            // within a run the keys differ exactly where the words' do
+                            const int j = i > 0 ? i - 1 : 0;
+                            const uint32_t kb = word.key(s_stage[0][j], key_hi ? 0u : s_stage[1][j]);
+                            if ((i == (int)run || kk != kb) && (int64_t)v < p.rows)
+                                atomicMin(p.sc.starts + v, (uint32_t)q);
                         }
                         p.a_out[q] = word.a(hi, lo);
                         p.b_out[q] = word.b(lo);
@@ -668,11 +674,11 @@ __global__ void status_ok(int32_t* __restrict__ status) {
     if (threadIdx.x == 0) *status = (int32_t)MP_OK;
 }
 
-// rowptr from the rows' first positions (kNoStart: an empty row, whose start
-// is that of the next row that has one, E after the last): a suffix minimum,
-// as the starts ascend.  rows_first finds the least start of every tile of
-// kFirstTile rows; rows_finish looks for the next tile that has one, then
-// scans its own tile from the end.
+// rowptr where edges are many next to rows, from the rows' first positions
+// (kNoStart: an empty row, whose start is that of the next row that has one, E
+// after the last): a suffix minimum, as the starts ascend.  rows_first finds
+// the least start of every tile of kFirstTile rows; rows_finish looks for the
+// next tile that has one, then scans its own tile from the end.
 constexpr int kFirstTile = 8192;
 constexpr int kFirstBlock = 1024;
 
@@ -752,6 +758,34 @@ __global__ __launch_bounds__(kFirstBlock) void rows_finish(const uint32_t* __res
         if (v0 + k < N) rowptr[v0 + k] = (RP)run;
         if (v0 + k == N) rowptr[N] = (RP)E;
     }
+}
+
+// rowptr from the sorted keys, where the rows are many (rowptr_by_keys): the
+// number of keys below v, by merged ranges of keys and rows.  Also the caller's
+// status word; with the sort's error word set, rowptr is left alone.
+struct KeyRows {
+    const uint32_t* keys;
+    int64_t N;
+    uint32_t mask;  // the bits that were sorted by
+    __device__ inline int64_t operator()(int64_t i) const {
+        const int64_t k = (int64_t)(keys[i] & mask) + 1;
+        return k < N ? k : N;
+    }
+};
+
+template <typename RP, bool VEC, int SPAN>
+__global__ __launch_bounds__(kMergeBlock) void rowptr_from_keys(const uint32_t* __restrict__ keys,
+                                                                uint32_t mask, int64_t E, int64_t N,
+                                                                const uint32_t* __restrict__ err,
+                                                                int32_t* __restrict__ status,
+                                                                RP* __restrict__ rowptr) {
+    const bool failed = *err != 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (status) *status = failed ? (int32_t)MP_ERR_SORT : (int32_t)MP_OK;
+        if (!failed) rowptr[N] = (RP)E;
+    }
+    if (failed) return;  // the same for all threads
+    merge_counts<SPAN, VEC>(KeyRows{keys, N, mask}, E, N, rowptr);
 }
 
 // rowptr[v] = the first position p with keys[p] >= v (E if none), by binary
@@ -892,8 +926,14 @@ RadixScratch radix_scratch(void* base, int64_t n, int64_t N) {
     sc.counter = reinterpret_cast<uint32_t*>(take(kMaxPasses * sizeof(uint32_t)));
     sc.err = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t)));
     sc.a_or = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t)));
-    sc.starts = reinterpret_cast<uint32_t*>(take((size_t)N * sizeof(uint32_t)));
-    sc.first = reinterpret_cast<uint32_t*>(take((size_t)ceil_div(N + 1, kFirstTile) * sizeof(uint32_t)));
+    if (rowptr_by_keys(n, N)) {
+        sc.keys = reinterpret_cast<uint32_t*>(take((size_t)n * sizeof(uint32_t)));
+        sc.starts = sc.first = nullptr;
+    } else {
+        sc.keys = nullptr;
+        sc.starts = reinterpret_cast<uint32_t*>(take((size_t)N * sizeof(uint32_t)));
+        sc.first = reinterpret_cast<uint32_t*>(take((size_t)ceil_div(N + 1, kFirstTile) * sizeof(uint32_t)));
+    }
     sc.bytes = off;
     return sc;
 }
@@ -913,11 +953,12 @@ hipError_t radix_sort_begin(const uint32_t* keys, const int32_t* a, int64_t n, i
     const int64_t tiles = ceil_div(n, kSortTile);
     // a pass over R = 2^width digits uses R descriptors per tile
     const int64_t ndesc = tiles * ((int64_t)1 << dp.max_width);
-    unsigned g = grid_for(ndesc > N ? ndesc : N, 256);
+    const int64_t nstarts = sc.starts ? N : 0;
+    unsigned g = grid_for(ndesc > nstarts ? ndesc : nstarts, 256);
     if (g > 8192) g = 8192;
     // every histogram word needs a thread, however few descriptors there are
     if (g < (unsigned)ceil_div(kMaxPasses * kMaxBuckets, 256)) g = (unsigned)ceil_div(kMaxPasses * kMaxBuckets, 256);
-    hipLaunchKernelGGL(radix_clear, dim3(g), dim3(256), 0, s, sc, ndesc, N);
+    hipLaunchKernelGGL(radix_clear, dim3(g), dim3(256), 0, s, sc, ndesc, nstarts);
     unsigned gh = grid_for(n, kGhistBlock * kGhistItems);
     if (gh > kGhistMaxGrid) gh = kGhistMaxGrid;
     hipLaunchKernelGGL(radix_ghist, dim3(gh), dim3(kGhistBlock), 0, s, keys, a, n, dp.passes, shifts,
@@ -967,8 +1008,49 @@ hipError_t launch_status_ok(int32_t* status, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_rowptr_from_starts(const RadixScratch& sc, int64_t E, int64_t N, void* rowptr,
-                                     int rp64, int32_t* status, hipStream_t s) {
+namespace {
+
+template <typename RP, int SPAN>
+hipError_t rowptr_keys_span(const RadixScratch& sc, uint32_t mask, int64_t E, int64_t N, RP* rowptr,
+                            int32_t* status, hipStream_t s) {
+    const dim3 g((unsigned)ceil_div(E + N, SPAN)), b(kMergeBlock);
+    if ((uintptr_t)rowptr % 16 == 0)  // four entries per store
+        hipLaunchKernelGGL((rowptr_from_keys<RP, true, SPAN>), g, b, 0, s, sc.keys, mask, E, N, sc.err,
+                           status, rowptr);
+    else
+        hipLaunchKernelGGL((rowptr_from_keys<RP, false, SPAN>), g, b, 0, s, sc.keys, mask, E, N, sc.err,
+                           status, rowptr);
+    return hipGetLastError();
+}
+
+template <typename RP>
+hipError_t rowptr_keys(const RadixScratch& sc, uint32_t mask, int64_t E, int64_t N, RP* rowptr,
+                       int32_t* status, hipStream_t s) {
+    return E + N < kMergeLong
+               ? rowptr_keys_span<RP, kMergeSpanShort>(sc, mask, E, N, rowptr, status, s)
+               : rowptr_keys_span<RP, kMergeSpanLong>(sc, mask, E, N, rowptr, status, s);
+}
+
+}  // namespace
+
+// The keys cost 8 bytes of traffic per edge, the starts 20 per row, an atomic
+// per row that has edges, and a launch more.  Whole COO -> CSR, us, by starts ->
+// by keys: 10M edges over 40M rows 515 -> 308 (with ids 600 -> 402), 20M 368 ->
+// 290, 10M 289 -> 269, 5M 257 -> 254, 2.5M 241 -> 244; 1M edges over 10M rows
+// 149 -> 96, 250k 71 -> 66; 100k over 50k 56 -> 48.  (Filling the rows between
+// two keys by the later key's thread was as fast on even rows, but one thread's
+// work where no edge ends in the last rows: 1 s for 40M rows.)
+bool rowptr_by_keys(int64_t E, int64_t N) {
+    return E <= 2 * N || (E <= 4 * N && E < kMergeLong);
+}
+
+hipError_t launch_rowptr(const RadixScratch& sc, int key_bits, int64_t E, int64_t N, void* rowptr,
+                         int rp64, int32_t* status, hipStream_t s) {
+    if (sc.keys) {
+        const uint32_t mask = key_bits < 32 ? (1u << key_bits) - 1u : ~0u;
+        return rp64 ? rowptr_keys(sc, mask, E, N, static_cast<int64_t*>(rowptr), status, s)
+                    : rowptr_keys(sc, mask, E, N, static_cast<int32_t*>(rowptr), status, s);
+    }
     const int64_t tiles = ceil_div(N + 1, kFirstTile);
     const dim3 g((unsigned)tiles), b(kFirstBlock);
     // (a single tile has no later ones)

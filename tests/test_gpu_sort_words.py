@@ -29,6 +29,13 @@ SIZES = [
     (200_000, 1 << 22, BIG),   # the same, exactly 64 bits
     (300_000, 1 << 22, BIG),   # too wide by one bit
     (100_000, 20_000_000, 7),  # digits of 9 bits, three passes
+    # edges enough for rowptr from the rows' starts rather than from the keys
+    (300_000, 20_000, 1_000),      # two passes, packed whole (15 + 10 + 19)
+    (300_000, 20_000, BIG),        # one digit left out (15 + 31 + 19)
+    (1_100_000, 262_144, BIG),     # digits of 9 bits, too wide (18 + 31 + 21)
+    (1_200_000, 270_000, 1 << 26),  # three passes, one digit left out (19 + 26 + 21)
+    # ... and on both sides of where that begins
+    (80_000, 20_000, 50), (80_001, 20_000, 50),
 ]
 
 
