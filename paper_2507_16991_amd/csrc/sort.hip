@@ -705,9 +705,43 @@ __global__ __launch_bounds__(kFirstBlock) void rows_first(const uint32_t* __rest
     }
 }
 
+// In place: first[t] = the least of first[t], first[t + 1], ... by one
+// workgroup, each thread taking consecutive tiles.  For the many tiles over
+// which rows_finish's own look ahead, 64 tiles a step, would become most of its
+// time where all edges end in the first rows (140M edges, 64M rows, the whole
+// sort: 3627 -> 3437 us).
+constexpr int64_t kLookTiles = 1024;  // tiles up to which rows_finish looks itself
+
+__global__ __launch_bounds__(1024) void rows_suffix(uint32_t* __restrict__ first, int64_t tiles) {
+    __shared__ uint32_t s_min[1024 / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int64_t per = (tiles + 1023) / 1024;
+    const int64_t t0 = threadIdx.x * per < tiles ? threadIdx.x * per : tiles;
+    const int64_t t1 = t0 + per < tiles ? t0 + per : tiles;
+    uint32_t m = kNoStart;
+    for (int64_t t = t0; t < t1; ++t) m = first[t] < m ? first[t] : m;
+    // least of the threads after this one
+    uint32_t inc = m;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t o = __shfl_down(inc, off, kWave);
+        if (lane + off < kWave && o < inc) inc = o;
+    }
+    if (lane == 0) s_min[wv] = inc;
+    __syncthreads();
+    uint32_t run = __shfl_down(inc, 1, kWave);
+    if (lane == kWave - 1) run = kNoStart;
+    for (int w = wv + 1; w < 1024 / kWave; ++w) run = s_min[w] < run ? s_min[w] : run;
+    for (int64_t t = t1 - 1; t >= t0; --t) {
+        const uint32_t f = first[t];
+        run = f < run ? f : run;
+        first[t] = run;
+    }
+}
+
 // Also the caller's status word (nullptr: not wanted); with the sort's error
-// word set, rowptr is left alone.
-template <typename RP>
+// word set, rowptr is left alone.  SUFFIX: rows_suffix has run.
+template <typename RP, bool SUFFIX>
 __global__ __launch_bounds__(kFirstBlock) void rows_finish(const uint32_t* __restrict__ starts,
                                                            int64_t N, int64_t E,
                                                            const uint32_t* __restrict__ first,
@@ -723,12 +757,19 @@ __global__ __launch_bounds__(kFirstBlock) void rows_finish(const uint32_t* __res
     if (failed) return;
     // the least start of the later tiles: that of the next tile that has any
     uint32_t after = (uint32_t)E;
-    for (int64_t t = (int64_t)blockIdx.x + 1; t < gridDim.x; t += kWave) {
-        const uint32_t f = t + lane < gridDim.x ? first[t + lane] : kNoStart;
-        const uint64_t some = __ballot(f != kNoStart);
-        if (some) {
-            after = __shfl(f, __ffsll((unsigned long long)some) - 1);
-            break;
+    if constexpr (SUFFIX) {
+        if ((int64_t)blockIdx.x + 1 < gridDim.x) {
+            const uint32_t f = first[blockIdx.x + 1];
+            if (f != kNoStart) after = f;
+        }
+    } else {
+        for (int64_t t = (int64_t)blockIdx.x + 1; t < gridDim.x; t += kWave) {
+            const uint32_t f = t + lane < gridDim.x ? first[t + lane] : kNoStart;
+            const uint64_t some = __ballot(f != kNoStart);
+            if (some) {
+                after = __shfl(f, __ffsll((unsigned long long)some) - 1);
+                break;
+            }
         }
     }
     const int64_t v0 = (int64_t)blockIdx.x * kFirstTile + (int64_t)threadIdx.x * PER;
@@ -1031,6 +1072,24 @@ hipError_t rowptr_keys(const RadixScratch& sc, uint32_t mask, int64_t E, int64_t
                : rowptr_keys_span<RP, kMergeSpanLong>(sc, mask, E, N, rowptr, status, s);
 }
 
+template <typename RP>
+hipError_t rowptr_starts(const RadixScratch& sc, int64_t E, int64_t N, RP* rowptr, int32_t* status,
+                         hipStream_t s) {
+    const int64_t tiles = ceil_div(N + 1, kFirstTile);
+    const dim3 g((unsigned)tiles), b(kFirstBlock);
+    // (a single tile has no later ones)
+    if (tiles > 1) hipLaunchKernelGGL(rows_first, g, b, 0, s, sc.starts, N, sc.first);
+    if (tiles > kLookTiles) {
+        hipLaunchKernelGGL(rows_suffix, dim3(1), dim3(1024), 0, s, sc.first, tiles);
+        hipLaunchKernelGGL((rows_finish<RP, true>), g, b, 0, s, sc.starts, N, E, sc.first, sc.err,
+                           status, rowptr);
+    } else {
+        hipLaunchKernelGGL((rows_finish<RP, false>), g, b, 0, s, sc.starts, N, E, sc.first, sc.err,
+                           status, rowptr);
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
 
 // The keys cost 8 bytes of traffic per edge, the starts 20 per row, an atomic
@@ -1051,17 +1110,8 @@ hipError_t launch_rowptr(const RadixScratch& sc, int key_bits, int64_t E, int64_
         return rp64 ? rowptr_keys(sc, mask, E, N, static_cast<int64_t*>(rowptr), status, s)
                     : rowptr_keys(sc, mask, E, N, static_cast<int32_t*>(rowptr), status, s);
     }
-    const int64_t tiles = ceil_div(N + 1, kFirstTile);
-    const dim3 g((unsigned)tiles), b(kFirstBlock);
-    // (a single tile has no later ones)
-    if (tiles > 1) hipLaunchKernelGGL(rows_first, g, b, 0, s, sc.starts, N, sc.first);
-    if (rp64)
-        hipLaunchKernelGGL(rows_finish<int64_t>, g, b, 0, s, sc.starts, N, E, sc.first, sc.err, status,
-                           static_cast<int64_t*>(rowptr));
-    else
-        hipLaunchKernelGGL(rows_finish<int32_t>, g, b, 0, s, sc.starts, N, E, sc.first, sc.err, status,
-                           static_cast<int32_t*>(rowptr));
-    return hipGetLastError();
+    return rp64 ? rowptr_starts(sc, E, N, static_cast<int64_t*>(rowptr), status, s)
+                : rowptr_starts(sc, E, N, static_cast<int32_t*>(rowptr), status, s);
 }
 
 hipError_t launch_rowptr_by_search(const uint32_t* keys, int64_t E, int64_t N, void* rowptr,

@@ -84,3 +84,21 @@ def test_csr_and_transpose(E, N, src_max, kind):
     assert np.array_equal(colT.cpu().numpy(), row[order])
     assert np.array_equal(posT.cpu().numpy(), order)
     assert np.array_equal(valT.cpu().numpy(), val[order])
+
+
+@pytest.mark.parametrize("E,N", [(17_000_000, 8_388_607), (17_000_000, 8_388_608),  # 1024 and 1025 tiles
+                                 (40_000_000, 18_000_000)])
+@pytest.mark.parametrize("where", ["first rows", "last rows", "both ends"])
+def test_rowptr_of_rows_beyond_the_last_edge(E, N, where):
+    """All edges end in a few rows, and every other row's start is looked for in
+    the tiles of rows after it."""
+    dst = torch.randint(0, 5, (E,), dtype=torch.int32, device=DEV)
+    if where == "last rows":
+        dst += N - 5
+    elif where == "both ends":
+        dst[::2] += N - 5
+    src = torch.zeros(E, dtype=torch.int32, device=DEV)
+    rowptr, _, _, _ = mp.coo_to_csr(src, dst, N)
+    want = torch.zeros(N + 1, dtype=torch.int64, device=DEV)
+    want[1:] = torch.bincount(dst, minlength=N).cumsum(0)
+    assert torch.equal(rowptr.long(), want)
