@@ -262,12 +262,12 @@ __global__ __launch_bounds__(kBlock) void message_backward(const IT* __restrict_
                                                            const int32_t* __restrict__ argout,
                                                            const TG* __restrict__ g, int64_t N,
                                                            int64_t E, int64_t F, int64_t cpr,
-                                                           int L, int S, int part,
+                                                           int L, int S, int part, int64_t parts,
                                                            float* __restrict__ dmsg) {
     const int lane = threadIdx.x & (kWave - 1);
     const int slot = lane / L;
     const int j = lane - slot * L;
-    const int64_t waves = N + (E + part - 1) / part - 1;  // every row, every part but the first
+    const int64_t waves = N + parts;
     for (int64_t wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)) +
                       (int64_t)blockIdx.x * (kBlock / kWave);
          wv < waves; wv += (int64_t)gridDim.x * (kBlock / kWave)) {
@@ -323,11 +323,18 @@ __global__ __launch_bounds__(kBlock) void message_backward(const IT* __restrict_
 }
 
 // Edges of a row that its own wavefront writes.  Short parts balance better
-// and cost a row lookup per part of the edge list (4 round trips, hidden by
-// the other wavefronts' stores where there are many): 256 while the parts
-// fit the card's wavefronts about 8 times over, 1024 beyond.
-constexpr int64_t kPartEdges = int64_t(1) << 24;
-inline int backward_part(int64_t E) { return E <= kPartEdges ? 256 : 1024; }
+// and cost a row lookup (up to 4 round trips) per part of the edge list: 256
+// while the parts are a few times the card's wavefronts at most, then about
+// 128 rounds of the S slots, and four times that beyond kPartLong (us with 256
+// -> with more: F = 5, 1.2M edges of even rows 13.4 -> 12.5, 10M 51 -> 43; but
+// 20k edges with a hub of 7k 5.8 -> 7.0).
+constexpr int64_t kPartShort = int64_t(1) << 20, kPartLong = int64_t(1) << 24;
+inline int backward_part(int64_t E, int S) {
+    int part = 256;
+    if (E < kPartShort) return part;
+    while (2 * part <= 128 * S) part *= 2;
+    return E <= kPartLong ? part : 4 * part;
+}
 
 // Launch at most this many blocks; larger tables are walked by the grid stride.
 constexpr int64_t kMaxGrid = int64_t(1) << 20;
@@ -381,18 +388,19 @@ hipError_t backward_mode(const MessageBackward& a, hipStream_t s) {
     const int S = kWave / L;
     const TG* g = static_cast<const TG*>(a.g);
     const IT* rp = static_cast<const IT*>(a.rowptr);
-    const int part = backward_part(a.E);
-    const int64_t blocks = ceil_div(a.N + ceil_div(a.E, part) - 1, kBlock / kWave);
+    const int part = backward_part(a.E, S);
+    const int64_t parts = ceil_div(a.E, part) - 1;  // all but the first
+    const int64_t blocks = ceil_div(a.N + parts, kBlock / kWave);
     const dim3 grid((unsigned)(blocks < kMaxGrid ? blocks : kMaxGrid)), block(kBlock);
     if (a.reduce == kMax)
         hipLaunchKernelGGL((message_backward<TG, IT, EPL, kMax>), grid, block, 0, s, rp, a.argout,
-                           g, a.N, a.E, a.F, cpr, L, S, part, a.dmsg);
+                           g, a.N, a.E, a.F, cpr, L, S, part, parts, a.dmsg);
     else if (a.reduce == kMean)
         hipLaunchKernelGGL((message_backward<TG, IT, EPL, kMean>), grid, block, 0, s, rp, a.argout,
-                           g, a.N, a.E, a.F, cpr, L, S, part, a.dmsg);
+                           g, a.N, a.E, a.F, cpr, L, S, part, parts, a.dmsg);
     else
         hipLaunchKernelGGL((message_backward<TG, IT, EPL, kSum>), grid, block, 0, s, rp, a.argout,
-                           g, a.N, a.E, a.F, cpr, L, S, part, a.dmsg);
+                           g, a.N, a.E, a.F, cpr, L, S, part, parts, a.dmsg);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """Kernels that cut the edge list into ranges, at the sizes where a range's ends
 fall inside hub rows, on row ends and among empty rows: the row of every
 position (256 or 1024 rows and positions per wavefront, in merged order) and the
-gradient of materialized messages (a row's first 256 or 1024 edges, then parts
+gradient of materialized messages (a row's first 256 edges or more, then parts
 of that many).  Integers and copies are exact; the mean's quotient is correctly
 rounded."""
 import sys
@@ -123,6 +123,33 @@ def test_message_gradient(name, reduce, F):
                               {"sum": mp.MP_SUM, "mean": mp.MP_MEAN, "max": mp.MP_MAX}[reduce], E=E,
                               argout=None if arg is None else torch.from_numpy(arg).to(DEV))
     assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("e", [(1 << 20) - 1, 1 << 20, (1 << 24) + 5])
+@pytest.mark.parametrize("F,reduce", [(7, "max"), (8, "sum"), (130, "sum")])
+def test_message_gradient_in_long_parts(e, F, reduce):
+    """256 edges a part below 2^20 edges, then 256 to 4096 by the width, and four
+    times that beyond 2^24: rows that end on and next to multiples of those, and
+    a hub over several parts."""
+    if e * F > 1 << 28:
+        F = 5
+    d = np.concatenate([degrees("range ends"), [4095, 4096, 4097, 16_383, 16_384, 16_385, 0, 1]])
+    deg = np.tile(d, (e - 70_000) // int(d.sum()))
+    deg = np.append(deg, e - int(deg.sum()))
+    rp, rp_d = rowptr_of(deg, torch.int32)
+    N = len(deg)
+    g = torch.randn(N, F, device=DEV)
+    row = torch.repeat_interleave(torch.arange(N, device=DEV), torch.from_numpy(deg).to(DEV))
+    arg = None
+    if reduce == "max":
+        deg_d = torch.from_numpy(deg).to(DEV)[:, None]
+        arg = (rp_d[:-1, None] + torch.randint(0, 1 << 30, (N, F), device=DEV) % deg_d.clamp(min=1)).int()
+        arg = torch.where(deg_d > 0, arg, -1).int()
+    got = mp.message_backward(rp_d, g, mp.MP_SUM if reduce == "sum" else mp.MP_MAX, E=e, argout=arg)
+    want = g[row]
+    if reduce == "max":
+        want *= arg[row] == torch.arange(e, device=DEV)[:, None]
+    assert torch.equal(got, want)
 
 
 @pytest.mark.parametrize("F", [64, 70])  # one and two 64-feature tiles
