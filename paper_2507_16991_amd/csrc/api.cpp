@@ -168,8 +168,11 @@ struct mp_plan {
     int x_dtype;
     int64_t small_max, hub_min;
     int chunk_min;
-    int64_t n_tiny, n_small, n_mid, n_hub, n_chunks;
-    int64_t mid_base, hub_base;
+    // rows of the list that are small for narrow chunks of features (the first
+    // n_small_narrow) and for wide ones (n_small); then mid rows up to hub_base
+    int64_t n_tiny, n_small_narrow, n_small, n_hub, n_chunks;
+    int64_t hub_base;
+    int64_t ge32, ge64;  // rows of at least 32 and 64 edges (or more)
     int32_t* rowlist;
     int32_t* rowbeg;
     int32_t* rowend;
@@ -187,6 +190,11 @@ inline int fits_off32(int64_t rows, int64_t ld, int elem_bytes) {
                    ld * elem_bytes < ((int64_t)1 << 24)
                ? 1
                : 0;
+}
+
+RowLengths row_lengths(const mp_plan* plan, int64_t N_dst) {
+    return plan ? RowLengths{N_dst, plan->E, true, plan->ge32, plan->ge64}
+                : RowLengths{N_dst, 0, false, 0, 0};
 }
 
 // Fill the work description of SpmmParams from a plan (or the plan-free
@@ -218,12 +226,12 @@ int run_spmm(const mp_plan* plan, SpmmParams& P, const Geometry& g, int x_dtype,
         P.chunk_min = plan->chunk_min;
         P.n_tiny = tiny ? plan->n_tiny : 0;
         P.small_base = P.n_tiny;
-        P.n_small = plan->n_small - P.n_tiny;
+        P.mid_base = g.wide || P.recs ? plan->n_small : plan->n_small_narrow;
+        P.n_small = P.mid_base - P.n_tiny;
         P.n_hub = plan->n_hub;
-        P.mid_base = plan->mid_base;
         P.hub_base = plan->hub_base;
         P.n_hub_waves = plan->n_chunks * ft;
-        P.n_mid_waves = plan->n_mid * ft;
+        P.n_mid_waves = (plan->hub_base - P.mid_base) * ft;
         P.n_small_waves = ceil_div(P.n_small, slots) * ft;
         if (plan->n_chunks > 0) {
             Carver c(ws);
@@ -316,8 +324,8 @@ int multi_impl(const mp_plan* plan, const void* rowptr, int rowptr_itype, const 
         return MP_ERR_ALIGN;
     if (N_dst == 0) return MP_OK;
     const uintptr_t align = (uintptr_t)x | (uintptr_t)(ldx * eb);
-    Geometry g = make_geometry(F, x_dtype, align, wide_rows(kUseStats, F, x_dtype, align, N_dst,
-                                                           plan ? plan->E : 0));
+    Geometry g = make_geometry(F, x_dtype, align,
+                               wide_rows(kUseStats, 0, F, x_dtype, align, row_lengths(plan, N_dst)));
     P.rowptr = rowptr;
     P.rp64 = rowptr_itype == MP_I64;
     P.col = col;
@@ -393,8 +401,8 @@ int spmm_launch(const SpmmCall& c, hipStream_t s) {
     const int eb = c.x_dtype == MP_BF16 ? 2 : 4;
     const uintptr_t align = (uintptr_t)c.x | (uintptr_t)(c.ldx * eb);
     Geometry g = make_geometry(c.F, c.x_dtype, align,
-                               wide_rows(kUseAggregate, c.F, c.x_dtype, align, c.N_dst,
-                                         c.plan ? c.plan->E : 0));
+                               wide_rows(kUseAggregate, c.reduce, c.F, c.x_dtype, align,
+                                         row_lengths(c.plan, c.N_dst)));
     SpmmParams P{};
     P.rowptr = c.rowptr;
     P.rp64 = c.rowptr_itype == MP_I64;
@@ -577,28 +585,40 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
     p->E = E;
     p->F = F;
     p->x_dtype = x_dtype;
-    // rows of up to 16 edges per slot get one slot; longer rows a wavefront
-    const Geometry geo = make_geometry(F, x_dtype, 16,
-                                       wide_rows(kUseAggregate, F, x_dtype, 16, N_dst, E));
-    p->small_max = o.small_max > 0 ? o.small_max : 16 * (int64_t)geo.S;
+    // rows of up to 16 edges per slot get one slot; longer rows a wavefront.  Where
+    // rows may be cut into narrow or wide chunks (wide_rows), each has its
+    // limit; of up to 32 features, wide ones are taken only where no row has
+    // 64 edges, and all are small then
+    const Geometry nar = make_geometry(F, x_dtype, 16, false);
+    const Geometry wid = make_geometry(F, x_dtype, 16, true);
+    p->small_max = o.small_max > 0 ? o.small_max : 16 * (int64_t)nar.S;
     if (p->small_max > 16383) p->small_max = 16383;
+    const int64_t split = p->small_max;
+    if (o.small_max <= 0 && wid.wide) {
+        const int64_t most = F < kWideAlways ? 63 : 16 * (int64_t)wid.S;
+        if (p->small_max < most) p->small_max = most;
+    }
     // a wavefront takes S * U edges per step; rows longer than 32 steps are
     // split into chunks of at least 32 steps, so that no wavefront runs a long
     // chain of dependent steps on its own.  Where the edges do not give 4096
     // wavefronts that many, the longest chain is the call's time: chunks of
     // down to 8 steps, for rows of more than two (power-law graph of 120k
-    // edges, F = 75: fp32 sum 28 -> 20 us, max 35 -> 25)
-    const int64_t step_edges = (int64_t)geo.S * (geo.S * 8 > 64 ? 64 / geo.S : 8);
+    // edges, F = 75: fp32 sum 28 -> 20 us, max 35 -> 25).  The short chunks are
+    // by the narrow cut's steps, the long ones by the wide cut's
+    auto step_of = [](const Geometry& g) { return (int64_t)g.S * (g.S * 8 > 64 ? 64 / g.S : 8); };
+    const int64_t step_edges = step_of(nar);
+    const int64_t most_steps = 32 * step_of(wid) / step_edges;
     // -- as far as the partials stay within mp_spmm_noalloc's scratch whatever the
     // reduction (a hub's chunks are under twice its edges / chunk, a partial at
-    // most 12 bytes per feature); explicit thresholds go with 32 steps
+    // most 12 bytes per feature); explicit thresholds go with the most steps
     const int64_t cells = MP_NOALLOC_SCRATCH_BYTES / 12 - 256;
     int64_t steps = E / (4096 * step_edges);
     const int64_t steps_fit = E * F / (cells / 2 * step_edges) + 1;
     if (steps < steps_fit) steps = steps_fit;
-    steps = steps < 8 ? 8 : (steps > 32 ? 32 : steps);
-    if (o.hub_min > 0 || o.chunk_min > 0) steps = 32;
-    p->hub_min = o.hub_min > 0 ? o.hub_min : (steps < 16 ? 2 * steps : 32) * step_edges;
+    steps = steps < 8 ? 8 : (steps > most_steps ? most_steps : steps);
+    if (o.hub_min > 0 || o.chunk_min > 0) steps = most_steps;
+    p->hub_min = o.hub_min > 0 ? o.hub_min
+                               : (steps < most_steps / 2 ? 2 * steps : most_steps) * step_edges;
     if (p->hub_min < p->small_max) p->hub_min = p->small_max;
     p->chunk_min = (int)(o.chunk_min > 0 ? o.chunk_min : steps * step_edges);
     p->rowlist = L.rowlist;
@@ -609,7 +629,7 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
         *out = p;
         return MP_OK;
     }
-    hipError_t e = launch_plan(PlanParams{rowptr, rp64, N_dst, p->small_max, p->hub_min,
+    hipError_t e = launch_plan(PlanParams{rowptr, rp64, N_dst, split, p->small_max, p->hub_min,
                                           p->chunk_min, L.tile_cnt, L.rowlist, L.rowbeg, L.rowend,
                                           L.chunk_off, L.header},
                                s);
@@ -620,12 +640,21 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
         delete p;
         return MP_ERR_HIP;
     }
-    p->mid_base = h[kClassMid];
     p->hub_base = h[kClassHub];
-    p->n_small = p->mid_base;
-    // rows of classes below kTinyClassEnd have at most kTinyDeg edges
-    p->n_tiny = h[kTinyClassEnd] < (uint32_t)p->mid_base ? h[kTinyClassEnd] : p->mid_base;
-    p->n_mid = p->hub_base - p->mid_base;
+    p->n_small = h[kClassMid];
+    // the first class beyond `edges` edges (small rows: bit length, plus one beyond split)
+    auto class_after = [&](int64_t edges) {
+        int bits = 0;
+        while (edges >> bits) ++bits;
+        const int c = bits + 1;
+        return c < kClassMid ? c : kClassMid;
+    };
+    p->n_small_narrow = h[class_after(split)];
+    // (rows of 2^k edges and more have bit length k + 1: class k + 1, or k + 2)
+    p->ge32 = N_dst - h[32 > split ? 7 : 6];
+    p->ge64 = N_dst - h[64 > split ? 8 : 7];
+    // tiny rows: the first classes (the list is sorted by class), if small
+    p->n_tiny = h[kTinyClassEnd] < (uint32_t)p->n_small ? h[kTinyClassEnd] : p->n_small;
     p->n_hub = N_dst - p->hub_base;
     p->n_chunks = h[kPlanClasses + 1];
     *out = p;
@@ -909,7 +938,8 @@ int mp_spmm_backward_x(const mp_plan* planT, const void* rowptrT, int rowptrT_it
     const bool masked = reduce == MP_MAX && !records;
     Geometry g = make_geometry(
         F, t_dtype, (uintptr_t)table,
-        !masked && wide_rows(kUseAggregate, F, t_dtype, (uintptr_t)table, N_src, E));
+        !masked && wide_rows(kUseAggregate, MP_SUM, F, t_dtype, (uintptr_t)table,
+                             row_lengths(planT, N_src)));
     SpmmParams P{};
     P.rowptr = rowptrT;
     P.rp64 = rowptrT_itype == MP_I64;
@@ -972,7 +1002,8 @@ int mp_spmm_backward_w(const void* rowptr, int rowptr_itype, const int32_t* col,
     uintptr_t al = (uintptr_t)x;
     al |= eg == ex ? (uintptr_t)grad_out : (eg > ex ? (uintptr_t)grad_out >> 1 : (uintptr_t)grad_out << 1);
     if (reduce == MP_MAX) al |= ex == 4 ? (uintptr_t)argout : (uintptr_t)argout >> 1;
-    Geometry g = make_geometry(F, x_dtype, al, wide_rows(kUseDot, F, x_dtype, al, N_dst, E));
+    Geometry g = make_geometry(F, x_dtype, al, wide_rows(kUseDot, 0, F, x_dtype, al,
+                                                        RowLengths{N_dst, E, false, 0, 0}));
     GradWParams P{};
     P.rowptr = rowptr;
     P.rp64 = rowptr_itype == MP_I64;
@@ -1123,7 +1154,8 @@ int mp_edge_dot(const void* a, int a_dtype, const void* b, int b_dtype, const in
     uintptr_t al = (uintptr_t)b;
     al |= ea == eb ? (uintptr_t)a : (ea > eb ? (uintptr_t)a >> 1 : (uintptr_t)a << 1);
     // (tables of one row per edge: no row's chunks are shared)
-    Geometry g = make_geometry(F, b_dtype, al, wide_rows(kUseDot, F, b_dtype, al, 0, E));
+    Geometry g = make_geometry(F, b_dtype, al, wide_rows(kUseDot, 0, F, b_dtype, al,
+                                                        RowLengths{0, E, false, 0, 0}));
     GradWParams P{};
     P.col = bidx;
     P.row = nullptr;
@@ -1384,7 +1416,8 @@ int mp_hetero_spmm(int n_types, const int64_t* N_per_type, const void* const* x_
         (uintptr_t)rowptr % (rowptr_itype == MP_I64 ? 8 : 4))
         return MP_ERR_ALIGN;
     Geometry g = make_geometry(F, x_dtype, xa,
-                               wide_rows(kUseAggregate, F, x_dtype, xa, N_dst, plan ? plan->E : 0));
+                               wide_rows(kUseAggregate, reduce, F, x_dtype, xa,
+                                         row_lengths(plan, N_dst)));
     SpmmParams P{};
     P.rowptr = rowptr;
     P.rp64 = rowptr_itype == MP_I64;

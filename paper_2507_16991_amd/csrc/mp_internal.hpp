@@ -200,6 +200,7 @@ enum : int { kSum = MP_SUM, kMean = MP_MEAN, kMax = MP_MAX };
 // slots of L lanes; when Ltot > 64 the row is split into FT feature tiles of
 // 64 lanes, each handled by its own wavefront.
 struct Geometry {
+    bool wide;       // the wide cut of rows that only narrow loads divide
     int elem_bytes;  // 4 (fp32) or 2 (bf16)
     int epl;         // elements per lane-chunk: vector bytes / elem_bytes
     int64_t ltot;    // lane-chunks per feature row
@@ -212,12 +213,19 @@ struct Geometry {
 // divide the row and are aligned.
 Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align, bool wide);
 // Whether rows that only narrow loads divide are better cut into wide chunks,
-// by what is done with them, over `rows` rows of `edges` edges in all.
+// by what is done with them (reduce: of kUseAggregate) and by how long they are.
 enum RowUse { kUseAggregate, kUseStats, kUseDot };
-bool wide_rows(RowUse use, int64_t F, int x_dtype, uintptr_t x_align, int64_t rows, int64_t edges);
+struct RowLengths {
+    int64_t rows, edges;
+    bool planned;        // the plan has counted
+    int64_t ge32, ge64;  // the rows of at least 32 and 64 edges (or more than those)
+};
+bool wide_rows(RowUse use, int reduce, int64_t F, int x_dtype, uintptr_t x_align,
+               const RowLengths& r);
+constexpr int64_t kWideAlways = 33;  // features from which plans take rows by the wide cut
 
 // Degree classes of the plan (keys of the row sort).
-constexpr int kSmallClasses = 16;       // class c < 16: small row, deg < 2^c ... see plan
+constexpr int kSmallClasses = 16;       // small rows: see plan_row
 constexpr int kClassMid = kSmallClasses;
 constexpr int kClassHub = kSmallClasses + 1;
 constexpr int kPlanClasses = kClassHub + 1;
@@ -517,7 +525,7 @@ struct PlanParams {
     const void* rowptr;
     int rp64;
     int64_t N;
-    int64_t small_max, hub_min;
+    int64_t split, small_max, hub_min;  // a class starts after `split` edges too
     int chunk_min;
     uint32_t* tile_cnt;   // [plan_tile_counts(N)]
     int32_t* rowlist;     // [N] rows by class, then by id

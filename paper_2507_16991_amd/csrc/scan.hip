@@ -30,7 +30,8 @@ struct PlanRow {
 };
 
 // Class of a row: small rows by the bit length of the degree (0 for an empty
-// row), then mid, then hub.
+// row), one more beyond `split` edges, then mid, then hub.  (Two limits of small rows,
+// as rows may be aggregated by a narrow and by a wide cut of their features.)
 template <typename IT>
 __device__ inline PlanRow plan_row(const IT* __restrict__ rowptr, int64_t i, const PlanParams& P) {
     PlanRow r;
@@ -46,7 +47,7 @@ __device__ inline PlanRow plan_row(const IT* __restrict__ rowptr, int64_t i, con
     } else if (d > P.small_max) {
         r.cls = kClassMid;
     } else {
-        r.cls = d <= 0 ? 0u : (uint32_t)(64 - __clzll((unsigned long long)d));
+        r.cls = d <= 0 ? 0u : (uint32_t)(64 - __clzll((unsigned long long)d)) + (d > P.split);
     }
     return r;
 }

@@ -1651,7 +1651,8 @@ Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align, bool wide) {
     g.epl = vec / g.elem_bytes;
     // four elements a lane all the same, the last chunk moved back to end with
     // the row
-    if (wide && g.epl < 4 && F >= 4) g.epl = 4;
+    g.wide = wide && g.epl < 4 && F >= 4;
+    if (g.wide) g.epl = 4;
     g.ltot = ceil_div(F, g.epl);
     if (g.ltot <= kWave) {
         g.L = (int)g.ltot;
@@ -1667,32 +1668,55 @@ Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align, bool wide) {
 
 // Wide chunks (loads and stores of 16 bytes at any element, where the aligned
 // cut has 4 or 8 bytes a lane, or 2) need a quarter of the instructions and
-// put more rows into a wavefront; but a load that crosses lines costs up to a
-// tenth of a gather that the memory bounds.  Measured, us of a call, narrow ->
-// wide:
-//   * few edges a row (bound by instructions and latency): F = 75, 4 edges:
-//     fp32 286 -> 130, bf16 287 -> 99; F = 13: 55 -> 45; F = 253, 16 edges:
-//     287 -> 259;
-//   * 30 to 50 edges a row, fp32: F = 47 88 -> 93, F = 50 90 -> 96, F = 253
-//     424 -> 443, where narrow rows fill a wavefront's lanes; but F = 75 154 ->
-//     137 and F = 361 692 -> 606, where they leave a partly filled tile, and
-//     F = 9 37 -> 29;
-//   * the same in bf16: F = 47 63 -> 57, F = 253 240 -> 227, F = 50 (4-byte
-//     loads) 53 -> 55;
-//   * statistics: F = 75 198 -> 165, but F = 22 54 -> 78 (fewer than eight
-//     lanes a row take the slow forms), and F = 47 112 -> 155 on a plan whose
-//     classes are for narrow chunks, so otherwise as the aggregations;
-//   * per-edge dots: F = 75 299 -> 162; with four edges a row, which share
-//     their gradient chunks in fewer slots, F = 22 59 -> 68, F = 75 176 -> 137.
-bool wide_rows(RowUse use, int64_t F, int x_dtype, uintptr_t x_align, int64_t rows, int64_t edges) {
+// put more rows into a wavefront.  Against that, a wavefront's slots are added
+// up at the end of every row that it has to itself, and there are more of them;
+// under eight lanes a row, small rows take the slow form, with fewer edges in
+// flight; and a load that crosses lines costs up to a tenth of a gather that
+// the memory bounds.  Time of wide over narrow chunks, measured over even and
+// uneven degrees of 4 to 60 edges, 20k to 8M edges, fp32 (bf16):
+//   * 33 features and more over a plan: 0.40 to 1.05 while rows have under 24
+//     edges on average; with 24 and more, F = 47 0.97 to 1.09, F = 50 to 1.14 (F =
+//     47 0.74 to 1.03, F = 50 to 1.09), F = 253 0.95 to 1.08; but F = 75 0.6 to 0.99,
+//     where narrow chunks leave a partly filled tile; F = 101 0.6 to 0.9 on 1M
+//     edges, 1.08 on 8M;
+//   * up to 32 features: sum 0.67 to 0.95 on rows of up to 63 edges (bf16 to
+//     1.2 at 30 edges), 1.1 to 2.6 where there are longer ones; max and the fused
+//     pair 0.7 to 1.0 while few rows have 32 edges, 1.0 to 1.5 at 30, 1.2 to 4.5 where
+//     there are longer ones (max alone from 21 features on 0.7 to 0.9 at 30).
+//     Two features a lane as they are: nothing under ten features, and 1.0 to
+//     1.15 for the fused pair.  fp32 rows of 30 edges, 8M edges: 1.0 to 1.2;
+//   * without a plan every row has a wavefront: up to 64 features 1.0 to 1.8,
+//     and 0.25 to 0.6 only where a hub row is all of the time; beyond, 0.4 to
+//     1.0 (hub rows alone up to 1.3, statistics 2.0: their one wavefront
+//     instead of one per 64 features);
+//   * statistics as the aggregations, but 1.0 to 1.3 and more up to 32 features;
+//   * dots: 0.4 to 0.98; but two features a lane: under ten features 1.05,
+//     bf16 of 128 and more 1.04, and with four edges a row, which share their
+//     gradient chunks in fewer slots, up to 1.15.
+bool wide_rows(RowUse use, int reduce, int64_t F, int x_dtype, uintptr_t x_align,
+               const RowLengths& r) {
     const Geometry g = make_geometry(F, x_dtype, x_align, false);
     if (g.epl >= 4 || F < 4) return false;
-    if (use == kUseStats && F < 32) return false;
-    if (use == kUseDot) return edges >= 8 * rows || (g.epl == 1 && F >= 32);
-    if (edges < 24 * rows) return true;
-    if (x_dtype == MP_BF16) return g.epl == 1 || F >= 64;
-    const bool full = 10 * g.ltot >= 9 * (int64_t)kWave * g.FT;
-    return F < 32 || (g.FT > 1 && !(full && F <= 256));
+    const bool bf16 = x_dtype == MP_BF16, pairs = g.epl == 2;
+    if (use == kUseDot) {
+        if (pairs && (F < 10 || (bf16 && F >= 128))) return false;
+        return r.edges >= 8 * r.rows || (!pairs && F >= 32);
+    }
+    if (!r.planned) return g.FT > 1;
+    const bool many = r.edges >= 24 * r.rows;  // edges a row
+    const bool large = r.edges >= (int64_t(1) << 22);
+    if (F < kWideAlways) {
+        if (use == kUseStats || r.ge64 > 0 || (!bf16 && many && large)) return false;
+        const bool hs = (reduce & (kSum | kMean)) != 0, hm = (reduce & kMax) != 0;
+        const bool few_long = 8 * r.ge32 <= r.rows;
+        if (!hm) return (!pairs || F >= 10) && (!bf16 || few_long);
+        if (!hs && F >= 21) return true;
+        return few_long && (!pairs || (!hs && F >= 10));
+    }
+    if (!many) return true;
+    if (bf16) return !pairs || F >= 64;
+    const int64_t lanes = (int64_t)kWave * g.FT;
+    return g.FT > 1 && (F > 256 || (large ? 2 * lanes >= 3 * g.ltot : 10 * g.ltot < 9 * lanes));
 }
 
 hipError_t launch_spmm(const SpmmParams& p, int x_dtype, int epl, hipStream_t s) {

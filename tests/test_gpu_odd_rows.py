@@ -38,13 +38,13 @@ def shifted(a, dtype, shift, ld=None):
 
 @pytest.mark.parametrize("F", [4, 5, 7, 29, 31, 33, 50, 75, 253, 255, 257, 261])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("deg_hi", [9, 80])
+@pytest.mark.parametrize("deg_hi", [9, 80, -24, -64])  # below 0: no row is longer, else one hub
 @pytest.mark.parametrize("shift,pad", [(0, 0), (1, 0), (0, 3)])
 def test_all_outputs(F, dtype, deg_hi, shift, pad):
-    rng = np.random.default_rng(F + deg_hi)
+    rng = np.random.default_rng(F + abs(deg_hi))
     n_dst, n_src = 61, 40
-    deg = rng.integers(0, deg_hi, n_dst)
-    deg[[3, 7]] = [0, 700]  # an empty row and a hub
+    deg = rng.integers(0, abs(deg_hi), n_dst)
+    deg[[3, 7]] = [0, 700 if deg_hi > 0 else -deg_hi - 1]  # an empty row and a hub
     rp = np.concatenate([[0], np.cumsum(deg)])
     E = int(rp[-1])
     row = np.repeat(np.arange(n_dst), deg)
