@@ -40,8 +40,9 @@
  *    (their behaviour is then undefined); mp_validate_coo and mp_validate_csr
  *    count them.
  *  - Determinism.  Every output is a deterministic function of the inputs:
- *    the floating-point summation order is fixed by the plan geometry, and no
- *    floating-point atomics are used.
+ *    the floating-point summation order is fixed by the plan geometry (and for
+ *    mp_spmm_backward_x of MP_MAX by the size of the workspace, see there), and
+ *    no floating-point atomics are used.
  */
 #ifndef MP_H_
 #define MP_H_
@@ -362,7 +363,9 @@ int mp_csr_transpose(const void* rowptr, int rowptr_itype, const int32_t* col, i
  * MP_MAX also the wins of every edge: the win masks, ceil(F / 32) 32-bit words
  * per edge (bit f of the words of forward position p: argout[row(p), f] == p),
  * or, on larger graphs whose edges win few features, records of 32 bytes per
- * edge (at most 8 GiB; with room for the masks only, the masks are used). */
+ * edge (at most 8 GiB).  A smaller workspace with room for the masks is
+ * accepted, and the masks are used: the size of the workspace then decides in
+ * which order a row's wins are added. */
 int mp_spmm_backward_x_workspace(const mp_plan* planT, int64_t N_dst, int64_t E, int64_t F,
                                  int reduce, size_t* bytes);
 

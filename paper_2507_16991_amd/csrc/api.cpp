@@ -916,11 +916,9 @@ int mp_spmm_backward_x(const mp_plan* planT, const void* rowptrT, int rowptrT_it
         t_dtype = MP_F32;
     }
     uint32_t* mbits = nullptr;
-    // (records are written in 16-byte stores; a workspace with room for the
-    // masks alone gets the masks)
+    // (a workspace with room for the masks alone gets the masks)
     const bool records = reduce == MP_MAX && use_win_records(N_dst, E, F) &&
-                         ws_bytes >= part + win_records_bytes(E) &&
-                         (uintptr_t)extra_buf % 16 == 0;
+                         ws_bytes >= part + win_records_bytes(E);
     if (reduce == MP_MAX) {
         // max: the wins of every forward position, then a sum over the
         // transposed CSR of the features each edge wins

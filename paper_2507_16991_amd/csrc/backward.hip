@@ -212,6 +212,9 @@ __global__ __launch_bounds__(kBlock) void win_masks(const IT* __restrict__ rowpt
 // feature order; bytes 24..29 their feature ids; byte 30 zero; byte 31 the
 // number of wins (at most 255).
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4w __attribute__((ext_vector_type(4), aligned(4)));
+
 constexpr int kRecRows = 4;        // consecutive rows of a wavefront
 constexpr int kRecPart = 1024;     // positions of a row that its own wavefront writes
 
@@ -305,11 +308,12 @@ __global__ __launch_bounds__(kBlock) void win_records(const IT* __restrict__ row
                 }
                 __builtin_amdgcn_wave_barrier();
             }
-            uint4* const out = reinterpret_cast<uint4*>(recs + (beg + c0) * kWinWords);
+            // (aligned to a word: wherever the caller's workspace begins)
+            u32x4w* const out = reinterpret_cast<u32x4w*>(recs + (beg + c0) * kWinWords);
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int i = k * kWave + lane;  // 16-byte half i of the chunk's records
-                if (i < 2 * n) out[i] = *reinterpret_cast<const uint4*>(rec + 4 * i);
+                if (i < 2 * n) out[i] = *reinterpret_cast<const u32x4*>(rec + 4 * i);
             }
             __builtin_amdgcn_wave_barrier();
         }

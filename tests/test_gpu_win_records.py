@@ -90,3 +90,28 @@ def test_records_are_for_large_graphs_of_few_wins():
     assert size(E // 2 // 64, E, 64) == 8 and size(3 * (E - 64) // 64, E - 64, 64) == 8
     assert size(E // 257, E, 257) == 36
     assert size(1 << 23, 1 << 28, 64) == 32 and size(1 << 23, (1 << 28) + 64, 64) == 8
+
+
+@pytest.mark.parametrize("F", [7, 100])
+def test_same_bits_wherever_the_workspace_begins(F):
+    """The order of additions depends on the inputs and the workspace's size, not
+    on its address: random G, whose sums differ with the order."""
+    n, E = 2 * E_MIN // F, E_MIN
+    gen = torch.Generator(device=DEV).manual_seed(F)
+    dst = torch.randint(0, n, (E,), generator=gen, device=DEV, dtype=torch.int32)
+    src = torch.randint(0, 500, (E,), generator=gen, device=DEV, dtype=torch.int32)
+    rp, col, _, _ = mp.coo_to_csr(src, dst, n)
+    x = torch.randn(500, F, generator=gen, device=DEV)
+    g = torch.randn(n, F, generator=gen, device=DEV)
+    _, _, arg = mp.spmm(rp, col, x, mp.MP_MAX)
+    rpT, colT, posT, _ = mp.csr_transpose(rp, col, 500)
+    plan = mp.Plan(rpT, E, F)
+    nb = mp.mp_spmm_backward_x_workspace(plan.handle, n, E, F, mp.MP_MAX)
+    got = []
+    for shift in (0, 4, 12, 16):
+        ws = torch.empty(nb + shift, dtype=torch.uint8, device=DEV)[shift:]
+        out = torch.empty(500, F, device=DEV)
+        mp.mp_spmm_backward_x(plan.handle, rpT, mp.MP_I32, colT, posT, None, rp, mp.MP_I32, arg, g,
+                              mp.MP_F32, n, 500, E, F, mp.MP_MAX, out, mp.MP_F32, ws, nb)
+        got.append(out)
+    assert all(torch.equal(o, got[0]) for o in got[1:])
