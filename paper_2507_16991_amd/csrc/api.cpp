@@ -845,6 +845,15 @@ size_t backward_x_extra(int64_t N_dst, int64_t E, int64_t F, int reduce) {
 // The same for win records, never less than for the masks.
 size_t win_records_bytes(int64_t E) { return align_up((size_t)E * kWinWords * 4, 256); }
 
+// Records hold fp32 values; the masks' way reads a bf16 gradient as it is, half
+// the bytes, which is ahead where few edges share a row's read and records are
+// mostly empty (us by masks -> by records, four edges a row: 2M edges F = 7 151 ->
+// 165, F = 12 160 -> 177, 8M edges F = 12 654 -> 746; eight edges a row: F = 5 94 ->
+// 108, F = 13 126 -> 112).
+static bool masks_for_bf16(int g_dtype, int64_t N_dst, int64_t E, int64_t F) {
+    return g_dtype == MP_BF16 && (F < 8 || E < 6 * N_dst);
+}
+
 int mp_spmm_backward_x_workspace(const mp_plan* planT, int64_t N_dst, int64_t E, int64_t F,
                                  int reduce, size_t* bytes) {
     if (!bytes) return MP_ERR_NULL;
@@ -918,6 +927,7 @@ int mp_spmm_backward_x(const mp_plan* planT, const void* rowptrT, int rowptrT_it
     uint32_t* mbits = nullptr;
     // (a workspace with room for the masks alone gets the masks)
     const bool records = reduce == MP_MAX && use_win_records(N_dst, E, F) &&
+                         !masks_for_bf16(g_dtype, N_dst, E, F) &&
                          ws_bytes >= part + win_records_bytes(E);
     if (reduce == MP_MAX) {
         // max: the wins of every forward position, then a sum over the
