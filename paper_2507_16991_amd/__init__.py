@@ -712,7 +712,11 @@ def spmm_backward_x(rowptrT, colT, grad_out, reduce, *, posT=None, wT=None, rowp
                     argout=None, planT: Plan | None = None, out_dtype=torch.float32, out=None,
                     stream=None):
     """dL/dx of spmm for one reduction, over the transposed CSR (rowptr, the
-    forward one, is needed for mean and max)."""
+    forward one, is needed for mean and max).
+
+    Where the GPU's memory does not hold the full workspace of max (up to 32
+    bytes per edge), the call goes by the win masks, an eighth of that for
+    up to 32 features, which add in another order."""
     N_src = int(rowptrT.numel()) - 1
     N_dst, F = int(grad_out.shape[0]), int(grad_out.shape[1])
     E = int(colT.numel())
@@ -721,7 +725,17 @@ def spmm_backward_x(rowptrT, colT, grad_out, reduce, *, posT=None, wT=None, rowp
         out = torch.empty(N_src, F, dtype=out_dtype, device=dev)
     h = planT.handle if planT is not None else None
     nb = mp_spmm_backward_x_workspace(h, N_dst, E, F, reduce)
-    ws = _workspace(nb, dev) if nb else None
+    try:
+        ws = _workspace(nb, dev) if nb else None
+    except torch.OutOfMemoryError:
+        if reduce != MP_MAX:
+            raise
+        # the aggregation's own part and the masks (include/mp.h)
+        part = mp_spmm_backward_x_workspace(h, N_dst, E, F, MP_SUM)
+        masks = -(-part // 256) * 256 + -(-max(E, 1) * (-(-F // 32)) * 4 // 256) * 256
+        if masks >= nb:
+            raise
+        ws = _workspace(masks, dev)
     mp_spmm_backward_x(h, rowptrT, _itype_code(rowptrT.dtype), colT, posT, wT, rowptr,
                        _itype_code(rowptr.dtype) if rowptr is not None else MP_I32, argout,
                        grad_out, _dtype_code(grad_out.dtype), N_dst, N_src, E, F, reduce, out,

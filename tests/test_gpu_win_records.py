@@ -115,3 +115,35 @@ def test_same_bits_wherever_the_workspace_begins(F):
                               mp.MP_F32, n, 500, E, F, mp.MP_MAX, out, mp.MP_F32, ws, nb)
         got.append(out)
     assert all(torch.equal(o, got[0]) for o in got[1:])
+
+
+def test_masks_where_memory_does_not_hold_the_records(monkeypatch):
+    """The binding's call goes on with the smaller workspace; integer G, so both
+    ways give the same bits."""
+    F, E = 40, E_MIN
+    n = 2 * E // F
+    dst = torch.randint(0, n, (E,), device=DEV, dtype=torch.int32)
+    src = torch.randint(0, 300, (E,), device=DEV, dtype=torch.int32)
+    rp, col, _, _ = mp.coo_to_csr(src, dst, n)
+    _, _, arg = mp.spmm(rp, col, torch.randn(300, F, device=DEV), mp.MP_MAX)
+    g = torch.randint(-8, 9, (n, F), device=DEV).float()
+    rpT, colT, posT, _ = mp.csr_transpose(rp, col, 300)
+    plan = mp.Plan(rpT, E, F)
+    call = lambda: mp.spmm_backward_x(rpT, colT, g, mp.MP_MAX, posT=posT, rowptr=rp, argout=arg,
+                                      planT=plan)
+    want = call()
+    full = mp.mp_spmm_backward_x_workspace(plan.handle, n, E, F, mp.MP_MAX)
+    real, asked = mp._workspace, []
+
+    def small_card(nbytes, device):
+        asked.append(nbytes)
+        if nbytes >= full:
+            raise torch.OutOfMemoryError("no room")
+        return real(nbytes, device)
+
+    monkeypatch.setattr(mp, "_workspace", small_card)
+    assert torch.equal(call(), want)
+    assert len(asked) == 2 and asked[0] == full and asked[1] < full // 2
+    monkeypatch.setattr(mp, "_workspace", lambda nbytes, device: small_card(full, device))
+    with pytest.raises(torch.OutOfMemoryError):
+        call()
