@@ -26,6 +26,15 @@ def _announce(request):
                                    [30 * 2048 + 7, 0], [2048] * 5])
 @pytest.mark.parametrize("F,Fo", [(8, 8), (24, 136)])
 def test_weight_gradient(sizes, F, Fo):
+    check(sizes, F, Fo)
+
+
+@pytest.mark.parametrize("chunks", [17, 64, 65])  # elements enough: shared beyond 64 chunks
+def test_weight_gradient_of_many_elements(chunks):
+    check([chunks * 2048 - 5, 3], 264, 504)
+
+
+def check(sizes, F, Fo):
     rng = np.random.default_rng(len(sizes) + F)
     seg = [0] + list(np.cumsum(sizes))
     n, T = seg[-1], len(sizes)
