@@ -50,11 +50,10 @@ __device__ inline int64_t rp_at(const void* rp, int rp64, int64_t i) {
 // merged):
 //   124M edges over 2.4M rows      171   183   176
 //   power law, 1.2M, a row of 36k  240     8     9
-//   1M edges over 1M rows            8    18    12
-//   300k edges over 20k rows        11     6     7
-//   50k edges over 1M rows           7   484    10
-//   300 edges over 16k rows          5   883     9
-// What is left on small graphs is the searches' three round trips.
+//   1M edges over 1M rows            7    17    10
+//   300k edges over 20k rows        10     5     5
+//   50k edges over 1M rows           6   489     8
+//   300 edges over 16k rows          5   883     8
 // Bounds are clamped to [0, E], the last row's is E, so ids lie below N whatever
 // the input (an inconsistent rowptr only makes ids wrong).
 template <typename IT>

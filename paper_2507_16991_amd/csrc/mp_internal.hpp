@@ -340,19 +340,33 @@ __device__ inline int64_t row_of_position(const IT* __restrict__ rowptr, int64_t
 // (value i before output q where a(i) <= q; value i is item a(i) + i), and each
 // workgroup takes SPAN consecutive ITEMS, so its work is the same where many
 // values lie between two outputs, and many outputs between two values.  Two
-// wavefronts find the ends of its range by 64-way searches (2.4M values: four
-// round trips), its values are staged in LDS and each lane searches them for
+// wavefronts find the ends of its range by 64-way searches (mostly two round
+// trips), its values are staged in LDS and each lane searches them for
 // four consecutive outputs, which it stores together.
 //
 // Whatever the values, every output is written, with a count in [0, n], and the
-// work ends: the searches' rounds depend on n alone, and neighbouring
-// workgroups search for the same ends.
+// work ends: a search has at most one round per six bits of n and one more, and
+// neighbouring workgroups search for the same ends.
 
 // The number of values whose item lies before item d (the whole wavefront; all
-// lanes active).
+// lanes active).  A first round looks around the place that evenly spread
+// values would give, which mostly leaves one more round.
 template <typename A>
-__device__ inline int64_t merge_search(const A& a, int64_t n, int64_t d, int lane) {
+__device__ inline int64_t merge_search(const A& a, int64_t n, int64_t items, int64_t d, int lane) {
     int64_t r = 0, c = n;  // the result is in [r, r + c]
+    constexpr int64_t kWindow = kWave * kWave;
+    if (n > 2 * kWindow) {
+        const int64_t guess = (int64_t)((double)d * ((double)n / (double)items)) - kWindow / 2;
+        const int64_t w0 = guess < 0 ? 0 : (guess > n - kWindow ? n - kWindow : guess);
+        const int64_t i = w0 + (int64_t)(lane + 1) * kWave - 1;
+        const int k = __popcll(__ballot(a(i) + i < d));
+        if (k == 0) {  // in [0, w0 + kWave - 1]
+            c = w0 + kWave - 1;
+        } else {
+            r = w0 + (int64_t)k * kWave;
+            c = k == kWave ? n - r : kWave - 1;
+        }
+    }
     while (c > 0) {
         const int64_t step = (c + kWave - 1) / kWave;
         const int64_t i = (int64_t)(lane + 1) * step - 1;
@@ -376,7 +390,7 @@ __device__ inline void merge_counts(const A& a, int64_t n, int64_t m, OUT* __res
     const int64_t d0 = (int64_t)blockIdx.x * SPAN;
     const int64_t d1 = d0 + SPAN < n + m ? d0 + SPAN : n + m;
     if (wv < 2) {
-        const int64_t r = merge_search(a, n, wv == 0 ? d0 : d1, lane);
+        const int64_t r = merge_search(a, n, n + m, wv == 0 ? d0 : d1, lane);
         if (lane == 0) s_end[wv] = r;
     }
     __syncthreads();
