@@ -1700,7 +1700,8 @@ Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align, bool wide) {
 //     and 0.25 to 0.6 only where a hub row is all of the time; beyond, 0.4 to
 //     1.0 (hub rows alone up to 1.3, statistics 2.0: their one wavefront
 //     instead of one per 64 features);
-//   * statistics as the aggregations, but 1.0 to 1.3 and more up to 32 features;
+//   * statistics as the aggregations, but 1.0 to 1.3 and more up to 32 features,
+//     and 1.1 to 1.25 (of 7 us) on a few thousand edges;
 //   * dots: 0.4 to 0.98; but two features a lane: under ten features 1.05,
 //     bf16 of 128 and more 1.04, and with four edges a row, which share their
 //     gradient chunks in fewer slots, up to 1.15.
@@ -1708,12 +1709,15 @@ bool wide_rows(RowUse use, int reduce, int64_t F, int x_dtype, uintptr_t x_align
                const RowLengths& r) {
     const Geometry g = make_geometry(F, x_dtype, x_align, false);
     if (g.epl >= 4 || F < 4) return false;
+    // (eight features that only start unaligned: sum 13.6 -> 16.6 us)
+    if (F == 8 && use != kUseDot) return false;
     const bool bf16 = x_dtype == MP_BF16, pairs = g.epl == 2;
     if (use == kUseDot) {
         if (pairs && (F < 10 || (bf16 && F >= 128))) return false;
         return r.edges >= 8 * r.rows || (!pairs && F >= 32);
     }
     if (!r.planned) return g.FT > 1;
+    if (use == kUseStats && r.edges < (1 << 15)) return false;
     const bool many = r.edges >= 24 * r.rows;  // edges a row
     const bool large = r.edges >= (int64_t(1) << 22);
     if (F < kWideAlways) {
