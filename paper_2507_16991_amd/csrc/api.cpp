@@ -12,6 +12,7 @@
 
 #include "mp_internal.hpp"
 
+
 using namespace mp;
 
 namespace {
@@ -223,7 +224,6 @@ int run_spmm(const mp_plan* plan, SpmmParams& P, const Geometry& g, int x_dtype,
         P.rowbeg = plan->rowbeg;
         P.rowend = plan->rowend;
         P.chunk_off = plan->chunk_off;
-        P.chunk_min = plan->chunk_min;
         P.n_tiny = tiny ? plan->n_tiny : 0;
         P.small_base = P.n_tiny;
         P.mid_base = g.wide || P.recs ? plan->n_small : plan->n_small_narrow;
@@ -599,28 +599,40 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
         if (p->small_max < most) p->small_max = most;
     }
     // a wavefront takes S * U edges per step; rows longer than 32 steps are
-    // split into chunks of at least 32 steps, so that no wavefront runs a long
-    // chain of dependent steps on its own.  Where the edges do not give 4096
-    // wavefronts that many, the longest chain is the call's time: chunks of
-    // down to 8 steps, for rows of more than two (power-law graph of 120k
-    // edges, F = 75: fp32 sum 28 -> 20 us, max 35 -> 25).  The short chunks are
-    // by the narrow cut's steps, the long ones by the wide cut's
-    auto step_of = [](const Geometry& g) { return (int64_t)g.S * (g.S * 8 > 64 ? 64 / g.S : 8); };
-    const int64_t step_edges = step_of(nar);
-    const int64_t most_steps = 32 * step_of(wid) / step_edges;
+    // split into chunks of up to 32 steps (of the wide cut where the edges give
+    // 4096 wavefronts that many), so that no wavefront runs a long chain of
+    // dependent steps on its own
+    auto unroll = [](const Geometry& g) { return (int64_t)(g.S * 8 > 64 ? 64 / g.S : 8); };
+    const int64_t step_edges = nar.S * unroll(nar);
+    const int64_t wide_steps = F >= kWideAlways ? 32 * wid.S * unroll(wid) / step_edges : 32;
+    const int64_t mean = N_dst > 0 ? E / N_dst : 0;
+    const bool few_hubs = 32 * step_edges >= 4 * mean;  // long rows are the exception
+    // Where the edges do not give enough wavefronts 32 steps, shorter chunks.
+    // With few hubs the longest chain is the call's time: down to the chain of
+    // the small rows, 8 steps at least, and for rows of more than two of these
+    // (power-law graph of 120k edges, F = 75: fp32 sum 28 -> 20 us, max 35 -> 25;
+    // below the small rows' chain only the combining of the chunks adds, F = 20,
+    // 20k edges: max 46 -> 49).  Where most rows are long, each chunk costs more than the
+    // filled card gives: a quarter of the wavefronts (1024 segments of 500 rows, F =
+    // 100: statistics 51 -> 40 us; of 2392 rows, F = 16, bf16: 91 -> 62)
+    const int64_t least = few_hubs ? 16 * nar.S / unroll(nar) : 8;
+    int64_t steps = E / ((few_hubs ? 4096 : 1024) * step_edges);
+    if (steps < least) steps = least;
+    steps = steps < 8 ? 8 : (steps > 32 ? 32 : steps);
+    const int64_t by_wide = E / (4096 * step_edges);
+    if (by_wide > steps) steps = by_wide < wide_steps ? by_wide : (wide_steps > steps ? wide_steps : steps);
     // -- as far as the partials stay within mp_spmm_noalloc's scratch whatever the
     // reduction (a hub's chunks are under twice its edges / chunk, a partial at
     // most 12 bytes per feature); explicit thresholds go with the most steps
     const int64_t cells = MP_NOALLOC_SCRATCH_BYTES / 12 - 256;
-    int64_t steps = E / (4096 * step_edges);
     const int64_t steps_fit = E * F / (cells / 2 * step_edges) + 1;
-    if (steps < steps_fit) steps = steps_fit;
-    steps = steps < 8 ? 8 : (steps > most_steps ? most_steps : steps);
-    if (o.hub_min > 0 || o.chunk_min > 0) steps = most_steps;
-    p->hub_min = o.hub_min > 0 ? o.hub_min
-                               : (steps < most_steps / 2 ? 2 * steps : most_steps) * step_edges;
-    if (p->hub_min < p->small_max) p->hub_min = p->small_max;
+    if (steps < steps_fit) steps = steps_fit < wide_steps ? steps_fit : wide_steps;
+    if (o.hub_min > 0 || o.chunk_min > 0) steps = wide_steps;
     p->chunk_min = (int)(o.chunk_min > 0 ? o.chunk_min : steps * step_edges);
+    const bool soon = few_hubs && steps < 16 && 2 * steps * step_edges >= 4 * mean;
+    p->hub_min = o.hub_min > 0 ? o.hub_min
+                               : (soon ? 2 * steps : (steps > 32 ? steps : 32)) * step_edges;
+    if (p->hub_min < p->small_max) p->hub_min = p->small_max;
     p->rowlist = L.rowlist;
     p->rowbeg = L.rowbeg;
     p->rowend = L.rowend;

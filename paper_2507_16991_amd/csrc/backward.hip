@@ -472,9 +472,10 @@ __global__ __launch_bounds__(kBlock) void win_gather(SpmmParams P, int fp) {
             }
             row = P.rowlist[P.hub_base + lo];
             const int64_t r0 = rp_at(P.rowptr, P.rp64, row), r1 = rp_at(P.rowptr, P.rp64, row + 1);
-            int64_t csz = (r1 - r0 + kMaxChunksPerHub - 1) / kMaxChunksPerHub;
-            if (csz < P.chunk_min) csz = P.chunk_min;
-            e0 = r0 + (wv - (int64_t)P.chunk_off[P.hub_base + lo]) * csz;
+            const uint32_t first = P.chunk_off[P.hub_base + lo];
+            const uint32_t n = P.chunk_off[P.hub_base + lo + 1] - first;
+            const int64_t csz = ((uint32_t)(r1 - r0) + n - 1) / n;  // as in spmm_main
+            e0 = r0 + (wv - (int64_t)first) * csz;
             e1 = e0 + csz < r1 ? e0 + csz : r1;
         } else {
             const int64_t k = P.mid_base + wv - P.n_hub_waves;

@@ -259,7 +259,6 @@ struct SpmmParams {
     int64_t hub_base, mid_base, small_base, n_small, n_hub;
     int64_t n_tiny;          // rowlist[0, n_tiny): rows for the tiny-row kernel
     const uint32_t* chunk_off;  // indexed by rowlist position
-    int chunk_min;
     int reduce;
     void* out;
     int out_bf16;

@@ -1172,9 +1172,11 @@ void spmm_main(SpmmParams P) {
             const int64_t r0 = load_rp(P.rowptr, P.rp64, row);
             const int64_t r1 = load_rp(P.rowptr, P.rp64, row + 1);
             const int64_t deg = r1 - r0;
-            int64_t csz = (deg + kMaxChunksPerHub - 1) / kMaxChunksPerHub;
-            if (csz < P.chunk_min) csz = P.chunk_min;
-            const int64_t k = item - (int64_t)P.chunk_off[P.hub_base + lo];
+            // the row's chunks are equally long
+            const uint32_t first = P.chunk_off[P.hub_base + lo];
+            const uint32_t n = P.chunk_off[P.hub_base + lo + 1] - first;
+            const int64_t csz = ((uint32_t)deg + n - 1) / n;
+            const int64_t k = item - (int64_t)first;
             e0 = r0 + k * csz;
             e1 = e0 + csz < r1 ? e0 + csz : r1;
             cidx = item;

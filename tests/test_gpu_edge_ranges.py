@@ -153,10 +153,11 @@ def test_message_gradient_in_long_parts(e, F, reduce):
 
 
 @pytest.mark.parametrize("F", [64, 70])  # one and two 64-feature tiles
-def test_hub_rows_of_few_and_many_chunks(F):
+@pytest.mark.parametrize("opts", [(1, 1, 1), (4, 9, 7)])  # and chunks that do not divide the rows
+def test_hub_rows_of_few_and_many_chunks(F, opts):
     """Hub rows of one edge per chunk, their chunk counts on both sides of the
     16 (statistics) and 32 that one wavefront combines and at the 2048 of the
-    longest rows.
+    longest rows; and rows cut evenly into chunks of up to seven edges.
     Integer features: sums are exact in any order."""
     deg = np.array([2, 16, 17, 32, 33, 63, 64, 65, 0, 66, 512, 2047, 2048, 5000, 1, 130])
     rp, rp_d = rowptr_of(deg, torch.int32)
@@ -164,7 +165,7 @@ def test_hub_rows_of_few_and_many_chunks(F):
     rng = np.random.default_rng(9)
     x = rng.integers(-8, 9, (40, F)).astype(np.float32)
     col = rng.integers(0, 40, E).astype(np.int32)
-    plan = mp.Plan(rp_d, E, F, torch.float32, opts=(1, 1, 1))
+    plan = mp.Plan(rp_d, E, F, torch.float32, opts=opts)
     out, mx, arg = mp.spmm(rp_d, torch.from_numpy(col).to(DEV), torch.from_numpy(x).to(DEV),
                            mp.MP_SUM | mp.MP_MAX, plan=plan)
     multi = mp.spmm_multi(rp_d, torch.from_numpy(col).to(DEV), torch.from_numpy(x).to(DEV),
