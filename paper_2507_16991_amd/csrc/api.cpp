@@ -587,8 +587,8 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
     p->x_dtype = x_dtype;
     // rows of up to 16 edges per slot get one slot; longer rows a wavefront.  Where
     // rows may be cut into narrow or wide chunks (wide_rows), each has its
-    // limit; of up to 32 features, wide ones are taken only where no row has
-    // 64 edges, and all are small then
+    // limit; of up to 32 features, wide ones are taken only where no or few rows
+    // have 64 edges, and all others are small then
     const Geometry nar = make_geometry(F, x_dtype, 16, false);
     const Geometry wid = make_geometry(F, x_dtype, 16, true);
     p->small_max = o.small_max > 0 ? o.small_max : 16 * (int64_t)nar.S;
@@ -615,7 +615,10 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
     // 20k edges: max 46 -> 49).  Where most rows are long, each chunk costs more than the
     // filled card gives: a quarter of the wavefronts (1024 segments of 500 rows, F =
     // 100: statistics 51 -> 40 us; of 2392 rows, F = 16, bf16: 91 -> 62)
-    const int64_t least = few_hubs ? 16 * nar.S / unroll(nar) : 8;
+    // (and of rows that go by the wide cut 8 of its steps, up to 32 narrow ones)
+    int64_t least = few_hubs ? 16 * nar.S / unroll(nar) : 8;
+    if (few_hubs && least < wide_steps / 4 && F >= kWideAlways)
+        least = wide_steps / 4 < 32 ? wide_steps / 4 : 32;
     int64_t steps = E / ((few_hubs ? 4096 : 1024) * step_edges);
     if (steps < least) steps = least;
     steps = steps < 8 ? 8 : (steps > 32 ? 32 : steps);

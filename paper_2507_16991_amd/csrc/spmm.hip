@@ -1692,12 +1692,15 @@ Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align, bool wide) {
 //     47 0.74 to 1.03, F = 50 to 1.09), F = 253 0.95 to 1.08; but F = 75 0.6 to 0.99,
 //     where narrow chunks leave a partly filled tile; F = 101 0.6 to 0.9 on 1M
 //     edges, 1.08 on 8M;
-//   * up to 32 features: sum 0.67 to 0.95 on rows of up to 63 edges (bf16 to
-//     1.2 at 30 edges), 1.1 to 2.6 where there are longer ones; max and the fused
-//     pair 0.7 to 1.0 while few rows have 32 edges, 1.0 to 1.5 at 30, 1.2 to 4.5 where
-//     there are longer ones (max alone from 21 features on 0.7 to 0.9 at 30).
-//     Two features a lane as they are: nothing under ten features, and 1.0 to
-//     1.15 for the fused pair.  fp32 rows of 30 edges, 8M edges: 1.0 to 1.2;
+//   * up to 28 features (under eight lanes): sum 0.67 to 0.95 on rows of up to 63
+//     edges (bf16 at 30 edges 0.85 to 0.94 where two or four lanes take a row, to
+//     1.2 where they leave some idle), 1.1 to 2.6 where there are longer ones; max
+//     and the fused pair 0.7 to 1.0 while few rows have 32 edges, 1.0 to 1.5 at
+//     30, 1.2 to 4.5 where there are longer ones (max alone from 21 features on 0.7
+//     to 0.9 at 30).  Two features a lane as they are: nothing under ten
+//     features, and 1.0 to 1.15 for the fused pair, but 22 features of four to
+//     eight edges 0.87 to 0.97.  fp32 rows of 30 edges, 8M edges: 1.0 to 1.2;
+//   * 29 to 32 features: 0.55 to 0.9, but 1.1 to 1.5 where most rows have 64 edges;
 //   * without a plan every row has a wavefront: up to 64 features 1.0 to 1.8,
 //     and 0.25 to 0.6 only where a hub row is all of the time; beyond, 0.4 to
 //     1.0 (hub rows alone up to 1.3, statistics 2.0: their one wavefront
@@ -1723,12 +1726,16 @@ bool wide_rows(RowUse use, int reduce, int64_t F, int x_dtype, uintptr_t x_align
     const bool many = r.edges >= 24 * r.rows;  // edges a row
     const bool large = r.edges >= (int64_t(1) << 22);
     if (F < kWideAlways) {
-        if (use == kUseStats || r.ge64 > 0 || (!bf16 && many && large)) return false;
+        if (use == kUseStats || (!bf16 && many && large)) return false;
+        if (F > 28) return 8 * r.ge64 <= r.rows;  // eight lanes a row
+        if (r.ge64 > 0) return false;
         const bool hs = (reduce & (kSum | kMean)) != 0, hm = (reduce & kMax) != 0;
         const bool few_long = 8 * r.ge32 <= r.rows;
-        if (!hm) return (!pairs || F >= 10) && (!bf16 || few_long);
+        const bool full = F <= 8 || (F > 12 && F <= 16);  // two or four lanes a row: no idle ones
+        if (!hm) return (!pairs || F >= 10) && (!bf16 || few_long || full);
         if (!hs && F >= 21) return true;
-        return few_long && (!pairs || (!hs && F >= 10));
+        if (pairs) return hs ? F >= 21 && r.edges < 12 * r.rows : F >= 10 && few_long;
+        return few_long;
     }
     if (!many) return true;
     if (bf16) return !pairs || F >= 64;
