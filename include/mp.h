@@ -181,8 +181,8 @@ int mp_spmm_plan_build(const void* rowptr, int rowptr_itype, int64_t N_dst, int6
  *   hub_min     rows of more than this many edges (raised to small_max if
  *               lower) are cut into edge chunks aggregated by separate
  *               wavefronts and combined in chunk order;
- *   chunk_min   the fewest edges of such a chunk (at most 2048 chunks per
- *               row). */
+ *   chunk_min   the edges that such a chunk may have: a row is cut into
+ *               ceil(edges / chunk_min) equal chunks (at most 2048). */
 typedef struct mp_plan_opts {
     int64_t small_max;
     int64_t hub_min;

@@ -19,7 +19,8 @@
 // digit its pass has just sorted by: the element's place says it, and the
 // next pass puts it back (124M edges, 2.4M rows: 15 + 22 + 27 bits).  The last
 // pass writes src and id alone; rowptr comes from where it sees each row
-// start (or from the keys, where rows are many).  (Carrying id as a third array and keeping the sorted keys for rowptr
+// start (or from the keys, where rows are many).  (Carrying id as a third array
+// and keeping the sorted keys for rowptr
 // cost 80 bytes of traffic per edge where this takes 56 to 60: passes of 790,
 // 880 and 898 us on 124M edges -> 601, 663 and 800, rowptr 155 -> 27; CSR with
 // ids and transpose together 6.05 -> 4.85 ms.)
