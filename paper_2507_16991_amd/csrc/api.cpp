@@ -604,20 +604,23 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
     // dependent steps on its own
     auto unroll = [](const Geometry& g) { return (int64_t)(g.S * 8 > 64 ? 64 / g.S : 8); };
     const int64_t step_edges = nar.S * unroll(nar);
-    const int64_t wide_steps = F >= kWideAlways ? 32 * wid.S * unroll(wid) / step_edges : 32;
+    const bool by_wide_cut = F >= kWideAlways && wide_rows(kUseAggregate, MP_SUM, F, x_dtype, 16,
+                                                           RowLengths{N_dst, E, true, 0, 0});
+    const int64_t wide_steps = by_wide_cut ? 32 * wid.S * unroll(wid) / step_edges : 32;
     const int64_t mean = N_dst > 0 ? E / N_dst : 0;
     const bool few_hubs = 32 * step_edges >= 4 * mean;  // long rows are the exception
     // Where the edges do not give enough wavefronts 32 steps, shorter chunks.
-    // With few hubs the longest chain is the call's time: down to the chain of
-    // the small rows, 8 steps at least, and for rows of more than two of these
+    // With few hubs the longest chain is the call's time: down to half the chain
+    // of the small rows, 8 steps at least, and for rows of more than two of these
     // (power-law graph of 120k edges, F = 75: fp32 sum 28 -> 20 us, max 35 -> 25;
-    // below the small rows' chain only the combining of the chunks adds, F = 20,
-    // 20k edges: max 46 -> 49).  Where most rows are long, each chunk costs more than the
-    // filled card gives: a quarter of the wavefronts (1024 segments of 500 rows, F =
-    // 100: statistics 51 -> 40 us; of 2392 rows, F = 16, bf16: 91 -> 62)
+    // 325k edges, 61 a row, F = 171: the sum's training pass 62 -> 56; far below the
+    // small rows' chain only the combining of the chunks adds, F = 20, 20k edges:
+    // max 46 -> 49).  Where most rows are long, each chunk costs more than the filled
+    // card gives: a quarter of the wavefronts (1024 segments of 500 rows, F = 100:
+    // statistics 51 -> 40 us; of 2392 rows, F = 16, bf16: 91 -> 62)
     // (and of rows that go by the wide cut 8 of its steps, up to 32 narrow ones)
-    int64_t least = few_hubs ? 16 * nar.S / unroll(nar) : 8;
-    if (few_hubs && least < wide_steps / 4 && F >= kWideAlways)
+    int64_t least = few_hubs ? 8 * nar.S / unroll(nar) : 8;
+    if (few_hubs && least < wide_steps / 4 && by_wide_cut)
         least = wide_steps / 4 < 32 ? wide_steps / 4 : 32;
     int64_t steps = E / ((few_hubs ? 4096 : 1024) * step_edges);
     if (steps < least) steps = least;
@@ -632,7 +635,7 @@ int mp_spmm_plan_build_opts(const void* rowptr, int rowptr_itype, int64_t N_dst,
     if (steps < steps_fit) steps = steps_fit < wide_steps ? steps_fit : wide_steps;
     if (o.hub_min > 0 || o.chunk_min > 0) steps = wide_steps;
     p->chunk_min = (int)(o.chunk_min > 0 ? o.chunk_min : steps * step_edges);
-    const bool soon = few_hubs && steps < 16 && 2 * steps * step_edges >= 4 * mean;
+    const bool soon = few_hubs && steps < 16 && 2 * steps * step_edges >= 2 * mean;
     p->hub_min = o.hub_min > 0 ? o.hub_min
                                : (soon ? 2 * steps : (steps > 32 ? steps : 32)) * step_edges;
     if (p->hub_min < p->small_max) p->hub_min = p->small_max;
