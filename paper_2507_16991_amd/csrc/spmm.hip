@@ -1689,9 +1689,10 @@ Geometry make_geometry(int64_t F, int x_dtype, uintptr_t x_align, bool wide) {
 // uneven degrees of 4 to 60 edges, 20k to 8M edges, fp32 (bf16):
 //   * 33 features and more over a plan: 0.40 to 1.05 while rows have under 24
 //     edges on average; with 24 and more, F = 47 0.97 to 1.09, F = 50 to 1.14 (F =
-//     47 0.74 to 1.03, F = 50 to 1.09), F = 253 0.95 to 1.08; but F = 75 0.6 to 0.99,
-//     where narrow chunks leave a partly filled tile; F = 101 0.6 to 0.9 on 1M
-//     edges, 1.08 on 8M;
+//     47 0.74 to 1.03, F = 50 to 1.09), F = 253 0.95 to 1.08; but F = 75 0.6 to 0.99
+//     and F = 155 0.7 to 0.9, where narrow chunks leave a partly filled tile; F = 87
+//     to 115 0.6 to 0.9 on 1M edges, on 8M and more 1.02 to 1.08 for sum or max
+//     alone and 0.8 to 1.05 for the fused pair;
 //   * up to 28 features (under eight lanes): sum 0.67 to 0.95 on rows of up to 63
 //     edges (bf16 at 30 edges 0.85 to 0.94 where two or four lanes take a row, to
 //     1.2 where they leave some idle), 1.1 to 2.6 where there are longer ones; max
@@ -1739,8 +1740,11 @@ bool wide_rows(RowUse use, int reduce, int64_t F, int x_dtype, uintptr_t x_align
     }
     if (!many) return true;
     if (bf16) return !pairs || F >= 64;
+    if (g.FT == 1) return false;
+    if (F > 256) return true;
     const int64_t lanes = (int64_t)kWave * g.FT;
-    return g.FT > 1 && (F > 256 || (large ? 2 * lanes >= 3 * g.ltot : 10 * g.ltot < 9 * lanes));
+    const bool both = use == kUseStats || ((reduce & kMax) && (reduce & (kSum | kMean)));
+    return large && g.FT == 2 && !both ? 2 * lanes >= 3 * g.ltot : 10 * g.ltot < 9 * lanes;
 }
 
 hipError_t launch_spmm(const SpmmParams& p, int x_dtype, int epl, hipStream_t s) {
