@@ -538,15 +538,17 @@ struct PlanParams {
     const void* rowptr;
     int rp64;
     int64_t N;
-    int64_t split, small_max, hub_min;  // a class starts after `split` edges too
+    // a class starts after `split` edges too; rows beyond long_min are counted
+    int64_t split, small_max, hub_min, long_min;
     int chunk_min;
     uint32_t* tile_cnt;   // [plan_tile_counts(N)]
     int32_t* rowlist;     // [N] rows by class, then by id
     int32_t* rowbeg;      // [N] their ranges
     int32_t* rowend;      // [N]
     uint32_t* chunk_off;  // [N + 1] first chunk of every hub row's entry; [N]: all chunks
-    // first row-list position of every class, N, the number of chunks
-    uint32_t* header;     // [kPlanClasses + 2]
+    // first row-list position of every class, N, the number of chunks, and of
+    // rows beyond long_min
+    uint32_t* header;     // [kPlanClasses + 3]
 };
 int64_t plan_tile_counts(int64_t N);
 hipError_t launch_plan(const PlanParams& p, hipStream_t s);

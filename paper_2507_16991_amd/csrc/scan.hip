@@ -21,12 +21,14 @@ namespace mp {
 namespace {
 
 constexpr int kPlanItems = 16;  // rows per thread of a full tile
-constexpr int kPlanRows = kPlanClasses + 1;  // scanned rows: the classes' counts, then chunk counts
+// scanned rows: the classes' counts, then the chunks, then the long rows
+constexpr int kPlanRows = kPlanClasses + 2;
 
 struct PlanRow {
     int64_t beg, end;
     uint32_t cls;
     uint32_t chunks;  // 0 unless a hub
+    bool is_long;     // more than long_min edges
 };
 
 // Class of a row: small rows by the bit length of the degree (0 for an empty
@@ -39,6 +41,7 @@ __device__ inline PlanRow plan_row(const IT* __restrict__ rowptr, int64_t i, con
     r.end = (int64_t)rowptr[i + 1];
     const int64_t d = r.end - r.beg;
     r.chunks = 0;
+    r.is_long = d > P.long_min;
     if (d > P.hub_min) {
         r.cls = kClassHub;
         int64_t csz = (d + kMaxChunksPerHub - 1) / kMaxChunksPerHub;
@@ -69,43 +72,48 @@ __device__ inline uint32_t wave_scan(uint32_t v, int lane) {
 }
 
 // tile_cnt[c * tiles + tile] = rows of class c (c < kPlanClasses) in the tile,
-// and in row kPlanClasses its hub rows' chunks.
+// in row kPlanClasses its hub rows' chunks, and in the next its long rows.
 template <typename IT, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void plan_count(const IT* __restrict__ rowptr,
                                                             PlanParams P) {
     __shared__ uint32_t s_cnt[WAVES][32];
-    __shared__ uint32_t s_chunks[WAVES];
+    __shared__ uint32_t s_chunks[WAVES], s_long[WAVES];
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x / kWave;
     if (lane < 32) s_cnt[wv][lane] = 0;
     __builtin_amdgcn_wave_barrier();
     const int64_t base = ((int64_t)blockIdx.x * WAVES + wv) * kPlanItems * kWave;
-    uint32_t chunks = 0;
+    uint32_t chunks = 0, longs = 0;
 #pragma unroll 4
     for (int k = 0; k < kPlanItems; ++k) {
         const int64_t i = base + k * kWave + lane;
         const bool ok = i < P.N;
-        PlanRow r{0, 0, 0, 0};
+        PlanRow r{0, 0, 0, 0, false};
         if (ok) r = plan_row(rowptr, i, P);
         chunks += r.chunks;
+        longs += (uint32_t)__popcll(__ballot(r.is_long));
         const uint64_t peers = digit_peers<kPlanClassBits>(ok, r.cls);
         if (ok && count_below(peers) == 0) s_cnt[wv][r.cls] += (uint32_t)__popcll(peers);
         __builtin_amdgcn_wave_barrier();
     }
     chunks = wave_sum(chunks);
-    if (lane == 0) s_chunks[wv] = chunks;
+    if (lane == 0) {
+        s_chunks[wv] = chunks;
+        s_long[wv] = longs;
+    }
     __syncthreads();
     if (threadIdx.x < kPlanRows) {
         const int c = threadIdx.x;
         uint32_t t = 0;
-        for (int w = 0; w < WAVES; ++w) t += c < kPlanClasses ? s_cnt[w][c] : s_chunks[w];
+        for (int w = 0; w < WAVES; ++w)
+            t += c < kPlanClasses ? s_cnt[w][c] : (c == kPlanClasses ? s_chunks[w] : s_long[w]);
         P.tile_cnt[(int64_t)c * gridDim.x + blockIdx.x] = t;
     }
 }
 
 // In place, every row of tile_cnt: exclusive scan over the tiles (a wavefront
-// per row); header[c] = first row-list position of class c, then N and the
-// number of chunks; chunk_off[N] = the number of chunks.
+// per row); header[c] = first row-list position of class c, then N, the
+// number of chunks and of long rows; chunk_off[N] = the number of chunks.
 __global__ __launch_bounds__(1024) void plan_scan(PlanParams P, int64_t tiles) {
     __shared__ uint32_t s_total[32];
     const int lane = threadIdx.x & (kWave - 1);
@@ -138,6 +146,7 @@ __global__ __launch_bounds__(1024) void plan_scan(PlanParams P, int64_t tiles) {
         if (lane == 0) {
             P.header[kPlanClasses] = (uint32_t)P.N;
             P.header[kPlanClasses + 1] = s_total[kPlanClasses];
+            P.header[kPlanClasses + 2] = s_total[kPlanClasses + 1];
             P.chunk_off[P.N] = s_total[kPlanClasses];
         }
     }
@@ -151,7 +160,7 @@ template <typename IT, int WAVES, bool SINGLE>
 __global__ __launch_bounds__(WAVES * kWave) void plan_scatter(const IT* __restrict__ rowptr,
                                                               PlanParams P, int items) {
     __shared__ uint32_t s_cnt[WAVES][32];  // rows of each class, then where a wave's start
-    __shared__ uint32_t s_chunks[WAVES];
+    __shared__ uint32_t s_chunks[WAVES], s_long[WAVES];
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x / kWave;
     if (lane < 32) s_cnt[wv][lane] = 0;
@@ -159,12 +168,13 @@ __global__ __launch_bounds__(WAVES * kWave) void plan_scatter(const IT* __restri
     const int64_t base = ((int64_t)blockIdx.x * WAVES + wv) * items * kWave;
     PlanRow r[kPlanItems];
     uint32_t rank[kPlanItems], before[kPlanItems];  // before: chunks of earlier hub rows
-    uint32_t chunks = 0;
+    uint32_t chunks = 0, longs = 0;
 #pragma unroll
     for (int k = 0; k < kPlanItems; ++k) {
-        r[k] = PlanRow{0, 0, 0, 0};
+        r[k] = PlanRow{0, 0, 0, 0, false};
         const int64_t i = base + k * kWave + lane;
         if (k < items && i < P.N) r[k] = plan_row(rowptr, i, P);
+        if constexpr (SINGLE) longs += (uint32_t)__popcll(__ballot(r[k].is_long));
     }
 #pragma unroll
     for (int k = 0; k < kPlanItems; ++k) {
@@ -185,7 +195,10 @@ __global__ __launch_bounds__(WAVES * kWave) void plan_scatter(const IT* __restri
             }
         }
     }
-    if (lane == 0) s_chunks[wv] = chunks;
+    if (lane == 0) {
+        s_chunks[wv] = chunks;
+        s_long[wv] = longs;
+    }
     __syncthreads();
     if (threadIdx.x < kWave) {
         // where each class starts for this tile, then for each of its waves
@@ -220,6 +233,9 @@ __global__ __launch_bounds__(WAVES * kWave) void plan_scatter(const IT* __restri
             if constexpr (SINGLE) {
                 P.header[kPlanClasses + 1] = at;
                 P.chunk_off[P.N] = at;
+                uint32_t all = 0;
+                for (int w = 0; w < WAVES; ++w) all += s_long[w];
+                P.header[kPlanClasses + 2] = all;
             }
         }
     }

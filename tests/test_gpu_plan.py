@@ -74,3 +74,27 @@ def test_short_chunks_fit_the_static_scratch(rows, deg, F):
     assert np.array_equal(out.cpu().numpy(), (counts @ xs).astype(np.float32))
     present = np.where(counts[:, :, None] > 0, xs[None], -np.inf)
     assert np.array_equal(mx.cpu().numpy(), present.max(1).astype(np.float32))
+
+
+@pytest.mark.parametrize("N", [2000, 20_000])  # one launch, three
+@pytest.mark.parametrize("longest", [1024, 1025])  # 32 wavefront steps of 32 edges, and more
+def test_short_chunks_only_beside_long_rows(N, longest):
+    """Rows of 16 to 32 steps on a small graph are cut into chunks of 8 steps
+    only where there is a longer row, which is cut anyway."""
+    F = 64
+    deg = np.full(N, 4)
+    deg[[5, N // 2, N - 1]] = [700, 513, 512]
+    deg[77] = longest
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    E = int(rp[-1])
+    rng = np.random.default_rng(N)
+    x = rng.integers(-3, 4, (50, F)).astype(np.float32)
+    col = rng.integers(0, 50, E).astype(np.int32)
+    rp_d = torch.from_numpy(rp).to(DEV, torch.int32)
+    plan = mp.Plan(rp_d, E, F)
+    chunks = 0 if longest <= 1024 else 3 + 3 + 5  # of 700, 513 and 1025 edges by 256
+    assert mp.mp_spmm_workspace(plan.handle, mp.MP_SUM) == chunks * F * 4
+    out, _, _ = mp.spmm(rp_d, torch.from_numpy(col).to(DEV), torch.from_numpy(x).to(DEV), mp.MP_SUM,
+                        plan=plan)
+    sums = np.concatenate([np.zeros((1, F)), np.cumsum(x[col], axis=0, dtype=np.float64)])
+    assert np.array_equal(out.cpu().numpy(), (sums[rp[1:]] - sums[rp[:-1]]).astype(np.float32))
